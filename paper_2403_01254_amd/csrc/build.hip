@@ -6,7 +6,7 @@
 #include <cfloat>
 #include <climits>
 
-#include "rkhsba_device.h"
+#include "block_sort.h"
 
 namespace rkhsba {
 namespace {
@@ -123,25 +123,64 @@ __global__ __launch_bounds__(kThreads) void k_cell_coords(const float* const* __
   }
 }
 
-// Cell key of every point; in a label-stacked frame the class id selects the
-// layer of NZ cells that the point's z cell lies in (kz' = id * NZ + kz).
-__global__ __launch_bounds__(kThreads) void k_cell_keys(const int32_t* __restrict__ cell,
-                                                        const int64_t* __restrict__ off,
-                                                        const FrameInfo* __restrict__ frames, int K, int64_t n_total,
-                                                        const void* const* __restrict__ cls,
-                                                        uint32_t* __restrict__ keys, uint32_t* __restrict__ vals) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= n_total) return;
-  int f;
-  int64_t l;
-  frame_of(off, K, i, f, l);
-  const FrameInfo& F = frames[f];
-  const uint32_t kx = (uint32_t)(cell[3 * i] - F.org[0]);
-  const uint32_t ky = (uint32_t)(cell[3 * i + 1] - F.org[1]);
-  uint32_t kz = (uint32_t)(cell[3 * i + 2] - F.org[2]);
+// Cell key of point l of frame F; in a label-stacked frame the class id selects the layer of NZ cells that the
+// point's z cell lies in (kz' = id * NZ + kz).
+__device__ inline uint32_t cell_key(const int32_t* __restrict__ cell, const FrameInfo& F,
+                                    const void* const* __restrict__ cls, int f, int64_t l) {
+  const int32_t* c = cell + 3 * (F.pt_off + l);
+  const uint32_t kx = (uint32_t)(c[0] - F.org[0]);
+  const uint32_t ky = (uint32_t)(c[1] - F.org[1]);
+  uint32_t kz = (uint32_t)(c[2] - F.org[2]);
   if (F.n_lab > 0) kz += (uint32_t)static_cast<const uint16_t*>(cls[f])[l] * (uint32_t)F.dim[2];
-  keys[i] = (kz * (uint32_t)F.dim[1] + ky) * (uint32_t)F.dim[0] + kx;
-  vals[i] = (uint32_t)l;
+  return (kz * (uint32_t)F.dim[1] + ky) * (uint32_t)F.dim[0] + kx;
+}
+
+// One block per sort tile of a frame: keys, point indices and the tile's histogram of the first digit.
+__global__ __launch_bounds__(kSortThreads) void k_cell_keys(const int32_t* __restrict__ cell,
+                                                            const FrameInfo* __restrict__ frames,
+                                                            const void* const* __restrict__ cls,
+                                                            const SortTile* __restrict__ tiles,
+                                                            uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
+                                                            uint32_t* __restrict__ hist) {
+  __shared__ uint32_t h[256];
+  static_assert(kSortThreads == 256, "one thread per digit");
+  h[threadIdx.x] = 0u;
+  __syncthreads();
+  const SortTile t = tiles[blockIdx.x];
+  const FrameInfo F = frames[t.edge];
+  for (int k = threadIdx.x; k < t.count; k += kSortThreads) {
+    const int64_t i = t.start + k, l = i - F.pt_off;
+    const uint32_t key = cell_key(cell, F, cls, t.edge, l);
+    keys[i] = key;
+    vals[i] = (uint32_t)l;
+    atomicAdd(&h[key & 0xffu], 1u);
+  }
+  __syncthreads();
+  hist[(int64_t)blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
+}
+
+// One workgroup per frame of at most NT * IPT points: keys, and their sort in LDS.
+template <int NT, int IPT>
+__global__ __launch_bounds__(NT) void k_cell_sort(const int32_t* __restrict__ cell,
+                                                  const FrameInfo* __restrict__ frames,
+                                                  const void* const* __restrict__ cls,
+                                                  const SortSeg* __restrict__ segs, int bits,
+                                                  uint32_t* __restrict__ sorted_keys,
+                                                  uint32_t* __restrict__ sorted_vals, int lo, int hi) {
+  __shared__ typename BlockSort<NT, IPT>::Shared sh;
+  const SortSeg S = segs[blockIdx.x];
+  if (S.count <= lo || S.count > hi) return;  // (uniform) sorted in tiles, or by another launch
+  const FrameInfo F = frames[S.owner];
+  const int base = (int)(threadIdx.x >> 6) * 64 * IPT + (int)(threadIdx.x & 63);
+  uint32_t key[IPT];
+#pragma unroll
+  for (int r = 0; r < IPT; ++r)
+    key[r] = base + 64 * r < S.count ? cell_key(cell, F, cls, S.owner, base + 64 * r) : 0u;
+  BlockSort<NT, IPT>::sort(key, S.count, bits, sh);
+  for (int i = threadIdx.x; i < S.count; i += NT) {
+    sorted_keys[S.start + i] = sh.key[i];
+    sorted_vals[S.start + i] = sh.val[i];
+  }
 }
 
 // One block per frame: the first point (frame-local sorted index) of each
@@ -416,12 +455,19 @@ hipError_t launch_cell_coords(const float* const* d_xyz_ptrs, const int64_t* d_i
   return hipGetLastError();
 }
 
-hipError_t launch_cell_keys(const int32_t* d_cell, const int64_t* d_in_off, const FrameInfo* d_frames, int K,
-                            int64_t n_total, const void* const* d_class_ptrs, uint32_t* d_keys, uint32_t* d_vals,
-                            hipStream_t st) {
-  if (n_total > 0)
-    k_cell_keys<<<blocks(n_total), kThreads, 0, st>>>(d_cell, d_in_off, d_frames, K, n_total, d_class_ptrs, d_keys,
-                                                      d_vals);
+hipError_t launch_cell_sort(const int32_t* d_cell, const FrameInfo* d_frames, const void* const* d_class_ptrs,
+                            const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan, int bits,
+                            uint32_t* d_keys, uint32_t* d_vals, uint32_t* d_hist, uint32_t* d_sorted_keys,
+                            uint32_t* d_sorted_vals, hipStream_t st) {
+  if (plan.n_tiles > 0)
+    k_cell_keys<<<(unsigned)plan.n_tiles, kSortThreads, 0, st>>>(d_cell, d_frames, d_class_ptrs, d_tiles, d_keys,
+                                                                 d_vals, d_hist);
+  plan.block_launches([&](int c, int lo, int hi) {
+    const unsigned nb = (unsigned)plan.n_segs;
+    if (c == 0) k_cell_sort<512, 4><<<nb, 512, 0, st>>>(d_cell, d_frames, d_class_ptrs, d_segs, bits, d_sorted_keys, d_sorted_vals, lo, hi);
+    else if (c == 1) k_cell_sort<1024, 8><<<nb, 1024, 0, st>>>(d_cell, d_frames, d_class_ptrs, d_segs, bits, d_sorted_keys, d_sorted_vals, lo, hi);
+    else k_cell_sort<1024, 16><<<nb, 1024, 0, st>>>(d_cell, d_frames, d_class_ptrs, d_segs, bits, d_sorted_keys, d_sorted_vals, lo, hi);
+  });
   return hipGetLastError();
 }
 

@@ -215,7 +215,8 @@ struct SetLayout {
   uint64_t gen = 0;                 // pool generation the tables were built for
   int n_prob = 0, n_max = 0, E = 0;
   int64_t n_entries = 0;
-  int n_pass_total = 0, n_fin_total = 0, n_edge_tiles = 0, n_edge_segs = 0, bin_bits = 3;
+  int n_pass_total = 0, n_fin_total = 0, bin_bits = 3;
+  SortPlan plan;                    // of the binning segments
   bool stacked = false;             // every problem of the set is label-stacked
   struct Group {
     int pass_points, pass0, n_pass;
@@ -225,7 +226,6 @@ struct SetLayout {
   bool clamp = false;
   bool c_positive = false;          // every problem's inner products are > 0 (pair counts need no c != 0 test)
   DBuf<EdgeInfo> d_edges;
-  DBuf<int64_t> d_ent_off;
   DBuf<int32_t> d_fin_off;
   DBuf<SortTile> d_etiles;
   DBuf<SortSeg> d_esegs;
@@ -244,7 +244,6 @@ struct SetLayout {
   bool binned = false;
   uint64_t bin_gen = 0;             // scratch generation it was written under
   const void* bin_sc = nullptr;     // scratch set it lives in
-  const uint32_t* bin_k = nullptr;
   const uint32_t* bin_v = nullptr;
   hipGraphExec_t graph_rest = nullptr;  // iterations after the first of an iterate() call (binning reused)
   uint64_t graph_rest_gen = 0;
@@ -325,8 +324,7 @@ class Engine {
   void set_arena(Arena* a);
   // One evaluation of every item of the set at the device poses: per-edge sums in edge_out.
   // reuse_binning: keep the order of the layout's last binning (its passes stay spatially compact while
-  // the poses move a little) and only recompute which sources fall outside their target grids; done in
-  // full when the scratch no longer holds that binning.
+  // the poses move a little); binned in full when the scratch no longer holds that binning.
   void evaluate(SetLayout& lay, int mode, bool reuse_binning = false);
   // Assembly (+ history entry) of every problem.
   void assemble(SetLayout& lay);
@@ -412,7 +410,6 @@ class Engine {
   EvalScratch own_sc_, arena_sc_;
   EvalScratch* sc_ = &own_sc_;
   Arena* arena_ = nullptr;
-  const uint32_t* sorted_k_ = nullptr;
   const uint32_t* sorted_v_ = nullptr;
   uint64_t scratch_gen_ = 0;  // bumped when a scratch buffer moves
 

@@ -484,29 +484,25 @@ int Engine::add_problem(const ProbParams& par, int K, const int64_t* n_points, c
     RK_HIP(v1_.reserve(N));
     RK_HIP(k2_.reserve(N));
     RK_HIP(v2_.reserve(N));
-    RK_HIP(launch_cell_keys(cell_.p, d_in_off_.p, d_bframes_.p, K, N, d_feat_ptrs_.p, k1_.p, v1_.p, bst));
     std::vector<SortTile> tiles;
-    std::vector<SortSeg> segs(K);
-    for (int f = 0; f < K; ++f) {
-      segs[f].start = off[f];
-      segs[f].count = n_points[f];
-      segs[f].tile0 = (int32_t)tiles.size();
-      for (int64_t s = 0; s < n_points[f]; s += kSortTile)
-        tiles.push_back(SortTile{off[f] + s, (int32_t)std::min<int64_t>(kSortTile, n_points[f] - s), f, f, 0});
-      segs[f].n_tiles = (int32_t)tiles.size() - segs[f].tile0;
-    }
+    std::vector<SortSeg> segs;
+    SortPlan plan;
+    for (int f = 0; f < K; ++f) plan.add(segs, tiles, off[f], n_points[f], f);
     RK_HIP(d_tiles_.reserve(tiles.size()));
     RK_HIP(d_segs_.reserve(K));
     RK_HIP(hist_scratch_.reserve(tiles.size() * 256));
-    RK_HIP(hipMemcpyAsync(d_tiles_.p, tiles.data(), sizeof(SortTile) * tiles.size(), hipMemcpyHostToDevice, bst));
+    if (!tiles.empty())
+      RK_HIP(hipMemcpyAsync(d_tiles_.p, tiles.data(), sizeof(SortTile) * tiles.size(), hipMemcpyHostToDevice, bst));
     RK_HIP(hipMemcpyAsync(d_segs_.p, segs.data(), sizeof(SortSeg) * K, hipMemcpyHostToDevice, bst));
     int key_bits = 1;
     while (key_bits < 32 && (1ull << key_bits) < max_cells) ++key_bits;
-    bool in_tmp = false;
-    RK_HIP(launch_radix_sort(k1_.p, v1_.p, k2_.p, v2_.p, hist_scratch_.p, d_tiles_.p, (int)tiles.size(), d_segs_.p, K,
-                             key_bits, bst, &in_tmp));
+    const bool in_tmp = sort_ends_in_tmp(key_bits);
     uint32_t* sk = in_tmp ? k2_.p : k1_.p;
     uint32_t* sv = in_tmp ? v2_.p : v1_.p;
+    RK_HIP(launch_cell_sort(cell_.p, d_bframes_.p, d_feat_ptrs_.p, d_tiles_.p, d_segs_.p, plan, key_bits, k1_.p,
+                            v1_.p, hist_scratch_.p, sk, sv, bst));
+    RK_HIP(launch_radix_sort(k1_.p, v1_.p, k2_.p, v2_.p, hist_scratch_.p, d_tiles_.p, d_segs_.p, plan, key_bits, true,
+                             true, bst));
     RK_HIP(launch_gather(d_xyz_ptrs_.p, d_feat_ptrs_.p, kind, D, std::max(Dp, 1),
                          d_bframes_.p, d_in_off_.p, K, N, sv, d_pts, d_feat, d_perm, minmax_.p + 6 * K + 1, bst));
     RK_HIP(hipMemcpyAsync(d_keys, sk, sizeof(uint32_t) * N, hipMemcpyDeviceToDevice, bst));
@@ -748,7 +744,7 @@ void Engine::read_history(Problem* p, int count, double* loss, double* pairs) {
 }
 
 void Engine::read_source_counts(Problem* p, int m, int64_t* counts) {
-  RK_REQUIRE(m >= 0 && m < p->K && sorted_k_ && sorted_v_, RKHSBA_ESTATE, "no evaluation to read");
+  RK_REQUIRE(m >= 0 && m < p->K && sorted_v_, RKHSBA_ESTATE, "no evaluation to read");
   const FrameInfo& F = p->frames[m];
   std::vector<uint32_t> c(F.n), v(F.n);
   std::vector<int32_t> perm(F.n);
@@ -841,10 +837,10 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   int E_total = 0;
   for (const SetItem& it : items) E_total += it.E;
   std::vector<EdgeInfo> info(E_total);
-  std::vector<int64_t> ent(E_total);
   std::vector<int32_t> foff(E_total);
   std::vector<SortTile> tiles;
   std::vector<SortSeg> segs;
+  SortPlan plan;
   segs.reserve(E_total);
   std::vector<KConst> kcs(items.size());
   bool all_stacked = !items.empty();
@@ -914,15 +910,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
           parts.emplace_back(0, I.n_src);
         }
         for (const auto& pr : parts) {
-          SortSeg S0;
-          S0.start = entries + pr.first;
-          S0.count = pr.second;
-          S0.tile0 = (int32_t)tiles.size();
-          for (int64_t s = 0; s < pr.second; s += kSortTile)
-            tiles.push_back(SortTile{S0.start + s, (int32_t)std::min<int64_t>(kSortTile, pr.second - s),
-                                     (int32_t)segs.size(), e_glob, 0});
-          S0.n_tiles = (int32_t)tiles.size() - S0.tile0;
-          segs.push_back(S0);
+          plan.add(segs, tiles, entries + pr.first, pr.second, e_glob);
           I.n_pass += (int32_t)((pr.second + P - 1) / P);
         }
       }
@@ -934,7 +922,6 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
       I.prob = (int32_t)pi;
       gcount[gi] += I.n_pass;  // pass0 is assigned below, once every edge's target is known
       egroup[e_glob] = (int8_t)gi;
-      ent[e_glob] = entries;
       foff[e_glob] = I.fin_off;
       entries += I.n_src;
       passes += I.n_pass;
@@ -966,7 +953,6 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   if (blist.empty()) blist.push_back(0);
   if (vlist.empty()) vlist.push_back(0);
   need(lay.d_edges, E_total, "edges");
-  need(lay.d_ent_off, E_total, "ent_off");
   need(lay.d_fin_off, E_total, "fin_off");
   need(lay.d_etiles, tiles.size(), "etiles");
   need(lay.d_esegs, std::max<size_t>(segs.size(), 1), "esegs");
@@ -1007,7 +993,6 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   size_t stage_bytes = 0;
   auto stage_size = [&](size_t bytes) { stage_bytes += (bytes + 255) & ~(size_t)255; };
   stage_size(sizeof(EdgeInfo) * E_total);
-  stage_size(sizeof(int64_t) * E_total);
   stage_size(sizeof(int32_t) * E_total);
   stage_size(sizeof(SortTile) * tiles.size());
   stage_size(sizeof(SortSeg) * segs.size());
@@ -1030,7 +1015,6 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
     stage_off += (bytes + 255) & ~(size_t)255;
   };
   up(lay.d_edges.p, info.data(), sizeof(EdgeInfo) * E_total);
-  up(lay.d_ent_off.p, ent.data(), sizeof(int64_t) * E_total);
   up(lay.d_fin_off.p, foff.data(), sizeof(int32_t) * E_total);
   up(lay.d_etiles.p, tiles.data(), sizeof(SortTile) * tiles.size());
   up(lay.d_esegs.p, segs.data(), sizeof(SortSeg) * segs.size());
@@ -1081,8 +1065,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   lay.n_pass_total = (int)passes;
   lay.groups = std::move(groups);
   lay.n_fin_total = (int)fins;
-  lay.n_edge_tiles = (int)tiles.size();
-  lay.n_edge_segs = (int)segs.size();
+  lay.plan = plan;
   lay.stacked = all_stacked;
   lay.bin_bits = bin_bits;
   lay.clamp = clamp;
@@ -1107,27 +1090,18 @@ void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning) {
   const bool reuse = reuse_binning && lay.binned && binned_lay_ == &lay && lay.bin_sc == sc_ &&
                      lay.bin_gen == scratch_gen_;
   if (reuse) {
-    sorted_k_ = lay.bin_k;
+    // nothing to bin: the sweeps test the target grid from the transformed points themselves
     sorted_v_ = lay.bin_v;
-    // The keys are read only for their out-of-grid bit, and only by the per-point walks and the larger passes:
-    // the tiled sweeps test the grid from the transformed point themselves.
-    bool keys_read = false;
-    for (const SetLayout::Group& gr : lay.groups) keys_read = keys_read || !tiled_sweep(gr.pass_points, feat_kind);
-    if (keys_read)
-      RK_HIP(launch_bin(pts(), frames(), lay.d_edges.p, lay.d_etiles.p, lay.n_edge_tiles, sc_->xf.p, lay.d_kcs.p,
-                        const_cast<uint32_t*>(sorted_k_), const_cast<uint32_t*>(sorted_v_), true, st));
   } else {
-    RK_HIP(launch_bin(pts(), frames(), lay.d_edges.p, lay.d_etiles.p, lay.n_edge_tiles, sc_->xf.p, lay.d_kcs.p,
-                      sc_->bk.p, sc_->bv.p, false, st));
-    bool in_tmp = false;
+    uint32_t* sorted = sort_ends_in_tmp(lay.bin_bits) ? sc_->bv2.p : sc_->bv.p;
+    RK_HIP(launch_bin(pts(), frames(), lay.d_edges.p, lay.d_etiles.p, lay.d_esegs.p, lay.plan, sc_->xf.p, lay.d_kcs.p,
+                      lay.bin_bits, sc_->bk.p, sc_->bv.p, sc_->bhist.p, sorted, st));
     RK_HIP(launch_radix_sort(sc_->bk.p, sc_->bv.p, sc_->bk2.p, sc_->bv2.p, sc_->bhist.p, lay.d_etiles.p,
-                             lay.n_edge_tiles, lay.d_esegs.p, lay.n_edge_segs, lay.bin_bits, st, &in_tmp));
-    sorted_k_ = in_tmp ? sc_->bk2.p : sc_->bk.p;
-    sorted_v_ = in_tmp ? sc_->bv2.p : sc_->bv.p;
+                             lay.d_esegs.p, lay.plan, lay.bin_bits, true, false, st));
+    sorted_v_ = sorted;
     lay.binned = true;
     lay.bin_gen = scratch_gen_;
     lay.bin_sc = sc_;
-    lay.bin_k = sorted_k_;
     lay.bin_v = sorted_v_;
     binned_lay_ = &lay;
   }
@@ -1140,7 +1114,6 @@ void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning) {
   pa.frames = frames();
   pa.edges = lay.d_edges.p;
   pa.xf = sc_->xf.p;
-  pa.keys = sorted_k_;
   pa.vals = sorted_v_;
   pa.mom = sc_->mom.p;
   pa.cnt = sc_->cnt.p;
@@ -1171,7 +1144,6 @@ void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning) {
   fa.edges = lay.d_edges.p;
   fa.xf = sc_->xf.p;
   fa.frames = frames();
-  fa.keys = sorted_k_;
   fa.vals = sorted_v_;
   fa.mom = sc_->mom.p;
   fa.cnt = sc_->cnt.p;

@@ -22,7 +22,7 @@
 // perturbations, Sec. V-A) in FP64, and reduces them per block of 256 points.
 #include <cfloat>
 
-#include "rkhsba_device.h"
+#include "block_sort.h"
 
 namespace rkhsba {
 namespace {
@@ -81,47 +81,84 @@ __global__ void k_edge_setup(const double* __restrict__ poses, const EdgeInfo* _
   xf[e] = o;
 }
 
-// One block per sort tile (kSortTile consecutive entries of one edge): the
-// Morton code of each source point's target-frame cell, clamped to the grid
-// and its margin of reach cells, with kInvalidBit set when the point lies
-// beyond them (it has no pair).  SORTED: the entries already hold sorted
-// source indices (an earlier binning of the same set); only keys are written.
-template <bool SORTED>
+// Binning key of a source point (frame-local sorted index src of frame Fm): the Morton code of its target-frame
+// cell, clamped to the grid and its margin of reach cells, at the resolution of the frame's sub-cells.
+__device__ inline uint32_t bin_key(const float4* __restrict__ pts, const FrameInfo& Fm, const FrameInfo& Fn,
+                                   const EdgeXf& X, const KConst& kc, uint32_t src) {
+  const int r = kc.reach_cells;
+  const int lim = 1 << 30;
+  const float4 x = pts[Fm.pt_off + src];
+  const float3 q = rule_q32(X, x.x, x.y, x.z);
+  // sub-cell coordinates: scaling by 2^key_sub is exact, so a sub-cell coordinate shifted right by key_sub is
+  // the point's cell coordinate
+  const double u[3] = {(double)q.x * kc.inv_cell - Fn.org[0], (double)q.y * kc.inv_cell - Fn.org[1],
+                       (double)q.z * kc.inv_cell - Fn.org[2]};
+  const int sub = Fn.key_sub;
+  uint32_t kk[3];
+  for (int a = 0; a < 3; ++a) {
+    const int top = Fn.dim[a] + 2 * r - 1;
+    const int cf = clamp_floor(u[a] * (double)(1 << sub), -lim, lim) + (r << sub);
+    kk[a] = (uint32_t)min(max(cf, 0), ((top + 1) << sub) - 1) >> Fn.mort_shift;
+  }
+  return morton3(kk[0], kk[1], kk[2]);
+}
+
+// One block per sort tile (kSortTile consecutive entries of one segment): keys, source indices and the tile's
+// histogram of the first digit.
 __global__ __launch_bounds__(kSortThreads) void k_bin(const float4* __restrict__ pts,
                                                       const FrameInfo* __restrict__ frames,
                                                       const EdgeInfo* __restrict__ edges,
                                                       const SortTile* __restrict__ tiles,
                                                       const EdgeXf* __restrict__ xf, const KConst* __restrict__ kcs,
-                                                      uint32_t* __restrict__ keys, uint32_t* __restrict__ vals) {
+                                                      uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
+                                                      uint32_t* __restrict__ hist) {
+  __shared__ uint32_t h[256];
+  static_assert(kSortThreads == 256, "one thread per digit");
+  h[threadIdx.x] = 0u;
+  __syncthreads();
   const SortTile t = tiles[blockIdx.x];
-  const int e = t.edge;
-  const EdgeInfo ed = edges[e];
+  const EdgeInfo ed = edges[t.edge];
   const KConst kc = kcs[ed.prob];
   const FrameInfo Fm = frames[ed.m];
   const FrameInfo Fn = frames[ed.n];
-  const EdgeXf X = xf[e];
-  const int r = kc.reach_cells;
-  const int lim = 1 << 30;
+  const EdgeXf X = xf[t.edge];
   for (int k = threadIdx.x; k < t.count; k += kSortThreads) {
     const int64_t i = t.start + k;
-    const uint32_t src = SORTED ? vals[i] : (uint32_t)(i - ed.ent_off);
-    const float4 x = pts[Fm.pt_off + src];
-    const float3 q = rule_q32(X, x.x, x.y, x.z);
-    // cell coordinates (validity) and sub-cell coordinates (the key): scaling by 2^key_sub is exact, so a
-    // sub-cell coordinate shifted right by key_sub is its cell coordinate
-    const double u[3] = {(double)q.x * kc.inv_cell - Fn.org[0], (double)q.y * kc.inv_cell - Fn.org[1],
-                         (double)q.z * kc.inv_cell - Fn.org[2]};
-    const int sub = Fn.key_sub;
-    const uint32_t invalid = source_in_grid(q, Fn, kc) ? 0u : kInvalidBit;
-    uint32_t kk[3];
-    for (int a = 0; a < 3; ++a) {
-      const int top = Fn.dim[a] + 2 * r - 1;
-      const int cf = clamp_floor(u[a] * (double)(1 << sub), -lim, lim) + (r << sub);
-      kk[a] = (uint32_t)min(max(cf, 0), ((top + 1) << sub) - 1) >> Fn.mort_shift;
-    }
-    keys[i] = invalid | morton3(kk[0], kk[1], kk[2]);
-    if constexpr (!SORTED) vals[i] = src;
+    const uint32_t src = (uint32_t)(i - ed.ent_off);
+    const uint32_t key = bin_key(pts, Fm, Fn, X, kc, src);
+    keys[i] = key;
+    vals[i] = src;
+    atomicAdd(&h[key & 0xffu], 1u);
   }
+  __syncthreads();
+  hist[(int64_t)blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
+}
+
+// One workgroup per segment of at most NT * IPT entries: keys, and their sort in LDS.  All digits take one launch
+// and no pass over memory, where the tiled sort takes two launches per digit: latency bound either way (2 frames x
+// 1,000 points, three digits: 10 launches, 40 us of kernels -> 1 launch, 9 us).
+template <int NT, int IPT>
+__global__ __launch_bounds__(NT) void k_bin_sort(const float4* __restrict__ pts, const FrameInfo* __restrict__ frames,
+                                                 const EdgeInfo* __restrict__ edges,
+                                                 const SortSeg* __restrict__ segs, const EdgeXf* __restrict__ xf,
+                                                 const KConst* __restrict__ kcs, int bits,
+                                                 uint32_t* __restrict__ sorted, int lo, int hi) {
+  __shared__ typename BlockSort<NT, IPT>::Shared sh;
+  const SortSeg S = segs[blockIdx.x];
+  if (S.count <= lo || S.count > hi) return;  // (uniform) sorted in tiles, or by another launch
+  const EdgeInfo ed = edges[S.owner];
+  const KConst kc = kcs[ed.prob];
+  const FrameInfo Fm = frames[ed.m];
+  const FrameInfo Fn = frames[ed.n];
+  const EdgeXf X = xf[S.owner];
+  const uint32_t src0 = (uint32_t)(S.start - ed.ent_off);
+  const int base = (int)(threadIdx.x >> 6) * 64 * IPT + (int)(threadIdx.x & 63);
+  uint32_t key[IPT];
+#pragma unroll
+  for (int r = 0; r < IPT; ++r)
+    key[r] = base + 64 * r < S.count ? bin_key(pts, Fm, Fn, X, kc, src0 + (uint32_t)(base + 64 * r)) : 0u;
+  BlockSort<NT, IPT>::sort(key, S.count, bits, sh);
+  for (int i = threadIdx.x; i < S.count; i += NT) sorted[S.start + i] = src0 + sh.val[i];
 }
 
 // ---------------------------------------------------------------- pass table
@@ -179,17 +216,14 @@ __global__ __launch_bounds__(kThreads) void k_pairs(PairArgs a) {
   const int64_t entry = pi.entry0 + s;
   const bool in_range = s < pi.count;
   bool valid = in_range;
-  uint32_t src = 0;
-  if (valid) {
-    valid = !(a.keys[entry] & kInvalidBit);
-    src = a.vals[entry];
-  }
+  const uint32_t src = in_range ? a.vals[entry] : 0u;
   float3 q = make_float3(0.f, 0.f, 0.f);
   uint32_t lbl = 0;
   float fs[DP > 0 ? DP : 1];
   if (valid) {
     const float4 x = a.pts[pi.src_off + src];
     q = rule_q32(X, x.x, x.y, x.z);
+    valid = source_in_grid(q, Fn, kc);
     lbl = __float_as_uint(x.w);
     if constexpr (FEAT != FEAT_CLASS) load_feature_row<FEAT, DP>(a.feat, pi.src_off + src, fs);
   }
@@ -730,15 +764,18 @@ hipError_t launch_edge_setup(const double* d_poses, const EdgeInfo* d_edges, int
 }
 
 hipError_t launch_bin(const float4* d_pts, const FrameInfo* d_frames, const EdgeInfo* d_edges,
-                      const SortTile* d_tiles, int n_tiles, const EdgeXf* d_xf, const KConst* d_kcs, uint32_t* d_keys,
-                      uint32_t* d_vals, bool rebin_sorted, hipStream_t st) {
-  if (n_tiles <= 0) return hipSuccess;
-  if (rebin_sorted)
-    k_bin<true><<<(unsigned)n_tiles, kSortThreads, 0, st>>>(d_pts, d_frames, d_edges, d_tiles, d_xf, d_kcs, d_keys,
-                                                            d_vals);
-  else
-    k_bin<false><<<(unsigned)n_tiles, kSortThreads, 0, st>>>(d_pts, d_frames, d_edges, d_tiles, d_xf, d_kcs, d_keys,
-                                                             d_vals);
+                      const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan, const EdgeXf* d_xf,
+                      const KConst* d_kcs, int bits, uint32_t* d_keys, uint32_t* d_vals, uint32_t* d_hist,
+                      uint32_t* d_sorted, hipStream_t st) {
+  if (plan.n_tiles > 0)
+    k_bin<<<(unsigned)plan.n_tiles, kSortThreads, 0, st>>>(d_pts, d_frames, d_edges, d_tiles, d_xf, d_kcs, d_keys,
+                                                           d_vals, d_hist);
+  plan.block_launches([&](int c, int lo, int hi) {
+    const unsigned nb = (unsigned)plan.n_segs;
+    if (c == 0) k_bin_sort<512, 4><<<nb, 512, 0, st>>>(d_pts, d_frames, d_edges, d_segs, d_xf, d_kcs, bits, d_sorted, lo, hi);
+    else if (c == 1) k_bin_sort<1024, 8><<<nb, 1024, 0, st>>>(d_pts, d_frames, d_edges, d_segs, d_xf, d_kcs, bits, d_sorted, lo, hi);
+    else k_bin_sort<1024, 16><<<nb, 1024, 0, st>>>(d_pts, d_frames, d_edges, d_segs, d_xf, d_kcs, bits, d_sorted, lo, hi);
+  });
   return hipGetLastError();
 }
 

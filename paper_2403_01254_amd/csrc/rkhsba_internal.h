@@ -17,10 +17,6 @@
 
 namespace rkhsba {
 
-// Binning keys: a 30-bit Morton code of the source point's target-frame cell (clamped to the grid and its
-// margin), with this bit set when the point lies outside both (it has no pair).  The sort orders the code
-// bits only, so a point keeps its place when a later evaluation with the same binning flips the bit.
-constexpr uint32_t kInvalidBit = 0x80000000u;
 constexpr int kMaxDense = 64;
 
 enum Mode { MODE_LOSS = 0, MODE_NORMAL = 1 };
@@ -113,20 +109,74 @@ struct SortTile {
 };
 struct SortSeg {
   int64_t start;
-  int64_t count;
+  int32_t count;     // elements (a frame's or a class id's points, < 2^31)
+  int32_t owner;     // edge of the binning entries (edge sorts), or the frame (point sorts)
   int32_t tile0;     // first tile
-  int32_t n_tiles;
+  int32_t n_tiles;   // 0: sorted by one workgroup in LDS (at most kBlockSortMax elements)
 };
 constexpr int kSortThreads = 256;
 constexpr int kSortItems = 8;
 constexpr int kSortTile = kSortThreads * kSortItems;
+// Segments of at most this many elements are sorted by one workgroup in LDS, in one launch for all digits; larger
+// ones in tiles, two launches per digit.  The limit is what one workgroup's 160 KB hold (6 B per element and the
+// digit counters).
+constexpr int kBlockSortMax = 16384;
+
+// How the segments of one launch are sorted (host-side counts of a segment table).
+struct SortPlan {
+  int n_segs = 0;
+  int n_tiles = 0;        // tiles of the segments above kBlockSortMax
+  int max_seg_tiles = 0;  // most tiles of one segment
+  int max_block = 0;      // largest segment sorted by one workgroup (0: none)
+  int n_class[3] = {0, 0, 0};  // segments per workgroup size (block_class)
+  // Workgroups of 512 threads x 4 elements, 1024 x 8 and 1024 x 16.
+  static int block_class(int count) { return count <= 2048 ? 0 : count <= 8192 ? 1 : 2; }
+  // Runs launch(class, lo, hi) for the segments of lo < count <= hi.  A few segments (up to one per CU) take one
+  // launch of the largest segment's workgroup: they run side by side, and a launch costs more than a workgroup
+  // larger than its segment.  Many take one launch per workgroup size, so that the small ones do not hold the
+  // large ones' LDS.  (LiDAR, 64 x 100,000 points, 7,680 class-id segments: build and binning sorts 1.72 ms per
+  // solve in tiles, 1.26 ms with these.)
+  template <typename Launch>
+  void block_launches(Launch&& launch) const {
+    const int hi[3] = {2048, 8192, kBlockSortMax};
+    if (max_block <= 0) return;
+    if (n_segs <= 256) return launch(block_class(max_block), 0, kBlockSortMax);
+    for (int c = 0; c < 3; ++c)
+      if (n_class[c] > 0) launch(c, c > 0 ? hi[c - 1] : 0, hi[c]);
+  }
+  // Adds a segment of `count` elements; fills its tile range and appends its tiles.
+  template <typename Tiles, typename Segs>
+  void add(Segs& segs, Tiles& tiles, int64_t start, int64_t count, int32_t owner) {
+    SortSeg S{};
+    S.start = start;
+    S.count = (int32_t)count;
+    S.owner = owner;
+    S.tile0 = n_tiles;
+    if (count > kBlockSortMax) {
+      for (int64_t s = 0; s < count; s += kSortTile)
+        tiles.push_back(SortTile{start + s, (int32_t)(count - s < kSortTile ? count - s : kSortTile), n_segs, owner, 0});
+      S.n_tiles = (int32_t)((count + kSortTile - 1) / kSortTile);
+      n_tiles += S.n_tiles;
+      if (S.n_tiles > max_seg_tiles) max_seg_tiles = S.n_tiles;
+    } else {
+      if (S.count > max_block) max_block = S.count;
+      ++n_class[block_class(S.count)];
+    }
+    segs.push_back(S);
+    ++n_segs;
+  }
+};
 
 // ---------------------------------------------------------------- launchers
 // Each returns hipSuccess or the first HIP error.  All run on `st`.
 
+// Digit passes of the tiled segments, over key bits [0, bits).  hist0: the tiles' counts of digit 0 are in
+// `hist` already.  keep_keys: the sorted keys are wanted too, not only the values.  The result ends in (keys, vals) or, for an odd number of digits, in (keys_tmp, vals_tmp):
+// sort_ends_in_tmp(bits).
 hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp,
-                             uint32_t* hist, const SortTile* d_tiles, int n_tiles, const SortSeg* d_segs,
-                             int n_segs, int bits, hipStream_t st, bool* result_in_tmp);
+                             uint32_t* hist, const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan,
+                             int bits, bool hist0, bool keep_keys, hipStream_t st);
+inline bool sort_ends_in_tmp(int bits) { return (((bits + 7) / 8) & 1) != 0; }
 
 hipError_t launch_exclusive_scan(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* tmp, uint64_t* d_total,
                                  hipStream_t st);
@@ -139,10 +189,13 @@ int dense_pad(int D, int feat_path);
 hipError_t launch_cell_coords(const float* const* d_xyz_ptrs, const int64_t* d_in_off, int K, int64_t n_total,
                               double inv_cell, const void* const* d_class_ptrs, int32_t* d_cell, int32_t* d_minmax,
                               int32_t* d_label_max, hipStream_t st);
-// Cell keys; frames with n_lab > 0 take the class ids (d_class_ptrs) into kz'.
-hipError_t launch_cell_keys(const int32_t* d_cell, const int64_t* d_in_off, const FrameInfo* d_frames, int K,
-                            int64_t n_total, const void* const* d_class_ptrs, uint32_t* d_keys, uint32_t* d_vals,
-                            hipStream_t st);
+// Cell keys (frames with n_lab > 0 take the class ids, d_class_ptrs, into kz') and their sort by frame, stable.
+// Frames of at most kBlockSortMax points end in (d_sorted_keys, d_sorted_vals) at once; the keys and values of the
+// others are left in (d_keys, d_vals), with their tiles' counts of digit 0, for launch_radix_sort.
+hipError_t launch_cell_sort(const int32_t* d_cell, const FrameInfo* d_frames, const void* const* d_class_ptrs,
+                            const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan, int bits,
+                            uint32_t* d_keys, uint32_t* d_vals, uint32_t* d_hist, uint32_t* d_sorted_keys,
+                            uint32_t* d_sorted_vals, hipStream_t st);
 // For every label-stacked frame f (frame-local key order) and class id l in [0, n_lab]: the first point
 // of layer l (l = n_lab: the frame's count), at d_out[d_lab_off[f] + l].
 hipError_t launch_label_starts(const uint32_t* d_keys, const FrameInfo* d_frames, const int64_t* d_lab_off, int K,
@@ -168,12 +221,13 @@ hipError_t launch_frame_centroid(const float4* d_pts, int n, double* d_out, hipS
 hipError_t launch_fill_passes(const EdgeInfo* d_edges, int E, const FrameInfo* d_frames, const SortSeg* d_segs,
                               PassInfo* d_passes, hipStream_t st);
 hipError_t launch_edge_setup(const double* d_poses, const EdgeInfo* d_edges, int E, EdgeXf* d_xf, hipStream_t st);
-// Binning keys and source indices of every entry, one block per sort tile of an edge.  rebin_sorted: the
-// entries hold the sorted source indices of an earlier binning (d_vals, read only); only the keys, and with
-// them the invalid bits, are recomputed at the current transforms.
+// Source binning.  Segments of at most kBlockSortMax entries: keys and sort in one workgroup each, their sorted
+// source indices written to d_sorted.  The others: keys and source indices of every entry, one block per tile,
+// with the tile's counts of digit 0, for launch_radix_sort.
 hipError_t launch_bin(const float4* d_pts, const FrameInfo* d_frames, const EdgeInfo* d_edges,
-                      const SortTile* d_tiles, int n_tiles, const EdgeXf* d_xf, const KConst* d_kcs, uint32_t* d_keys,
-                      uint32_t* d_vals, bool rebin_sorted, hipStream_t st);
+                      const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan, const EdgeXf* d_xf,
+                      const KConst* d_kcs, int bits, uint32_t* d_keys, uint32_t* d_vals, uint32_t* d_hist,
+                      uint32_t* d_sorted, hipStream_t st);
 
 struct PairArgs {
   const float4* pts;
@@ -183,8 +237,7 @@ struct PairArgs {
   const FrameInfo* frames;
   const EdgeInfo* edges;
   const EdgeXf* xf;
-  const uint32_t* keys;   // sorted binning keys
-  const uint32_t* vals;   // sorted binning values (source point, frame-local sorted index)
+  const uint32_t* vals;   // source points in binning order (frame-local sorted index)
   float* mom;             // moments, component-major: mom[c * n_entries + entry]
   uint32_t* cnt;          // in-radius pair count per entry
   const KConst* kcs;      // per problem of the set, indexed by EdgeInfo::prob
@@ -213,7 +266,6 @@ struct FinArgs {
   const EdgeInfo* edges;
   const EdgeXf* xf;
   const FrameInfo* frames;
-  const uint32_t* keys;
   const uint32_t* vals;
   const float* mom;
   const uint32_t* cnt;

@@ -27,7 +27,7 @@
 //      source walks the rows of its own ball, its lanes splitting the rows.
 #include <cfloat>
 
-#include "rkhsba_device.h"
+#include "block_sort.h"
 
 namespace rkhsba {
 namespace {
@@ -96,19 +96,6 @@ __device__ inline T xor_add(T v) {
   }
 }
 
-// Inclusive add-scan of unsigned values over the wavefront's 64 lanes, in the same DPP steps as the max-scan
-// below (row shifts, then the last lane of a row added to the rows after it).
-__device__ inline uint32_t wave_inclusive_scan(uint32_t v) {
-  int m = (int)v;
-  m += __builtin_amdgcn_update_dpp(0, m, 0x111, 0xf, 0xf, true);   // row_shr:1
-  m += __builtin_amdgcn_update_dpp(0, m, 0x112, 0xf, 0xf, true);   // row_shr:2
-  m += __builtin_amdgcn_update_dpp(0, m, 0x114, 0xf, 0xf, true);   // row_shr:4
-  m += __builtin_amdgcn_update_dpp(0, m, 0x118, 0xf, 0xf, true);   // row_shr:8
-  m += __builtin_amdgcn_update_dpp(0, m, 0x142, 0xa, 0xf, false);  // row_bcast:15
-  m += __builtin_amdgcn_update_dpp(0, m, 0x143, 0xc, 0xf, false);  // row_bcast:31
-  return (uint32_t)m;
-}
-
 // Inclusive max-scan of unsigned values over the wavefront's 64 lanes: four
 // row shifts within each row of 16 lanes, then the last lane of a row
 // broadcast to the rows after it.  Lanes a shift leaves without a source read
@@ -141,15 +128,6 @@ __device__ inline floatx4 tile_products(const float* __restrict__ tfeat, int s, 
 #pragma unroll
   for (int k = 0; k < DP / 4; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[k], fsrc[k], acc, 0, 0, 0);
   return acc;
-}
-
-// Orders LDS accesses between the lanes of the workgroup, which is one
-// wavefront: its LDS operations are carried out in issue order, so only the
-// compiler must not move them across this point.
-__device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // The same products for feature rows stored in bfloat16 or fp8 e4m3: one
