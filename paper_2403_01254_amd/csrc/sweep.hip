@@ -25,92 +25,10 @@
 //   5. Spread passes (class ids): a pass whose box is wider than a few r_c
 //      (isolated outliers, jumps of the Morton order) skips steps 1-3: each
 //      source walks the rows of its own ball, its lanes splitting the rows.
-#include <cfloat>
-
-#include "block_sort.h"
+#include "sweep_device.h"
 
 namespace rkhsba {
 namespace {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr int kLanes = 64;
-constexpr int kTile = 64;
-
-__device__ inline int clamp_floor_d(double v, int lo, int hi) {
-  v = floor(v);
-  v = fmin(fmax(v, (double)lo), (double)hi);
-  return (int)v;
-}
-
-__device__ inline float uniform_f(float v) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
-}
-
-// Cross-lane moves within rows of 16 lanes (DPP: no LDS round trip).
-template <int CTRL>
-__device__ inline float dpp_f(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-constexpr int kDppXor1 = 0xb1;         // quad_perm [1,0,3,2]
-constexpr int kDppXor2 = 0x4e;         // quad_perm [2,3,0,1]
-constexpr int kDppHalfMirror = 0x141;  // lane i <-> 7 - i within each half row
-constexpr int kDppMirror = 0x140;      // lane i <-> 15 - i within each row
-constexpr int kDppRor8 = 0x128;        // lane i <- lane (i + 8) mod 16 within each row, i.e. i ^ 8
-
-// Minimum / maximum over the P consecutive lanes of each lane group (P = 8, 16 or 32): the quad, then the
-// other quad of the half row, then the other half row, then the other row of the 32.
-template <int P>
-__device__ inline float group_min(float v) {
-  static_assert(P == 8 || P == 16 || P == 32, "groups of 8, 16 or 32 lanes");
-  v = fminf(v, dpp_f<kDppXor1>(v));
-  v = fminf(v, dpp_f<kDppXor2>(v));
-  v = fminf(v, dpp_f<kDppHalfMirror>(v));
-  if constexpr (P >= 16) v = fminf(v, dpp_f<kDppMirror>(v));
-  if constexpr (P == 32) v = fminf(v, __shfl_xor(v, 16, 64));
-  return v;
-}
-template <int P>
-__device__ inline float group_max(float v) {
-  static_assert(P == 8 || P == 16 || P == 32, "groups of 8, 16 or 32 lanes");
-  v = fmaxf(v, dpp_f<kDppXor1>(v));
-  v = fmaxf(v, dpp_f<kDppXor2>(v));
-  v = fmaxf(v, dpp_f<kDppHalfMirror>(v));
-  if constexpr (P >= 16) v = fmaxf(v, dpp_f<kDppMirror>(v));
-  if constexpr (P == 32) v = fmaxf(v, __shfl_xor(v, 16, 64));
-  return v;
-}
-
-// v + (v of lane ^ O), the same sum in both lanes (addition is commutative): a DPP row rotation for O = 8,
-// a cross-lane read through the LDS crossbar for 16 and 32.
-template <int O, typename T>
-__device__ inline T xor_add(T v) {
-  static_assert(O == 8 || O == 16 || O == 32, "lane distance");
-  if constexpr (O == 8) {
-    const uint32_t u = __builtin_bit_cast(uint32_t, v);
-    return v + __builtin_bit_cast(T, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u, kDppRor8, 0xf, 0xf, false));
-  } else {
-    return v + __shfl_xor(v, O, 64);
-  }
-}
-
-// Inclusive max-scan of unsigned values over the wavefront's 64 lanes: four
-// row shifts within each row of 16 lanes, then the last lane of a row
-// broadcast to the rows after it.  Lanes a shift leaves without a source read
-// the identity 0.
-__device__ inline uint32_t wave_inclusive_max(uint32_t v) {
-  const int x = (int)v;
-  int m = x;
-  m = (int)max((uint32_t)m, (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x111, 0xf, 0xf, true));  // row_shr:1
-  m = (int)max((uint32_t)m, (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x112, 0xf, 0xf, true));  // row_shr:2
-  m = (int)max((uint32_t)m, (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x114, 0xf, 0xf, true));  // row_shr:4
-  m = (int)max((uint32_t)m, (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x118, 0xf, 0xf, true));  // row_shr:8
-  m = (int)max((uint32_t)m, (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x142, 0xa, 0xf, false));  // row_bcast:15
-  m = (int)max((uint32_t)m, (uint32_t)__builtin_amdgcn_update_dpp(0, m, 0x143, 0xc, 0xf, false));  // row_bcast:31
-  return (uint32_t)m;
-}
 
 // Feature inner products of one 16-candidate sub-tile with the pass's 16
 // source points: D[cand 4(l/16)+r][source l%16] += F_cand[., 4k + l/16] *
@@ -134,7 +52,6 @@ __device__ inline floatx4 tile_products(const float* __restrict__ tfeat, int s, 
 // 16x16x32 MFMA (FP32 accumulation) per 32 feature dimensions.  Lane (s, g)
 // supplies elements 8g..8g+7 of the slice, of candidate 16 sub + s (A, from
 // the LDS tile, RB bytes per row) and of its own source point (B, registers).
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short shortx8 __attribute__((ext_vector_type(8)));
 
 template <int FEAT, int DP, int RB>
@@ -157,17 +74,6 @@ __device__ inline floatx4 tile_products_lp(const uint8_t* __restrict__ tl, int s
     }
   }
   return acc;
-}
-
-// Squared distance of candidate z to the box [lo, hi], rounded like the membership rule: each axis term
-// max(lo - z, z - hi, 0) and the fused sum in rule_s2's order.  Rounding is monotone, so for every point q of
-// the box this is at most rule_s2(q, z): a candidate above rc2 here fails the rule for every source in the box.
-__device__ inline float box_s2(float3 lo, float3 hi, float4 z) {
-#pragma clang fp contract(off)
-  const float bx = fmaxf(fmaxf(lo.x - z.x, z.x - hi.x), 0.f);
-  const float by = fmaxf(fmaxf(lo.y - z.y, z.y - hi.y), 0.f);
-  const float bz = fmaxf(fmaxf(lo.z - z.z, z.z - hi.z), 0.f);
-  return fmaf(bz, bz, fmaf(by, by, bx * bx));
 }
 
 // MM: the moments are accumulated on the matrix core.  With u = z - ref (ref =
@@ -294,12 +200,8 @@ __global__ __launch_bounds__(kLanes) void k_sweep(PairArgs a) {
   };
 
   const double inv = kc.inv_cell, cell = kc.cell, reach = kc.reach;
-  const int z0 = max(clamp_floor_d(((double)lo.z - reach) * inv - Fn.org[2], -1, Fn.dim[2]), 0);
-  const int z1 = min(clamp_floor_d(((double)hi.z + reach) * inv - Fn.org[2], -1, Fn.dim[2]), Fn.dim[2] - 1);
-  const int y0 = max(clamp_floor_d(((double)lo.y - reach) * inv - Fn.org[1], -1, Fn.dim[1]), 0);
-  const int y1 = min(clamp_floor_d(((double)hi.y + reach) * inv - Fn.org[1], -1, Fn.dim[1]), Fn.dim[1] - 1);
-  const int ny = y1 - y0 + 1;
-  int n_rows = (z1 >= z0 && y1 >= y0) ? (z1 - z0 + 1) * ny : 0;
+  const RowBox rbx = row_box(Fn, kc, lo, hi);
+  int n_rows = rbx.n;
   // rows of the label layer the pass walks in a label-stacked target frame: the sources of a pass share
   // one class id (passes never straddle a class id of a stacked source frame)
   const int64_t lrow = label_rows(Fn, (uint32_t)__builtin_amdgcn_readlane((int)lbl, __builtin_ctzll(__ballot(valid))));
@@ -492,30 +394,24 @@ __global__ __launch_bounds__(kLanes) void k_sweep(PairArgs a) {
   };
 
   uint32_t head = 0, tail = 0;  // CF: the ring holds the kept candidates head .. tail - 1 (uniform)
+  uint64_t batches = 0;  // of the 64 batches of 64 rows that rb lies in: those with a row near a source
   for (int rb = 0; rb < n_rows; rb += kLanes) {
+    // (class ids: the ring takes every candidate near the box, and its order is that of all rows)
+    if (!CF && n_rows > kManyRows) {  // uniform
+      if ((rb & (64 * kLanes - 1)) == 0) batches = near_batches<P>(Fn, kc, rbx, q, valid, rb, kLanes);
+      const uint64_t ahead = batches >> ((rb / kLanes) & 63);
+      if (!(ahead & 1ull)) {  // on to the next batch near a source, or to the next 64
+        rb = ahead ? rb + kLanes * (__builtin_ctzll(ahead) - 1) : rb | (64 * kLanes - kLanes);
+        continue;
+      }
+    }
     // ---- one row per lane: its contiguous candidate range
     uint32_t j0 = 0, cntr = 0;
     const int r = rb + lane;
     if (r < n_rows) {
-      const int kz = z0 + r / ny, ky = y0 + r % ny;
-      const double cz = (double)(kz + Fn.org[2]) * cell;
-      const double cy = (double)(ky + Fn.org[1]) * cell;
-      const double bz = fmax(0.0, fmax(cz - (double)hi.z, (double)lo.z - (cz + cell)));
-      const double by = fmax(0.0, fmax(cy - (double)hi.y, (double)lo.y - (cy + cell)));
-      const double r2 = kc.reach2 - by * by - bz * bz;
-      if (r2 >= 0.0) {
-        const int4 R = trows[(int64_t)kz * Fn.dim[1] + ky];
-        if (R.y >= R.x) {
-          const double h = (double)__builtin_amdgcn_sqrtf((float)r2) * (1.0 + 0x1p-16);  // widened as above
-          const int xa = max(clamp_floor_d(((double)lo.x - h) * inv - Fn.org[0], -1, Fn.dim[0]), R.x);
-          const int xb = min(clamp_floor_d(((double)hi.x + h) * inv - Fn.org[0], -1, Fn.dim[0]), R.y);
-          if (xa <= xb) {
-            const uint32_t* xt = a.xtab + Fn.xt_off + (uint32_t)R.z;
-            j0 = xt[xa - R.x];
-            cntr = xt[xb + 1 - R.x] - j0;
-          }
-        }
-      }
+      int oz, oy;
+      rbx.split(r, oz, oy);
+      row_range(Fn, kc, trows, a.xtab, lo, hi, rbx.z0 + oz, rbx.y0 + oy, j0, cntr);
     }
     const uint32_t incl = wave_inclusive_scan(cntr);
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
