@@ -82,7 +82,8 @@ __global__ void k_edge_setup(const double* __restrict__ poses, const EdgeInfo* _
 }
 
 // Binning key of a source point (frame-local sorted index src of frame Fm): the Morton code of its target-frame
-// cell, clamped to the grid and its margin of reach cells, at the resolution of the frame's sub-cells.
+// cell, clamped to the grid and its margin of reach cells, at the resolution of the frame's sub-cells, and
+// kOutsideBit.
 __device__ inline uint32_t bin_key(const float4* __restrict__ pts, const FrameInfo& Fm, const FrameInfo& Fn,
                                    const EdgeXf& X, const KConst& kc, uint32_t src) {
   const int r = kc.reach_cells;
@@ -100,7 +101,7 @@ __device__ inline uint32_t bin_key(const float4* __restrict__ pts, const FrameIn
     const int cf = clamp_floor(u[a] * (double)(1 << sub), -lim, lim) + (r << sub);
     kk[a] = (uint32_t)min(max(cf, 0), ((top + 1) << sub) - 1) >> Fn.mort_shift;
   }
-  return morton3(kk[0], kk[1], kk[2]);
+  return (source_in_grid(q, Fn, kc) ? 0u : kOutsideBit) | morton3(kk[0], kk[1], kk[2]);
 }
 
 // One block per sort tile (kSortTile consecutive entries of one segment): keys, source indices and the tile's

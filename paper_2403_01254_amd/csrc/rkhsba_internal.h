@@ -17,6 +17,10 @@
 
 namespace rkhsba {
 
+// Binning keys: a 30-bit Morton code of the source point's target-frame cell (clamped to the grid and its
+// margin), with this bit set when the point lies outside both (it has no pair).  The last 8-bit digit of codes of
+// more than 24 bits includes it, so that those points come last; shorter codes leave them at their clamped place.
+constexpr uint32_t kOutsideBit = 0x80000000u;
 constexpr int kMaxDense = 64;
 
 enum Mode { MODE_LOSS = 0, MODE_NORMAL = 1 };
