@@ -35,7 +35,8 @@ PEAK_FP32_TFLOPS = 157.3          # MI355X published FP32 vector peak
 # residual 3 + squared distance 5 + scale 1 + exp 1 + weight 1 + A 1 + w*d 3 + B 3 + C 12
 FLOPS_PER_PAIR_GEOM = 30
 # the sweep kernel and the engine that lays out its pass table (the pass order changes the kernel's traffic)
-PAIR_KERNEL_SOURCES = [os.path.join(ROOT, "paper_2403_01254_amd", "csrc", f) for f in ("sweep.hip", "sweep_device.h", "engine.hip")]
+PAIR_KERNEL_SOURCES = [os.path.join(ROOT, "paper_2403_01254_amd", "csrc", f)
+                      for f in ("sweep.hip", "sweep_dense.hip", "sweep_device.h", "engine.hip")]
 # calibrated HBM bytes per sweep launch from rocprofv3 counters, per workload (profiles/)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_{workload}_traffic.json")
 WORKLOADS = {

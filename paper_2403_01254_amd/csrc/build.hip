@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kThreads) void k_gather_feat(const void* const* __r
     const int64_t o = sorted_vals[p];
     const float v = k < D ? static_cast<const float*>(feats[f])[o * D + k] : 0.0f;
     neg = v < 0.0f;
-    if (feat_kind == 1) static_cast<float*>(feat)[i] = v;
+    if (feat_kind == 1) static_cast<float*>(feat)[p * (IDX)Dp + (IDX)feat_slot(1, Dp, k)] = v;
     else if (feat_kind == 2) static_cast<uint16_t*>(feat)[i] = f32_to_bf16(v);
     else static_cast<uint8_t*>(feat)[i] = f32_to_e4m3(v);
   }

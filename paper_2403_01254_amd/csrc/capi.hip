@@ -783,7 +783,7 @@ int rkhsba_export_pairs(rkhsba_ctx* c, const double* poses, int m, int n, int64_
     RK_HIP(d_xf.reserve(1));
     RK_HIP(d_cnt.reserve(1));
     RK_HIP(hipMemcpyAsync(d_one.p, &one, sizeof(one), hipMemcpyHostToDevice, st));
-    RK_HIP(launch_edge_setup(g.poses(), d_one.p, 1, d_xf.p, st));
+    RK_HIP(launch_edge_setup(g.poses(), d_one.p, 1, d_xf.p, nullptr, st));
     const int fp = g.feat_kind == RKHSBA_FEAT_CLASS_ID ? FEAT_CLASS : FEAT_DENSE;
     RK_HIP(hipMemsetAsync(d_cnt.p, 0, sizeof(unsigned long long), st));
     RK_HIP(launch_export_pairs(g.pts(), g.rows(), g.xtab(), g.frames(), p->frames[m].n, g.perm(), g.feat(), d_xf.p, mg,

@@ -111,6 +111,9 @@ struct EvalScratch {
   DBuf<uint32_t> cnt;
   DBuf<double> partial, edge_out;
   DBuf<double> H, b, delta;
+  DBuf<uint2> items;        // spread passes of dense features, split over their sources
+  DBuf<uint32_t> n_items;
+  DBuf<uint8_t> split;
 };
 
 // First-fit allocator of element ranges [0, capacity).
@@ -223,6 +226,7 @@ struct SetLayout {
     bool topk;
   };
   std::vector<Group> groups;        // contiguous runs of the pass table, one sweep launch each
+  uint32_t item_cap = 0;            // room for the items of spread passes (0: passes are not split)
   bool clamp = false;
   bool c_positive = false;          // every problem's inner products are > 0 (pair counts need no c != 0 test)
   DBuf<EdgeInfo> d_edges;

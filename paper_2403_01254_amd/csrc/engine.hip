@@ -231,7 +231,7 @@ int64_t Engine::device_bytes() const {
   const EvalScratch& o = own_sc_;
   b += (int64_t)(o.xf.bytes() + o.bk.bytes() + o.bv.bytes() + o.bk2.bytes() + o.bv2.bytes() + o.bhist.bytes() +
                  o.mom.bytes() + o.cnt.bytes() + o.partial.bytes() + o.edge_out.bytes() + o.H.bytes() + o.b.bytes() +
-                 o.delta.bytes());
+                 o.delta.bytes() + o.items.bytes() + o.n_items.bytes() + o.split.bytes());
   return b;
 }
 
@@ -275,6 +275,7 @@ void Engine::compute_constants(Problem* p) {
   k.topk = o.top_k;
   k.inv2l2 = 1.0 / (2.0 * o.ell * o.ell);
   k.spread_limit = (float)(kSpreadFactor * rc);
+  k.r_c = (float)rc;
   p->kc = k;
 }
 
@@ -691,6 +692,7 @@ void Engine::set_ell(Problem* p, double ell) {
   k.reach_cells = (int)std::ceil(k.reach * k.inv_cell) + 1;
   k.inv2l2 = 1.0 / (2.0 * ell * ell);
   k.spread_limit = (float)(kSpreadFactor * rc);
+  k.r_c = (float)rc;
   p->kc = k;
   ++p->kc_version;
 }
@@ -852,7 +854,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   std::vector<int32_t> bstart_all, blist, vstart_all, vlist;
   int64_t entries = 0, passes = 0, fins = 0, h_total = 0, v_total = 0;
   int bin_bits = 3, n_max = 0;
-  bool clamp = false, positive = true;
+  bool clamp = false, positive = true, many_rows = false;
   int e_glob = 0;
   for (size_t pi = 0; pi < items.size(); ++pi) {
     const SetItem& it = items[pi];
@@ -860,6 +862,9 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
     kcs[pi] = p->kc;
     kcs[pi].Dp = Dp;
     clamp = clamp || p->kc.clamp;
+    for (const FrameInfo& F : p->frames)
+      many_rows = many_rows ||
+                  (feat_kind != RKHSBA_FEAT_CLASS_ID && (int64_t)F.dim[1] * F.dim[2] > kSplitRows);
     positive = positive && p->kc.c_positive;
     bin_bits = std::max(bin_bits, p->bin_bits);
     all_stacked = all_stacked && p->stacked;
@@ -1028,7 +1033,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
 
   // per-evaluation scratch
   const void* before[] = {sc_->xf.p, sc_->bk.p, sc_->bv.p, sc_->bk2.p, sc_->bv2.p, sc_->bhist.p, sc_->mom.p, sc_->cnt.p, sc_->partial.p, sc_->edge_out.p,
-                          sc_->H.p, sc_->b.p, sc_->delta.p};
+                          sc_->H.p, sc_->b.p, sc_->delta.p, sc_->items.p, sc_->n_items.p, sc_->split.p};
   need(sc_->xf, E_total, "xf");
   need(sc_->bk, entries, "bk");
   need(sc_->bv, entries, "bv");
@@ -1042,8 +1047,17 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   need(sc_->H, h_total, "H");
   need(sc_->b, v_total, "b");
   need(sc_->delta, v_total, "delta");
+  // Spread passes of dense features are split where a box can have that many rows; up to one item per pass of the
+  // set (passes beyond that are walked whole).  The allocation-free scratch has no room for the list.
+  uint32_t item_cap = 0;
+  if (!arena_ && many_rows && gcount[0] > 0) {
+    item_cap = (uint32_t)std::min<int64_t>(gcount[0] + 64, INT_MAX - gcount[0]);
+    need(sc_->items, item_cap, "items");
+    need(sc_->n_items, 1, "n_items");
+    need(sc_->split, (size_t)gcount[0], "split");
+  }
   const void* after[] = {sc_->xf.p, sc_->bk.p, sc_->bv.p, sc_->bk2.p, sc_->bv2.p, sc_->bhist.p, sc_->mom.p, sc_->cnt.p, sc_->partial.p, sc_->edge_out.p,
-                         sc_->H.p, sc_->b.p, sc_->delta.p};
+                         sc_->H.p, sc_->b.p, sc_->delta.p, sc_->items.p, sc_->n_items.p, sc_->split.p};
   if (!arena_)
     for (size_t i = 0; i < sizeof(before) / sizeof(before[0]); ++i)
       if (before[i] != after[i]) ++scratch_gen_;
@@ -1069,6 +1083,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   lay.stacked = all_stacked;
   lay.bin_bits = bin_bits;
   lay.clamp = clamp;
+  lay.item_cap = item_cap;
   lay.c_positive = positive && !items.empty();
   lay.h_total = h_total;
   lay.v_total = v_total;
@@ -1086,7 +1101,8 @@ void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning) {
   RK_REQUIRE(!arena_ || mode == MODE_LOSS || arena_->mom_components == 10, RKHSBA_ESTATE,
              "the arena holds loss-evaluation moments only");
   hipEvent_t t0 = prof_begin();
-  RK_HIP(launch_edge_setup(poses(), lay.d_edges.p, lay.E, sc_->xf.p, st));
+  RK_HIP(launch_edge_setup(poses(), lay.d_edges.p, lay.E, sc_->xf.p, lay.item_cap > 0 ? sc_->n_items.p : nullptr,
+                           st));
   const bool reuse = reuse_binning && lay.binned && binned_lay_ == &lay && lay.bin_sc == sc_ &&
                      lay.bin_gen == scratch_gen_;
   if (reuse) {
@@ -1121,6 +1137,11 @@ void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning) {
   pa.passes = lay.d_passes.p;
   pa.perm = perm();
   pa.n_entries = lay.n_entries;
+  pa.items = lay.item_cap > 0 ? sc_->items.p : nullptr;
+  pa.n_items = sc_->n_items.p;
+  pa.split = sc_->split.p;
+  pa.item_cap = lay.item_cap;
+  pa.split_factor = split_factor(lay.n_pass_total);
   pa.E = lay.E;
 
   pa.kc.Dp = Dp;
@@ -1132,7 +1153,10 @@ void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning) {
   for (const SetLayout::Group& gr : lay.groups) {
     pa.pass0 = gr.pass0;
     pa.n_pass = gr.n_pass;
-    if (tiled_sweep(gr.pass_points, feat_kind))
+    const bool matrix_moments = moment_path == 2 && mode == MODE_NORMAL && !source_counts;
+    if (gr.pass_points == 16 && feat_kind != RKHSBA_FEAT_CLASS_ID && !matrix_moments)
+      RK_HIP(launch_sweep_dense(pa, mode, feat_path, source_counts && mode == MODE_NORMAL, st));
+    else if (tiled_sweep(gr.pass_points, feat_kind))
       RK_HIP(launch_sweep(pa, mode, feat_path, gr.pass_points, moment_path == 2 && !source_counts,
                           source_counts && mode == MODE_NORMAL, st));
     else

@@ -73,8 +73,9 @@ __device__ inline void for_each_range(const FrameInfo& T, const int4* __restrict
 // ---------------------------------------------------------------- transforms and binning
 
 __global__ void k_edge_setup(const double* __restrict__ poses, const EdgeInfo* __restrict__ edges, int E,
-                             EdgeXf* __restrict__ xf) {
+                             EdgeXf* __restrict__ xf, uint32_t* __restrict__ n_items) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e == 0 && n_items) *n_items = 0u;
   if (e >= E) return;
   EdgeXf o;
   rule_relative(poses + 12 * edges[e].m, poses + 12 * edges[e].n, o.R, o.t);
@@ -759,8 +760,9 @@ hipError_t launch_fill_passes(const EdgeInfo* d_edges, int E, const FrameInfo* d
   return hipGetLastError();
 }
 
-hipError_t launch_edge_setup(const double* d_poses, const EdgeInfo* d_edges, int E, EdgeXf* d_xf, hipStream_t st) {
-  if (E > 0) k_edge_setup<<<(E + 63) / 64, 64, 0, st>>>(d_poses, d_edges, E, d_xf);
+hipError_t launch_edge_setup(const double* d_poses, const EdgeInfo* d_edges, int E, EdgeXf* d_xf, uint32_t* d_n_items,
+                             hipStream_t st) {
+  if (E > 0) k_edge_setup<<<(E + 63) / 64, 64, 0, st>>>(d_poses, d_edges, E, d_xf, d_n_items);
   return hipGetLastError();
 }
 

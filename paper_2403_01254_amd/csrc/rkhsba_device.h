@@ -74,11 +74,14 @@ template <int FEAT, int DP>
 __device__ inline void load_feature_row(const void* __restrict__ base, int64_t row, float (&out)[DP]) {
   if constexpr (FEAT == FEAT_DENSE) {
     const float4* f4 = reinterpret_cast<const float4*>(static_cast<const float*>(base) + row * DP);
+    float r[DP];
 #pragma unroll
     for (int k = 0; k < DP / 4; ++k) {
       const float4 v = f4[k];
-      out[4 * k] = v.x; out[4 * k + 1] = v.y; out[4 * k + 2] = v.z; out[4 * k + 3] = v.w;
+      r[4 * k] = v.x; r[4 * k + 1] = v.y; r[4 * k + 2] = v.z; r[4 * k + 3] = v.w;
     }
+#pragma unroll
+    for (int k = 0; k < DP; ++k) out[k] = r[feat_slot(FEAT, DP, k)];
   } else if constexpr (FEAT == FEAT_BF16) {
     const uint4* u4 = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(base) + row * DP);
 #pragma unroll

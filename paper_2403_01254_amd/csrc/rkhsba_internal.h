@@ -99,6 +99,7 @@ struct KConst {
   double inv2l2;     // 1 / (2 ell^2), for the FP64 ranking key of the topk selection
   int c_positive;    // FP32 dense features, none negative, and one dimension >= 1e-18 in every row: every
                      // inner product is > 0 (its term in that dimension is >= 1e-36, above FLT_MIN)
+  float r_c;           // truncation radius
   float spread_limit;  // class-id sweeps: passes whose box is wider than this walk per source point
 };
 constexpr int kMaxTopK = 8;
@@ -224,7 +225,9 @@ hipError_t launch_frame_centroid(const float4* d_pts, int n, double* d_out, hipS
 // of each edge cover each of its segments in runs of pass_size (64 for per-point walks).
 hipError_t launch_fill_passes(const EdgeInfo* d_edges, int E, const FrameInfo* d_frames, const SortSeg* d_segs,
                               PassInfo* d_passes, hipStream_t st);
-hipError_t launch_edge_setup(const double* d_poses, const EdgeInfo* d_edges, int E, EdgeXf* d_xf, hipStream_t st);
+// d_n_items (nullable): the sweep's item counter, cleared here.
+hipError_t launch_edge_setup(const double* d_poses, const EdgeInfo* d_edges, int E, EdgeXf* d_xf, uint32_t* d_n_items,
+                             hipStream_t st);
 // Source binning.  Segments of at most kBlockSortMax entries: keys and sort in one workgroup each, their sorted
 // source indices written to d_sorted.  The others: keys and source indices of every entry, one block per tile,
 // with the tile's counts of digit 0, for launch_radix_sort.
@@ -232,6 +235,26 @@ hipError_t launch_bin(const float4* d_pts, const FrameInfo* d_frames, const Edge
                       const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan, const EdgeXf* d_xf,
                       const KConst* d_kcs, int bits, uint32_t* d_keys, uint32_t* d_vals, uint32_t* d_hist,
                       uint32_t* d_sorted, hipStream_t st);
+
+// Passes whose box spans more rows than this skip the batches of rows that no source of theirs is near.  The
+// sources of such a pass lie in a few places far apart (a jump of the Morton order), and most rows of the box
+// around them all lie between: a box across a frame of 8 m in cells of 3 cm has 70,000 rows.  One wavefront
+// enumerates them 64 at a time, and such passes set the time of a launch.  Tested 64 batches at once, one per
+// lane.  The batches kept are enumerated as without the test, so the order of a source's candidates is the same.
+// Sweep of 8 depth frames x 30,000 points, 23 dimensions, 28 edges: 1342 -> 1000 us; 5 x 12,345 points, fp8:
+// 282 -> 163 us; 4 x 8,000 points, 20 dimensions: 180 -> 102 us.  Boxes of fewer rows would pay more for the test
+// (a compact pass has about (2 + box / r_c)^2 cell_subdiv^2 rows: 450 at 8 cells per r_c) than the few batches it
+// could skip.
+constexpr int kManyRows = 512;
+
+// Dense-feature passes whose box is wider than split_factor(passes of the launch) truncation radii and spans more
+// than kSplitRows rows are split over their sources (sweep_dense.hip).  A split pass costs more work in all, and
+// ends sooner: few passes are bound by the longest one, many by the work.  Sweep times in us, split at 2 / 4 r_c
+// (not at all): 8 x 30,000 points, 52,500 passes 907 / 844 (1004); 3 x 60,000, 11,250 passes 1987 / 2268 (2350); 3 x
+// 9,000 bfloat16, 1,700 passes 48 / 73 (86); 4 x 8,000, 3,000 passes 70 / 82 (113).  Boxes of a few rows (two to four
+// batches) are walked faster than they are split: 5 x 12,345 fp8 102 from 256 rows on, 111 from 128.
+constexpr int kSplitRows = 256;
+inline float split_factor(int64_t n_pass) { return n_pass <= 16384 ? 2.f : 4.f; }
 
 struct PairArgs {
   const float4* pts;
@@ -252,6 +275,11 @@ struct PairArgs {
   int32_t pass0;          // first pass of this launch in the pass table
   int32_t n_pass;         // passes of this launch
   KConst kc;              // set-wide: Dp and clamp (clamping is exact for non-negative features)
+  uint2* items;           // the spread passes of dense features, split: (pass, source mask); null: not split
+  uint32_t* n_items;      // items listed (zero when the sweep's first kernel begins)
+  uint8_t* split;         // per pass of the launch: listed as items
+  uint32_t item_cap;
+  float split_factor;     // passes whose box is wider than this many truncation radii count as spread
   int32_t stacked;        // every frame of the set is label-stacked (class ids): a candidate of the pass's
                           // layer always carries the pass's class id, and the sweeps skip that test
 };
@@ -264,6 +292,15 @@ hipError_t launch_pairs(const PairArgs& a, int mode, int feat_path, int pass_poi
 // the pass's first entry (the per-edge sums are the same).
 hipError_t launch_sweep(const PairArgs& a, int mode, int feat_path, int pass_points, bool matrix_moments,
                         bool source_counts, hipStream_t st);
+
+// Tiled sweep of dense features, passes of 16 sources, moments on the VALU; source_counts as above.
+hipError_t launch_sweep_dense(const PairArgs& a, int mode, int feat_path, bool source_counts, hipStream_t st);
+
+// Where element k of a dense feature row is stored: FP32 rows are stored column by column of the 16x16x4 matrix
+// instruction's operand (elements 4i + g for i = 0, 1, ... at g * Dp / 4), the others in order.
+__host__ __device__ constexpr int feat_slot(int feat_path, int Dp, int k) {
+  return feat_path == FEAT_DENSE ? (k & 3) * (Dp / 4) + (k >> 2) : k;
+}
 
 struct FinArgs {
   const float4* pts;

@@ -1,4 +1,6 @@
-// Tiled candidate sweep (16 source points per wavefront, 64-candidate tiles).
+// Tiled candidate sweep of class ids (16 source points per wavefront, 64-candidate tiles), and of dense features
+// with moments on the matrix cores (moment_path 2); sweep_dense.hip has dense features with moments on the vector
+// ALU, the library's choice.
 //
 // One wavefront (= one workgroup of 64 lanes) handles a pass of P = 16
 // Morton-adjacent source points of one edge.  Lane l works for source point
@@ -37,11 +39,11 @@ template <int DP, int FS>
 __device__ inline floatx4 tile_products(const float* __restrict__ tfeat, int s, int g, int sub,
                                         const float (&fsrc)[DP / 4]) {
   floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-  const float* arow = tfeat + (16 * sub + s) * FS + g;
+  const float* arow = tfeat + (16 * sub + s) * FS + g * (DP / 4);  // (stored column by column, feat_slot)
   // every A element read before the first product: one LDS round trip per sub-tile, not one per pair of slices
   float av[DP / 4];
 #pragma unroll
-  for (int k = 0; k < DP / 4; ++k) av[k] = arow[4 * k];
+  for (int k = 0; k < DP / 4; ++k) av[k] = arow[k];
   __builtin_amdgcn_sched_barrier(0);  // (the scheduler would otherwise interleave reads and products again)
 #pragma unroll
   for (int k = 0; k < DP / 4; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[k], fsrc[k], acc, 0, 0, 0);
@@ -82,8 +84,7 @@ __device__ inline floatx4 tile_products_lp(const uint8_t* __restrict__ tl, int s
 // (A operand = the weights the lanes just computed, B = Phi of the same
 // candidates), and A, B, C follow exactly from M and v = q - ref:
 //   A = M_1, B = A v - M_u, C = A v v^T - v M_u^T - M_u v^T + M_uu.
-// CM: the inner products as computed (0), negative ones clamped to 0 (1), or
-// known to be positive (2: the pair count then needs no c != 0 test).
+// CM: the inner products as computed (0), or negative ones clamped to 0 (1).
 // SC: every source point's own pair count goes to its entry of a.cnt (one more
 // VALU add per candidate; for parity checks of the pair set), instead of the
 // pass's count on its first entry (the per-edge totals are the same).
@@ -92,6 +93,7 @@ __device__ inline floatx4 tile_products_lp(const uint8_t* __restrict__ tl, int s
 // skipped.
 template <int MODE, int FEAT, int DP, int CM, bool MM, int P, bool SC = false, bool LS = false>
 __global__ __launch_bounds__(kLanes) void k_sweep(PairArgs a) {
+  static_assert(FEAT == FEAT_CLASS || MM, "dense features with vector-ALU moments: sweep_dense.hip");
   // P source points per pass (16; 8 or 32 for class ids); lane (s, g) takes CPL candidates of every
   // 16-candidate sub-tile
   static_assert(P == 16 || ((P == 8 || P == 32) && FEAT == FEAT_CLASS && !MM), "8 or 32-point passes: class ids only");
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(kLanes) void k_sweep(PairArgs a) {
       // B operand of the MFMA: feature 4k + g of this lane's source point
       const float* f = static_cast<const float*>(a.feat) + (pi.src_off + src) * DP;
 #pragma unroll
-      for (int k = 0; k < DP / 4; ++k) fsrc[k] = f[4 * k + g];
+      for (int k = 0; k < DP / 4; ++k) fsrc[k] = f[g * (DP / 4) + k];
     } else if constexpr (LP) {
       // B operand: elements 32k + 8g .. 32k + 8g + 7 of this lane's source row
       const uint8_t* f = static_cast<const uint8_t*>(a.feat) + (pi.src_off + src) * (int64_t)ROWB;
@@ -364,8 +366,7 @@ __global__ __launch_bounds__(kLanes) void k_sweep(PairArgs a) {
         const float w = in ? c * k : 0.f;
         // pairs counted per pass from the wavefront's lane masks (scalar unit), or per lane (SC)
         if constexpr (SC) {
-          if constexpr (FEAT == FEAT_CLASS || CM == 2) own += in ? 1u : 0u;
-          else own += (in && c != 0.f) ? 1u : 0u;
+          own += in ? 1u : 0u;
         } else if constexpr (LS) {
           cnt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(near));
         } else if constexpr (FEAT == FEAT_CLASS) {
@@ -373,8 +374,6 @@ __global__ __launch_bounds__(kLanes) void k_sweep(PairArgs a) {
           // condition would first turn it into a vector value and back)
           cnt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(near) &
                                     __builtin_amdgcn_ballot_w64(__float_as_uint(z.w) == lbl));
-        } else if constexpr (CM == 2) {
-          cnt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(in));
         } else {
           cnt += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(in) & __builtin_amdgcn_ballot_w64(c != 0.f));
         }
@@ -597,23 +596,23 @@ hipError_t dispatch(const PairArgs& a, int DP, hipStream_t st) {
   return hipGetLastError();
 }
 
-// clamped, known-positive (FP32 features, VALU moments) or plain inner products
-template <int MODE, int FEAT, bool MM, bool SC>
-hipError_t dispatch_clamp(const PairArgs& a, hipStream_t st) {
-  if (a.kc.clamp) return dispatch<MODE, FEAT, 1, MM, SC>(a, a.kc.Dp, st);
-  if constexpr (FEAT == FEAT_DENSE && !MM)
-    if (a.kc.c_positive) return dispatch<MODE, FEAT, 2, MM, SC>(a, a.kc.Dp, st);
-  return dispatch<MODE, FEAT, 0, MM, SC>(a, a.kc.Dp, st);
-}
-
 template <int MODE, bool MM, bool SC>
 hipError_t dispatch_mode(const PairArgs& a, int feat_path, hipStream_t st) {
-  switch (feat_path) {
-    case FEAT_CLASS: return dispatch<MODE, FEAT_CLASS, 0, MM, SC>(a, 0, st);
-    case FEAT_DENSE: return dispatch_clamp<MODE, FEAT_DENSE, MM, SC>(a, st);
-    case FEAT_BF16: return dispatch_clamp<MODE, FEAT_BF16, MM, SC>(a, st);
-    default: return dispatch_clamp<MODE, FEAT_FP8, MM, SC>(a, st);
+  if (feat_path == FEAT_CLASS) return dispatch<MODE, FEAT_CLASS, 0, MM, SC>(a, 0, st);
+  if constexpr (MM) {
+    const int DP = a.kc.Dp;
+    const bool clamp = a.kc.clamp != 0;
+    switch (feat_path) {
+      case FEAT_DENSE:
+        return clamp ? dispatch<MODE, FEAT_DENSE, 1, MM, SC>(a, DP, st) : dispatch<MODE, FEAT_DENSE, 0, MM, SC>(a, DP, st);
+      case FEAT_BF16:
+        return clamp ? dispatch<MODE, FEAT_BF16, 1, MM, SC>(a, DP, st) : dispatch<MODE, FEAT_BF16, 0, MM, SC>(a, DP, st);
+      case FEAT_FP8:
+        return clamp ? dispatch<MODE, FEAT_FP8, 1, MM, SC>(a, DP, st) : dispatch<MODE, FEAT_FP8, 0, MM, SC>(a, DP, st);
+      default: break;
+    }
   }
+  return hipErrorInvalidValue;
 }
 
 // Class ids in passes of P = 8 or 32 source points (moments on the VALU).

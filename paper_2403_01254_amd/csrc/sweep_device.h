@@ -1,7 +1,9 @@
 // Device helpers of the tiled candidate sweeps.
 #pragma once
 
+#include <algorithm>
 #include <cfloat>
+#include <type_traits>
 
 #include "block_sort.h"
 
@@ -59,6 +61,17 @@ __device__ inline float group_max(float v) {
   return v;
 }
 
+// The same over quads of consecutive lanes.
+__device__ inline float quad_min(float v) {
+  v = fminf(v, dpp_f<kDppXor1>(v));
+  return fminf(v, dpp_f<kDppXor2>(v));
+}
+__device__ inline float quad_max(float v) {
+  v = fmaxf(v, dpp_f<kDppXor1>(v));
+  return fmaxf(v, dpp_f<kDppXor2>(v));
+}
+
+// A lane's value as a uniform one.
 __device__ inline float lane_f(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
@@ -129,17 +142,6 @@ __device__ inline RowBox row_box(const FrameInfo& F, const KConst& kc, float3 lo
   B.n = (z1 >= B.z0 && y1 >= B.y0) ? (z1 - B.z0 + 1) * B.ny : 0;
   return B;
 }
-
-// Passes whose box spans more rows than this skip the batches of rows that no source of theirs is near.  The
-// sources of such a pass lie in a few places far apart (a jump of the Morton order), and most rows of the box
-// around them all lie between: a box across a frame of 8 m in cells of 3 cm has 70,000 rows.  One wavefront
-// enumerates them 64 at a time, and such passes set the time of a launch.  Tested 64 batches at once, one per
-// lane.  The batches kept are enumerated as without the test, so the order of a source's candidates is the same.
-// Sweep of 8 depth frames x 30,000 points, 23 dimensions, 28 edges: 1342 -> 1000 us; 5 x 12,345 points, fp8:
-// 282 -> 163 us; 4 x 8,000 points, 20 dimensions: 180 -> 102 us.  Boxes of fewer rows would pay more for the test
-// (a compact pass has about (2 + box / r_c)^2 cell_subdiv^2 rows: 450 at 8 cells per r_c) than the few batches it
-// could skip.
-constexpr int kManyRows = 512;
 
 // Of the 64 batches of `batch` consecutive rows from row rb of B on, those with a row within the reach of a valid
 // source (the first P lanes hold the sources' q; invalid ones are not valid).
