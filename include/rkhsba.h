@@ -102,7 +102,8 @@ typedef struct {
   int moment_path;       /* 16-point sweep, Gauss-Newton moments accumulated on 0 = library choice,
                             1 = vector ALU, 2 = matrix cores (default 0) */
   int use_graphs;        /* 1 = capture one Gauss-Newton iteration in a HIP graph and replay it (default 1;
-                            stage timing, when enabled, runs the launches one by one instead) */
+                            stage timing, when enabled, and iterations of few launches run the launches
+                            one by one instead) */
   int hessian_fp32;      /* 1 = per-edge sums of the normal-equation terms in FP32 with Kahan compensation,
                             0 = FP64 (default) */
   int top_k;             /* 0 = every pair inside r_c (default); 1..8 = per source point and edge only the

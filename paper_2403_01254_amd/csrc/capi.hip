@@ -394,8 +394,7 @@ int rkhsba_accumulate_normal_eqs(rkhsba_ctx* c, const double* poses, int E, cons
     g.upload_poses(p, poses);
     g.reset_state(p);
     const int n = 6 * p->K;
-    g.evaluate(c->lay_eval, MODE_NORMAL);
-    g.assemble(c->lay_eval);
+    g.evaluate(c->lay_eval, MODE_NORMAL, false, STEP_SYSTEM);
     const SolveArgs sa = g.solve_args(c->lay_eval);
     if (H) RK_HIP(hipMemcpyAsync(H, sa.H, sizeof(double) * n * n, hipMemcpyDeviceToHost, c->stream));
     if (b) RK_HIP(hipMemcpyAsync(b, sa.b, sizeof(double) * n, hipMemcpyDeviceToHost, c->stream));
@@ -419,8 +418,7 @@ int rkhsba_gn_step(rkhsba_ctx* c, double* poses, int E, const int32_t* edges, in
     g.upload_poses(p, poses);
     g.reset_state(p);
     g.iterate(c->lay_gn, n_iter);
-    g.evaluate(c->lay_gn, MODE_LOSS, n_iter > 0);  // the binning of this call's first iteration
-    g.loss_only(c->lay_gn);
+    g.evaluate(c->lay_gn, MODE_LOSS, n_iter > 0, STEP_LOSS);  // the binning of this call's first iteration
     std::vector<double> lh(n_iter + 1), ph(n_iter + 1);
     g.download_poses(p, poses);
     g.read_history(p, n_iter + 1, lh.data(), ph.data());
@@ -654,8 +652,7 @@ int rkhsba_gn_lengthscale(rkhsba_ctx* c, double* poses, int E, const int32_t* ed
       g.upload_poses(p, poses);
       g.reset_state(p);
       g.iterate(c->lay_gn, ni);
-      g.evaluate(c->lay_gn, MODE_LOSS);
-      g.loss_only(c->lay_gn);
+      g.evaluate(c->lay_gn, MODE_LOSS, false, STEP_LOSS);
       g.download_poses(p, poses);
       g.read_history(p, ni + 1, lh.data(), nullptr);
       status = g.read_status(p);

@@ -227,6 +227,7 @@ struct SetLayout {
   };
   std::vector<Group> groups;        // contiguous runs of the pass table, one sweep launch each
   uint32_t item_cap = 0;            // room for the items of spread passes (0: passes are not split)
+  bool small = false;               // every problem's step fits one workgroup (small_step)
   bool clamp = false;
   bool c_positive = false;          // every problem's inner products are > 0 (pair counts need no c != 0 test)
   DBuf<EdgeInfo> d_edges;
@@ -329,13 +330,10 @@ class Engine {
   // One evaluation of every item of the set at the device poses: per-edge sums in edge_out.
   // reuse_binning: keep the order of the layout's last binning (its passes stay spatially compact while
   // the poses move a little); binned in full when the scratch no longer holds that binning.
-  void evaluate(SetLayout& lay, int mode, bool reuse_binning = false);
-  // Assembly (+ history entry) of every problem.
-  void assemble(SetLayout& lay);
-  // Damped solve + pose update of every problem still iterating.
-  void solve(SetLayout& lay);
-  // History entry only (after a loss evaluation).
-  void loss_only(SetLayout& lay);
+  // step: what is done with the sums (Step): a history entry, the systems H and b, or a whole Gauss-Newton step of
+  // every problem still iterating.  xf_ready: the edge transforms of the current poses are in the scratch (left
+  // there by a step of the same layout).
+  void evaluate(SetLayout& lay, int mode, bool reuse_binning = false, int step = STEP_NONE, bool xf_ready = false);
   // n Gauss-Newton iterations (evaluate, assemble, solve) over the set; graph-replayed when enabled.
   void iterate(SetLayout& lay, int n, bool continue_binning = false);
   SolveArgs solve_args(SetLayout& lay);
@@ -378,7 +376,8 @@ class Engine {
 
  private:
   void compute_constants(Problem* p);
-  void record_iteration(SetLayout& lay, bool reuse_binning);
+  void record_iteration(SetLayout& lay, bool reuse_binning, bool xf_ready);
+  void edge_setup(SetLayout& lay);
   const SetLayout* binned_lay_ = nullptr;  // layout whose binning the scratch holds
 
   std::map<int, std::unique_ptr<Problem>> probs_;

@@ -854,7 +854,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   std::vector<int32_t> bstart_all, blist, vstart_all, vlist;
   int64_t entries = 0, passes = 0, fins = 0, h_total = 0, v_total = 0;
   int bin_bits = 3, n_max = 0;
-  bool clamp = false, positive = true, many_rows = false;
+  bool clamp = false, positive = true, many_rows = false, small = true;
   int e_glob = 0;
   for (size_t pi = 0; pi < items.size(); ++pi) {
     const SetItem& it = items[pi];
@@ -886,6 +886,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
     v_total += S.n;
     n_max = std::max(n_max, S.n);
     const int K = p->K;
+    int64_t fin_blocks = 0;
     std::vector<std::vector<int32_t>> blk((size_t)K * K), vec(K);
     for (int e = 0; e < it.E; ++e, ++e_glob) {
       const int m = it.edges[2 * e], n = it.edges[2 * e + 1];
@@ -931,6 +932,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
       entries += I.n_src;
       passes += I.n_pass;
       fins += I.n_fin;
+      fin_blocks += I.n_fin;
       if (m != n && m < K && n < K) {  // self and alias edges are evaluated but never assembled
         blk[(size_t)m * K + m].push_back(e_glob * 4 + 0);
         blk[(size_t)n * K + n].push_back(e_glob * 4 + 1);
@@ -940,6 +942,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
         vec[n].push_back(e_glob * 2 + 1);
       }
     }
+    small = small && small_step(S, fin_blocks);
     S.blk0 = (int32_t)bstart_all.size();
     for (size_t k = 0; k < blk.size(); ++k) {
       bstart_all.push_back((int32_t)blist.size());
@@ -1083,6 +1086,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   lay.stacked = all_stacked;
   lay.bin_bits = bin_bits;
   lay.clamp = clamp;
+  lay.small = small;
   lay.item_cap = item_cap;
   lay.c_positive = positive && !items.empty();
   lay.h_total = h_total;
@@ -1097,12 +1101,16 @@ static bool tiled_sweep(int pass_points, int feat_kind) {
   return pass_points == 16 || ((pass_points == 8 || pass_points == 32) && feat_kind == RKHSBA_FEAT_CLASS_ID);
 }
 
-void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning) {
+void Engine::edge_setup(SetLayout& lay) {
+  RK_HIP(launch_edge_setup(poses(), lay.d_edges.p, lay.E, sc_->xf.p, lay.item_cap > 0 ? sc_->n_items.p : nullptr,
+                           st));
+}
+
+void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning, int step, bool xf_ready) {
   RK_REQUIRE(!arena_ || mode == MODE_LOSS || arena_->mom_components == 10, RKHSBA_ESTATE,
              "the arena holds loss-evaluation moments only");
   hipEvent_t t0 = prof_begin();
-  RK_HIP(launch_edge_setup(poses(), lay.d_edges.p, lay.E, sc_->xf.p, lay.item_cap > 0 ? sc_->n_items.p : nullptr,
-                           st));
+  if (!xf_ready) edge_setup(lay);
   const bool reuse = reuse_binning && lay.binned && binned_lay_ == &lay && lay.bin_sc == sc_ &&
                      lay.bin_gen == scratch_gen_;
   if (reuse) {
@@ -1178,8 +1186,27 @@ void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning) {
   fa.n_fin_total = lay.n_fin_total;
   hipEvent_t t2 = prof_begin();
   RK_HIP(launch_finalize(fa, lay.d_fin_off.p, mode, fp32_sums, st));
+  if (lay.small && step != STEP_NONE) {
+    prof_end(RKHSBA_PROF_FINALIZE, t2);
+    StepArgs u{};
+    u.partial = sc_->partial.p;
+    u.edges = lay.d_edges.p;
+    u.xf = sc_->xf.p;
+    u.edge_out = sc_->edge_out.p;
+    u.n_items = lay.item_cap > 0 ? sc_->n_items.p : nullptr;
+    hipEvent_t t3 = prof_begin();
+    RK_HIP(launch_step(solve_args(lay), u, mode, step, fp32_sums, st));
+    prof_end(step == STEP_SOLVE ? RKHSBA_PROF_SOLVE : RKHSBA_PROF_FINALIZE, t3);
+    return;
+  }
   RK_HIP(launch_edge_reduce(sc_->partial.p, lay.d_edges.p, sc_->xf.p, lay.E, mode, fp32_sums, sc_->edge_out.p, st));
   prof_end(RKHSBA_PROF_FINALIZE, t2);
+  if (step == STEP_NONE) return;
+  hipEvent_t t3 = step == STEP_SOLVE ? prof_begin() : nullptr;
+  if (step == STEP_LOSS) RK_HIP(launch_loss_only(solve_args(lay), st));
+  else RK_HIP(launch_assemble(solve_args(lay), st));
+  if (step == STEP_SOLVE) RK_HIP(launch_solve_update(solve_args(lay), st));
+  prof_end(RKHSBA_PROF_SOLVE, t3);
 }
 
 SolveArgs Engine::solve_args(SetLayout& lay) {
@@ -1202,36 +1229,25 @@ SolveArgs Engine::solve_args(SetLayout& lay) {
   return s;
 }
 
-void Engine::assemble(SetLayout& lay) { RK_HIP(launch_assemble(solve_args(lay), st)); }
-
-void Engine::loss_only(SetLayout& lay) { RK_HIP(launch_loss_only(solve_args(lay), st)); }
-
-void Engine::solve(SetLayout& lay) {
-  hipEvent_t t = prof_begin();
-  RK_HIP(launch_solve_update(solve_args(lay), st));
-  prof_end(RKHSBA_PROF_SOLVE, t);
-}
-
-void Engine::record_iteration(SetLayout& lay, bool reuse_binning) {
-  evaluate(lay, MODE_NORMAL, reuse_binning);
-  hipEvent_t t = prof_begin();
-  RK_HIP(launch_assemble(solve_args(lay), st));
-  RK_HIP(launch_solve_update(solve_args(lay), st));
-  prof_end(RKHSBA_PROF_SOLVE, t);
+void Engine::record_iteration(SetLayout& lay, bool reuse_binning, bool xf_ready) {
+  evaluate(lay, MODE_NORMAL, reuse_binning, STEP_SOLVE, xf_ready && lay.small);
 }
 
 void Engine::iterate(SetLayout& lay, int n, bool continue_binning) {
   if (n <= 0) return;
   // A graph pays for its capture only when it is replayed: capture on a
-  // layout's second use, or when this call runs several iterations.
-  const bool graph = use_graphs && !prof && (n > 1 || lay.uses >= graph_min_uses);
+  // layout's second use, or when this call runs several iterations.  A set of
+  // small problems iterates in 3 to 5 launches, which the host issues faster
+  // than the device takes them, while consecutive replays start 8 us apart:
+  // 10 iterations of 2 frames x 5,000 points 0.73 ms replayed, 0.69 launched.
+  const bool graph = use_graphs && !prof && !lay.small && (n > 1 || lay.uses >= graph_min_uses);
   ++lay.uses;
   // The first iteration bins the sources afresh; the later ones keep its order (see evaluate).  With
   // continue_binning, an iteration right after one of the same layout keeps that order too.
   const bool warm = continue_binning && lay.binned && binned_lay_ == &lay && lay.bin_sc == sc_ &&
                     lay.bin_gen == scratch_gen_;
   if (!graph) {
-    for (int i = 0; i < n; ++i) record_iteration(lay, i > 0 || warm);
+    for (int i = 0; i < n; ++i) record_iteration(lay, i > 0 || warm, i > 0);
     return;
   }
   const uint64_t g = generation();
@@ -1239,7 +1255,7 @@ void Engine::iterate(SetLayout& lay, int n, bool continue_binning) {
     RK_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
     hipGraph_t graph = nullptr;
     try {
-      record_iteration(lay, reuse);
+      record_iteration(lay, reuse, false);
     } catch (...) {
       (void)hipStreamEndCapture(st, &graph);
       if (graph) (void)hipGraphDestroy(graph);

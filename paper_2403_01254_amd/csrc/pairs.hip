@@ -22,7 +22,7 @@
 // perturbations, Sec. V-A) in FP64, and reduces them per block of 256 points.
 #include <cfloat>
 
-#include "block_sort.h"
+#include "edge_sums.h"
 
 namespace rkhsba {
 namespace {
@@ -367,29 +367,6 @@ __global__ __launch_bounds__(kThreads) void k_pairs(PairArgs a) {
 // fixed order, then per edge over the blocks in order; the split into
 // blocks depends only on the edge's source count, so an edge's sums do not
 // depend on what else is evaluated with it.
-constexpr int kStA = 0, kStB = 1, kStXBm = 4, kStQB = 7, kStAx = 10, kStAxx = 13, kStAq = 19, kStSzz = 22,
-              kStXS = 28, kStWr2 = 37, kStF = 38, kStCnt = 39;
-
-// Running sums: FP64, or FP32 with Kahan compensation (option).
-template <typename T>
-struct Acc;
-template <>
-struct Acc<double> {
-  double s = 0.0;
-  __device__ void add(double v) { s += v; }
-  __device__ double value() const { return s; }
-};
-template <>
-struct Acc<float> {
-  float s = 0.f, c = 0.f;
-  __device__ void add(float v) {
-    const float y = v - c;
-    const float t = s + y;
-    c = (t - s) - y;
-    s = t;
-  }
-  __device__ float value() const { return s; }
-};
 
 template <int MODE, typename T>
 __global__ __launch_bounds__(kFinThreads) void k_finalize(FinArgs a, const int32_t* __restrict__ fin_off) {
@@ -501,14 +478,14 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize(FinArgs a, const int32
       st[kStWr2].add(Wr2);
     }
   }
-  // block sum in a fixed order: wavefront shuffles, then the four waves
+  // block sum in a fixed order: over the wavefront, then the four waves
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   constexpr int KC = MODE == MODE_LOSS ? 1 : kStCnt;  // slot of the pair count (summed in FP64 below)
+  T v[NS];
 #pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    const T t = wave_sum(st[k].value());
-    if (lane == 0) sh[w * NS + k] = t;
-  }
+  for (int k = 0; k < NS; ++k) v[k] = st[k].value();
+  const int slot = wave_sum_spread<NS>(v);
+  if (slot < NS) sh[w * NS + slot] = v[0];
   __shared__ double shc[kFinThreads / 64];
   const double wc = wave_sum(cnt_sum);  // all lanes take part in the shuffles
   if (lane == 0) shc[w] = wc;
@@ -525,134 +502,15 @@ __global__ __launch_bounds__(kFinThreads) void k_finalize(FinArgs a, const int32
   }
 }
 
-__device__ inline int sym_index(int r, int c) {  // upper triangle of a 6x6, row-major, r <= c
-  if (r > c) { const int t = r; r = c; c = t; }
-  return r * 6 - (r * (r - 1)) / 2 + (c - r);
-}
-
-// One block per edge: deterministic sum of the edge's finalisation blocks,
-// then the expansion of the 37 sums into F, b_m, b_n, H_mm, H_nn, H_mn.
+// One wavefront per edge.
 template <typename TT>
 __global__ __launch_bounds__(64) void k_edge_reduce(const double* __restrict__ partial,
                                                     const EdgeInfo* __restrict__ edges,
                                                     const EdgeXf* __restrict__ xf, int mode,
                                                     double* __restrict__ edge_out) {
-  __shared__ TT T[kFinStats];
-  __shared__ double n_pairs;
+  __shared__ EdgeSums<TT> sh;
   const EdgeInfo ed = edges[blockIdx.x];
-  const int ns = mode == MODE_LOSS ? 2 : kFinStats;
-  const int kc = ns - 1;  // pair-count slot
-  for (int t = threadIdx.x; t < kFinStats; t += blockDim.x) {
-    if (t == kc) {
-      double c = 0.0;
-      for (int b = 0; b < ed.n_fin; ++b) c += partial[(int64_t)(ed.fin_off + b) * kFinStats + t];
-      n_pairs = c;
-      T[t] = (TT)0;
-      continue;
-    }
-    Acc<TT> s;
-    if (t < ns)
-      for (int b = 0; b < ed.n_fin; ++b) s.add((TT)partial[(int64_t)(ed.fin_off + b) * kFinStats + t]);
-    T[t] = s.value();
-  }
-  __syncthreads();
-  double* out = edge_out + (int64_t)blockIdx.x * kEdgeVals;
-  if (mode == MODE_LOSS) {
-    for (int k = threadIdx.x; k < kEdgeVals; k += blockDim.x)
-      out[k] = k == 0 ? (double)T[0] : k == 91 ? n_pairs : 0.0;  // (sum w r^2 needs the moments)
-    return;
-  }
-  if (threadIdx.x != 0) return;
-  const EdgeXf X = xf[blockIdx.x];
-  TT Rmn[3][3];
-  for (int r = 0; r < 3; ++r)
-    for (int c = 0; c < 3; ++c) Rmn[r][c] = X.R[3 * c + r];
-  const TT A = T[kStA];
-  const TT* B = T + kStB;
-  TT v[kEdgeVals];
-  for (int k = 0; k < kEdgeVals; ++k) v[k] = 0.0;
-  v[0] = T[kStF];
-  for (int r = 0; r < 3; ++r) {
-    v[1 + r] = Rmn[r][0] * B[0] + Rmn[r][1] * B[1] + Rmn[r][2] * B[2];
-    v[4 + r] = T[kStXBm + r];
-    v[7 + r] = -B[r];
-    v[10 + r] = -T[kStQB + r];
-  }
-  auto skew = [](const TT* a, TT (&M)[3][3]) {
-    M[0][0] = 0.0;   M[0][1] = -a[2]; M[0][2] = a[1];
-    M[1][0] = a[2];  M[1][1] = 0.0;   M[1][2] = -a[0];
-    M[2][0] = -a[1]; M[2][1] = a[0];  M[2][2] = 0.0;
-  };
-  const int ri[6] = {0, 0, 0, 1, 1, 2}, ci[6] = {0, 1, 2, 1, 2, 2};
-  TT Axx[3][3], Szz[3][3];
-  for (int k = 0; k < 6; ++k) {
-    Axx[ri[k]][ci[k]] = Axx[ci[k]][ri[k]] = T[kStAxx + k];
-    Szz[ri[k]][ci[k]] = Szz[ci[k]][ri[k]] = T[kStSzz + k];
-  }
-  TT S[3];
-  for (int k = 0; k < 3; ++k) S[k] = T[kStAq + k] - B[k];
-  TT Hmm[6][6], Hnn[6][6], Hmn[6][6];
-  TT Kx[3][3], Ks[3][3];
-  skew(T + kStAx, Kx);
-  skew(S, Ks);
-  const TT trx = Axx[0][0] + Axx[1][1] + Axx[2][2];
-  const TT trs = Szz[0][0] + Szz[1][1] + Szz[2][2];
-  for (int r = 0; r < 3; ++r)
-    for (int c = 0; c < 3; ++c) {
-      const TT I = r == c ? 1.0 : 0.0;
-      Hmm[r][c] = A * I;
-      Hmm[r][3 + c] = -Kx[r][c];
-      Hmm[3 + r][c] = Kx[r][c];
-      Hmm[3 + r][3 + c] = trx * I - Axx[r][c];
-      Hnn[r][c] = A * I;
-      Hnn[r][3 + c] = -Ks[r][c];
-      Hnn[3 + r][c] = Ks[r][c];
-      Hnn[3 + r][3 + c] = trs * I - Szz[r][c];
-    }
-  // H_mn: [[-A R_mn, R_mn [S]], [-[A x] R_mn, sum [x] R_mn [S]]]
-  TT RKs[3][3], KxR[3][3], XRS[3][3];
-  for (int r = 0; r < 3; ++r)
-    for (int c = 0; c < 3; ++c) {
-      RKs[r][c] = Rmn[r][0] * Ks[0][c] + Rmn[r][1] * Ks[1][c] + Rmn[r][2] * Ks[2][c];
-      KxR[r][c] = Kx[r][0] * Rmn[0][c] + Kx[r][1] * Rmn[1][c] + Kx[r][2] * Rmn[2][c];
-      XRS[r][c] = 0.0;
-    }
-  // sum_p [x_p] R_mn [S_p] = sum_{i,j} (sum_p x_i S_j) [e_i] R_mn [e_j]
-  for (int i = 0; i < 3; ++i)
-    for (int j = 0; j < 3; ++j) {
-      const TT mij = T[kStXS + 3 * i + j];
-      TT ei[3] = {0, 0, 0}, ej[3] = {0, 0, 0};
-      ei[i] = 1.0;
-      ej[j] = 1.0;
-      TT Ki[3][3], Kj[3][3];
-      skew(ei, Ki);
-      skew(ej, Kj);
-      for (int r = 0; r < 3; ++r)
-        for (int c = 0; c < 3; ++c) {
-          TT t = 0.0;
-          for (int a0 = 0; a0 < 3; ++a0)
-            for (int b0 = 0; b0 < 3; ++b0) t += Ki[r][a0] * Rmn[a0][b0] * Kj[b0][c];
-          XRS[r][c] += mij * t;
-        }
-    }
-  for (int r = 0; r < 3; ++r)
-    for (int c = 0; c < 3; ++c) {
-      Hmn[r][c] = -A * Rmn[r][c];
-      Hmn[r][3 + c] = RKs[r][c];
-      Hmn[3 + r][c] = -KxR[r][c];
-      Hmn[3 + r][3 + c] = XRS[r][c];
-    }
-  for (int r = 0; r < 6; ++r)
-    for (int c = r; c < 6; ++c) {
-      v[13 + sym_index(r, c)] = Hmm[r][c];
-      v[34 + sym_index(r, c)] = Hnn[r][c];
-    }
-  for (int r = 0; r < 6; ++r)
-    for (int c = 0; c < 6; ++c) v[55 + 6 * r + c] = Hmn[r][c];
-  v[91] = (TT)0;
-  v[92] = T[kStWr2];
-  for (int k = 0; k < kEdgeVals; ++k) out[k] = (double)v[k];
-  out[91] = n_pairs;
+  reduce_edge<TT>(partial, ed, xf[blockIdx.x], mode, sh, edge_out + (int64_t)blockIdx.x * kEdgeVals);
 }
 
 // ---------------------------------------------------------------- pair export (parity)

@@ -363,6 +363,23 @@ struct SolveArgs {
   const int32_t* vec_start;
   const int32_t* vec_list;
 };
+// What follows an evaluation's finalisation: nothing but the per-edge values, the loss and pair-count history
+// entry, also H and b, or the whole Gauss-Newton step.
+enum Step { STEP_NONE = 0, STEP_LOSS = 1, STEP_SYSTEM = 2, STEP_SOLVE = 3 };
+struct StepArgs {
+  const double* partial;   // finalisation partial sums
+  const EdgeInfo* edges;
+  EdgeXf* xf;              // STEP_SOLVE leaves those of the moved poses
+  double* edge_out;
+  uint32_t* n_items;       // cleared (nullable)
+};
+// Whether one workgroup takes a problem's whole step: the system fits in LDS, and its edges and their finalisation
+// blocks are few enough for 16 wavefronts (4 edges each, 2 us an edge; the reduction of more spreads over the chip).
+constexpr int kStepEdges = 64;
+constexpr int64_t kStepFinBlocks = 4096;
+bool small_step(const ProbSys& S, int64_t fin_blocks);
+// The step of every problem of a set of small ones.
+hipError_t launch_step(const SolveArgs& a, const StepArgs& u, int mode, int step, bool fp32_sums, hipStream_t st);
 // Writes H, b of every problem (and the loss / pair-count history entry of the
 // current iteration).
 hipError_t launch_assemble(const SolveArgs& a, hipStream_t st);

@@ -517,8 +517,7 @@ struct rkhsba_server {
           // result does not depend on when other requests join or leave.
           const bool solo = max_active == 1;
           if (all_final) {
-            L.eng->evaluate(L.lay, MODE_LOSS, solo);
-            L.eng->loss_only(L.lay);
+            L.eng->evaluate(L.lay, MODE_LOSS, solo, STEP_LOSS);
           } else {
             L.eng->iterate(L.lay, 1, solo);
           }

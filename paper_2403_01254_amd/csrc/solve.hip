@@ -6,14 +6,14 @@
 // Assembly is one thread per entry of the system, summing that entry's
 // contributing edge blocks in edge order (host-built lists, deterministic).
 // The solve is one workgroup per problem: systems up to 128 unknowns are
-// eliminated in LDS (one barrier per column, no square roots) and solved in
-// one wavefront; larger ones run a blocked right-looking Cholesky with
-// 32-wide panels, the panel kept in LDS for the trailing update.
-#include "rkhsba_device.h"
+// eliminated in LDS, one frame's columns at a time; larger ones run a blocked
+// right-looking Cholesky with 32-wide panels, the panel kept in LDS for the
+// trailing update.  Sets of small problems run the whole step, from the
+// finalisation's partial sums to the moved poses, in one kernel (k_step).
+#include "edge_sums.h"
 
 namespace rkhsba {
 namespace {
-
 
 __device__ inline int sym_index(int r, int c) {
   if (r > c) { const int t = r; r = c; c = t; }
@@ -23,59 +23,63 @@ __device__ inline int sym_index(int r, int c) {
 // reduced index <-> frame when frame `fixed` is removed (fixed < 0: none)
 __device__ inline int frame_of_reduced(int k, int fixed) { return (fixed >= 0 && k >= fixed) ? k + 1 : k; }
 
+// Entry (row, col) of problem S's H, and entry `row` of its b: the contributing edges' values in edge order.
+__device__ inline double h_entry(const SolveArgs& a, const ProbSys& S, int row, int col) {
+  const int fa = frame_of_reduced(row / 6, S.fixed), fc = frame_of_reduced(col / 6, S.fixed);
+  const int r = row % 6, s = col % 6;
+  const int32_t* start = a.blk_start + S.blk0 + fa * S.K + fc;
+  double v = 0.0;
+  for (int k = start[0]; k < start[1]; ++k) {
+    const int code = a.blk_list[k];
+    const double* eo = a.edge_out + (int64_t)(code >> 2) * kEdgeVals;
+    switch (code & 3) {
+      case 0: v += eo[13 + sym_index(r, s)]; break;
+      case 1: v += eo[34 + sym_index(r, s)]; break;
+      case 2: v += eo[55 + 6 * r + s]; break;
+      default: v += eo[55 + 6 * s + r]; break;
+    }
+  }
+  return v;
+}
+__device__ inline double b_entry(const SolveArgs& a, const ProbSys& S, int row) {
+  const int fa = frame_of_reduced(row / 6, S.fixed), r = row % 6;
+  const int32_t* start = a.vec_start + S.vec0 + fa;
+  double v = 0.0;
+  for (int k = start[0]; k < start[1]; ++k) {
+    const int code = a.vec_list[k];
+    v += a.edge_out[(int64_t)(code >> 1) * kEdgeVals + ((code & 1) ? 7 : 1) + r];
+  }
+  return v;
+}
+
 // One thread per entry of a problem's system (grid.y = problem).
 __global__ __launch_bounds__(256) void k_assemble(SolveArgs a) {
   const ProbSys S = a.sys[blockIdx.y];
   const int n = S.n;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int32_t* blk_start = a.blk_start + S.blk0;
-  const int32_t* vec_start = a.vec_start + S.vec0;
-  if (idx < (int64_t)n * n) {
-    const int row = (int)(idx / n), col = (int)(idx % n);
-    const int fa = frame_of_reduced(row / 6, S.fixed), fc = frame_of_reduced(col / 6, S.fixed);
-    const int r = row % 6, s = col % 6;
-    const int blk = fa * S.K + fc;
-    double v = 0.0;
-    for (int k = blk_start[blk]; k < blk_start[blk + 1]; ++k) {
-      const int code = a.blk_list[k];
-      const double* eo = a.edge_out + (int64_t)(code >> 2) * kEdgeVals;
-      switch (code & 3) {
-        case 0: v += eo[13 + sym_index(r, s)]; break;
-        case 1: v += eo[34 + sym_index(r, s)]; break;
-        case 2: v += eo[55 + 6 * r + s]; break;
-        default: v += eo[55 + 6 * s + r]; break;
-      }
-    }
-    a.H[S.h_off + idx] = v;
-  } else if (idx < (int64_t)n * n + n) {
-    const int row = (int)(idx - (int64_t)n * n);
-    const int fa = frame_of_reduced(row / 6, S.fixed), r = row % 6;
-    double v = 0.0;
-    for (int k = vec_start[fa]; k < vec_start[fa + 1]; ++k) {
-      const int code = a.vec_list[k];
-      v += a.edge_out[(int64_t)(code >> 1) * kEdgeVals + ((code & 1) ? 7 : 1) + r];
-    }
-    a.b[S.v_off + row] = v;
-  }
+  if (idx < (int64_t)n * n) a.H[S.h_off + idx] = h_entry(a, S, (int)(idx / n), (int)(idx % n));
+  else if (idx < (int64_t)n * n + n) a.b[S.v_off + idx - (int64_t)n * n] = b_entry(a, S, (int)(idx - (int64_t)n * n));
 }
 
-// F (times sigma^2) and the pair count of the current evaluation of each
-// problem (one wavefront per problem, fixed summation order).
-__global__ __launch_bounds__(64) void k_loss_only(SolveArgs a) {
-  const ProbSys S = a.sys[blockIdx.x];
+// F (times sigma^2) and the pair count of the current evaluation of a problem (one wavefront, fixed summation
+// order).
+__device__ inline void record_loss(const SolveArgs& a, const ProbSys& S) {
+  const int lane = threadIdx.x & 63;
   double F = 0.0, np = 0.0;
-  for (int e = S.e0 + (int)threadIdx.x; e < S.e0 + S.E; e += 64) {
+  for (int e = S.e0 + lane; e < S.e0 + S.E; e += 64) {
     F += a.edge_out[(int64_t)e * kEdgeVals];
     np += a.edge_out[(int64_t)e * kEdgeVals + 91];
   }
   F = wave_sum(F);
   np = wave_sum(np);
   const int iter = a.state[S.state_off];
-  if (threadIdx.x == 0 && iter >= 0 && iter <= S.n_iter) {
+  if (lane == 0 && iter >= 0 && iter <= S.n_iter) {
     a.loss_hist[S.hist_off + iter] = S.sigma2 * F;
     a.pairs_hist[S.hist_off + iter] = np;
   }
 }
+
+__global__ __launch_bounds__(64) void k_loss_only(SolveArgs a) { record_loss(a, a.sys[blockIdx.x]); }
 
 // T <- T exp(xi^): closed-form SE(3) exponential (Rodrigues for the rotation,
 // V = I + B K + C K^2 for the translation), series for small angles.
@@ -139,6 +143,113 @@ __device__ inline double lane_value(double v, int lane) {
   return __hiloint2double(hi, lo);
 }
 
+// ---- systems that fit in LDS (n <= kLdsSystem unknowns, 6 per frame)
+//
+// (H + mu I) delta = -b as L D L^T delta = -b (L unit lower triangular, no square roots), eliminated right-looking
+// in blocks of one frame's 6 columns, with -b as one more row: after the elimination row n holds y = D^-1 L^-1 (-b),
+// and L^T delta = y is solved in one wavefront with two rows per lane.  A block step has two barriers; the threads
+// of the rows below each factor the 6 x 6 diagonal block for themselves (it is short, and a barrier less).  One
+// column per barrier and a separate forward solve took 0.7 us per unknown (n = 42: 32 us a solve; now the whole step
+// around it takes 17).
+constexpr int kSolveThreads = 1024;
+constexpr int kLdsSystem = 128;
+constexpr int kLdsDoubles = kLdsSystem * (kLdsSystem + 1);  // shared buffer of both paths
+
+struct SmallShared {
+  double A[(kLdsSystem + 1) * (kLdsSystem + 1)];  // rows 0 .. n (n: -b), row stride n + 1; lower triangle used
+  double t[6][kLdsSystem + 1];                    // the panel's rows before the division by the pivots
+  int bad;                                        // a pivot was not positive
+};
+
+// 1 / d to within an ulp: the hardware estimate and two Newton steps, a third of a division's chain.  The ends of
+// the range, where the estimate or a step could leave it, divide.
+__device__ inline double reciprocal(double d) {
+  if (!(d > 1e-290 && d < 1e290)) return 1.0 / d;
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(fma(-d, r, 1.0), r, r);
+  return fma(fma(-d, r, 1.0), r, r);
+}
+
+// S.A holds the lower triangle of H + mu I and -b; all threads of the block.  Solution in y (global, n); false (in
+// every thread) when a pivot is not positive.
+__device__ bool solve_small(int n, SmallShared& S, double* __restrict__ y) {
+  const int t = threadIdx.x, tx = t & 31, ty = t >> 5, ld = n + 1;
+  double* A = S.A;
+  if (t == 0) S.bad = 0;
+  __syncthreads();
+  for (int p = 0; p < n; p += 6) {
+    const int m0 = p + 6;
+    // rows below the block, and its own first row's thread (for the pivot test of the last block)
+    if (t <= n - m0) {
+      const int i = m0 + t;
+      double d[6][6], x[6], rd[6];
+      bool ok = true;
+#pragma unroll
+      for (int r = 0; r < 6; ++r)
+#pragma unroll
+        for (int c = 0; c <= r; ++c) d[r][c] = A[(p + r) * ld + p + c];
+#pragma unroll
+      for (int c = 0; c < 6; ++c) x[c] = A[i * ld + p + c];
+      // the block's L (below the diagonal of d) and pivots, column by column; the row in step with it
+#pragma unroll
+      for (int j = 0; j < 6; ++j) {
+        ok = ok && d[j][j] > 0.0;
+        rd[j] = reciprocal(d[j][j]);
+#pragma unroll
+        for (int r = j + 1; r < 6; ++r) {
+          const double l = d[r][j] * rd[j];
+#pragma unroll
+          for (int c = j + 1; c <= r; ++c) d[r][c] = fma(-l, d[c][j], d[r][c]);
+        }
+        const double l = x[j] * rd[j];
+#pragma unroll
+        for (int c = j + 1; c < 6; ++c) x[c] = fma(-l, d[c][j], x[c]);
+      }
+      if (!ok) S.bad = 1;
+#pragma unroll
+      for (int c = 0; c < 6; ++c) {
+        S.t[c][i] = x[c];
+        A[i * ld + p + c] = x[c] * rd[c];
+      }
+      if (t == n - m0) {  // (row n's thread) the block's own L, for the backward solve
+#pragma unroll
+        for (int r = 1; r < 6; ++r)
+#pragma unroll
+          for (int c = 0; c < r; ++c) S.t[c][p + r] = d[r][c] * rd[c];
+      }
+    }
+    __syncthreads();
+    if (S.bad) return false;  // every thread reads the same flag
+    // trailing rows and columns, row n included; the block's L moves to its place
+    for (int i = m0 + ty; i <= n; i += 32)
+      for (int k = m0 + tx; k <= min(i, n - 1); k += 32) {
+        double v = A[i * ld + k];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) v = fma(-S.t[c][i], A[k * ld + p + c], v);
+        A[i * ld + k] = v;
+      }
+    if (t < 36) {
+      const int r = t / 6, c = t % 6;
+      if (c < r) A[(p + r) * ld + p + c] = S.t[c][p + r];
+    }
+    __syncthreads();
+  }
+  if (t < 64) {  // L^T x = y, columns from the last
+    double u0 = t < n ? A[n * ld + t] : 0.0, u1 = t + 64 < n ? A[n * ld + t + 64] : 0.0;
+#pragma unroll 6
+    for (int j = n - 1; j > 0; --j) {
+      const double l0 = t < j ? A[j * ld + t] : 0.0, l1 = t + 64 < j ? A[j * ld + t + 64] : 0.0;
+      const double xj = lane_value(j < 64 ? u0 : u1, j & 63);
+      u0 = fma(-l0, xj, u0);
+      u1 = fma(-l1, xj, u1);
+    }
+    if (t < n) y[t] = u0;
+    if (t + 64 < n) y[t + 64] = u1;
+  }
+  __syncthreads();
+  return true;
+}
+
 // Right-looking elimination of an n x n symmetric block held in LDS (row
 // stride ld, lower triangle used), without square roots: step j subtracts
 // a_ij a_kj / d_j from every trailing entry (j < k <= i), d_j the pivot of
@@ -160,53 +271,6 @@ __device__ bool eliminate_lds(double* A, int n, int ld, double* rd) {
     __syncthreads();
   }
   return true;
-}
-
-// ---- systems that fit in LDS (n <= kLdsSystem)
-//
-// (H + mu I) delta = -b as M D^-1 M^T delta = -b: forward M u = -b, then
-// M^T delta = D u, both in wavefront 0 with two rows per lane.
-constexpr int kSolveThreads = 1024;
-constexpr int kLdsSystem = 128;
-constexpr int kLdsDoubles = kLdsSystem * (kLdsSystem + 1);  // shared buffer of both paths
-
-__device__ void solve_lds(const ProbSys& S, const SolveArgs& a, double mu, double* A, double* rd, int32_t* status) {
-  const int n = S.n, ld = n + 1;  // odd stride: column reads spread over the banks
-  const int t = threadIdx.x;
-  const double* H = a.H + S.h_off;
-  for (int idx = t; idx < n * n; idx += kSolveThreads) {
-    const int i = idx / n, k = idx - i * n;
-    if (k <= i) A[i * ld + k] = H[idx] + (i == k ? mu : 0.0);
-  }
-  __syncthreads();
-  const bool ok = eliminate_lds(A, n, ld, rd);
-  if (!ok) {
-    if (t == 0) *status = -4;
-    return;
-  }
-  if (t < 64) {
-    const double* b = a.b + S.v_off;
-    double u0 = t < n ? -b[t] : 0.0, u1 = t + 64 < n ? -b[t + 64] : 0.0;
-    // forward: u_j = (r_j - sum_{k<j} M_jk u_k) / d_j
-    for (int j = 0; j < n; ++j) {
-      const double uj = lane_value(j < 64 ? u0 : u1, j & 63) * rd[j];
-      if (t == (j & 63)) {
-        if (j < 64) u0 = uj; else u1 = uj;
-      }
-      if (t > j && t < n) u0 -= A[t * ld + j] * uj;
-      if (t + 64 > j && t + 64 < n) u1 -= A[(t + 64) * ld + j] * uj;
-    }
-    // backward: x_j = u_j - (1/d_j) sum_{k>j} M_kj x_k, columns from the last
-    for (int j = n - 1; j >= 0; --j) {
-      const double xj = lane_value(j < 64 ? u0 : u1, j & 63);
-      if (t < j) u0 -= rd[t] * A[j * ld + t] * xj;
-      if (t + 64 < j) u1 -= rd[t + 64] * A[j * ld + t + 64] * xj;
-    }
-    double* y = a.delta + S.v_off;
-    if (t < n) y[t] = u0;
-    if (t + 64 < n) y[t + 64] = u1;
-  }
-  __syncthreads();
 }
 
 // ---- larger systems: blocked right-looking Cholesky in global memory
@@ -498,39 +562,116 @@ __device__ void solve_blocked(const ProbSys& S, const SolveArgs& a, double mu, d
   }
 }
 
+union SolveShared {
+  SmallShared small;
+  struct {
+    double buf[kLdsDoubles];
+    uint32_t zflags[kFlagWords];
+  } blocked;
+};
+
 // One workgroup per problem: damped solve and pose update.  A problem whose
 // iteration count has reached n_iter (its last evaluation gave the final
 // loss) is left unchanged.  Every branch below is block-uniform.
 __global__ __launch_bounds__(kSolveThreads) void k_solve_update(SolveArgs a) {
-  __shared__ double buf[kLdsDoubles];
-  __shared__ uint32_t zflags[kFlagWords];
-  __shared__ double rd[kLdsSystem];
-  __shared__ double sh[kSolveThreads / 64];
+  __shared__ SolveShared sh;
+  __shared__ double red[kSolveThreads / 64];
   const ProbSys S = a.sys[blockIdx.x];
   int32_t* st = a.state + S.state_off;
   const int iter = st[0];
   const bool run = iter < S.n_iter && st[1] == 0 && S.n > 0;
   __syncthreads();
   if (run) {
-    const int n = S.n;
+    const int n = S.n, t = threadIdx.x;
     const double* H = a.H + S.h_off;
     double tr = 0.0;
-    for (int i = threadIdx.x; i < n; i += kSolveThreads) tr += H[(int64_t)i * n + i];
-    tr = block_sum(tr, sh);
+    for (int i = t; i < n; i += kSolveThreads) tr += H[(int64_t)i * n + i];
+    tr = block_sum(tr, red);
     if (tr > 0.0) {  // otherwise no pair touches a free frame: nothing moves
       const double mu = S.damping_rel * tr / n;
-      if (n <= kLdsSystem) solve_lds(S, a, mu, buf, rd, st + 1);
-      else solve_blocked(S, a, mu, buf, st + 1, zflags);
+      if (n <= kLdsSystem) {
+        for (int idx = t; idx < n * n; idx += kSolveThreads) {
+          const int i = idx / n, k = idx - i * n;
+          if (k <= i) sh.small.A[i * (n + 1) + k] = H[idx] + (i == k ? mu : 0.0);
+        }
+        for (int i = t; i < n; i += kSolveThreads) sh.small.A[n * (n + 1) + i] = -a.b[S.v_off + i];
+        if (!solve_small(n, sh.small, a.delta + S.v_off) && t == 0) st[1] = -4;
+      } else {
+        solve_blocked(S, a, mu, sh.blocked.buf, st + 1, sh.blocked.zflags);
+      }
       __syncthreads();
       if (st[1] == 0) {
         const double* y = a.delta + S.v_off;
-        for (int k = threadIdx.x; k < n / 6; k += kSolveThreads)
+        for (int k = t; k < n / 6; k += kSolveThreads)
           right_update(a.poses + 12 * (S.slot0 + frame_of_reduced(k, S.fixed)), y + 6 * k);
       }
     }
   }
   __syncthreads();
   if (threadIdx.x == 0 && iter <= S.n_iter) st[0] = iter + 1;
+}
+
+// What follows an evaluation's finalisation, for sets of small problems (small_step): one workgroup per problem sums
+// and expands its edges, one wavefront each, records the loss, and then writes H and b as well (STEP_SYSTEM), or
+// (STEP_SOLVE) assembles the system in LDS, solves it, moves the poses and prepares the next evaluation's edge
+// transforms.  The same operations in the same order as k_edge_reduce, k_assemble, k_loss_only,
+// k_solve_update and k_edge_setup, which a large set needs more than one workgroup for: launches and the gaps
+// between them are most of a small iteration (2 frames x 5,000 points: 57 us an iteration, now
+// 36, of which this kernel 12.4; 8 frames and 28 edges of 2,000 points: 17 us).
+template <int MODE, int STEP, typename TT>
+__global__ __launch_bounds__(kSolveThreads) void k_step(SolveArgs a, StepArgs u) {
+  __shared__ SmallShared sh;
+  __shared__ EdgeSums<TT> sums[kSolveThreads / 64];
+  __shared__ double red[kSolveThreads / 64];
+  const ProbSys S = a.sys[blockIdx.x];
+  const int t = threadIdx.x, w = t >> 6;
+  if (blockIdx.x == 0 && t == 0 && u.n_items) *u.n_items = 0u;  // of the next evaluation's sweep
+  for (int e = S.e0 + w; e < S.e0 + S.E; e += kSolveThreads / 64)
+    reduce_edge<TT>(u.partial, u.edges[e], u.xf[e], MODE, sums[w], u.edge_out + (int64_t)e * kEdgeVals);
+  __threadfence_block();
+  __syncthreads();
+  if (w == 0) record_loss(a, S);
+  const int n = S.n;
+  if constexpr (STEP == STEP_SYSTEM) {
+    for (int idx = t; idx < n * n; idx += kSolveThreads) a.H[S.h_off + idx] = h_entry(a, S, idx / n, idx % n);
+    for (int i = t; i < n; i += kSolveThreads) a.b[S.v_off + i] = b_entry(a, S, i);
+  }
+  if constexpr (STEP == STEP_SOLVE) {
+    int32_t* st = a.state + S.state_off;
+    const int iter = st[0];
+    const bool run = iter < S.n_iter && st[1] == 0 && n > 0;
+    if (run) {
+      double* A = sh.A;
+      for (int idx = t; idx < n * n; idx += kSolveThreads) {
+        const int i = idx / n, k = idx - i * n;
+        if (k <= i) A[i * (n + 1) + k] = h_entry(a, S, i, k);
+      }
+      for (int i = t; i < n; i += kSolveThreads) A[n * (n + 1) + i] = -b_entry(a, S, i);
+      __syncthreads();
+      double tr = 0.0;
+      for (int i = t; i < n; i += kSolveThreads) tr += A[i * (n + 1) + i];
+      tr = block_sum(tr, red);
+      if (tr > 0.0) {  // otherwise no pair touches a free frame: nothing moves
+        const double mu = S.damping_rel * tr / n;
+        for (int i = t; i < n; i += kSolveThreads) A[i * (n + 1) + i] += mu;
+        if (solve_small(n, sh, a.delta + S.v_off)) {
+          const double* y = a.delta + S.v_off;
+          for (int k = t; k < n / 6; k += kSolveThreads)
+            right_update(a.poses + 12 * (S.slot0 + frame_of_reduced(k, S.fixed)), y + 6 * k);
+        } else if (t == 0) {
+          st[1] = -4;
+        }
+      }
+    }
+    __threadfence_block();
+    __syncthreads();
+    if (t == 0 && iter <= S.n_iter) st[0] = iter + 1;
+    for (int e = S.e0 + t; e < S.e0 + S.E; e += kSolveThreads) {
+      EdgeXf o;
+      rule_relative(a.poses + 12 * u.edges[e].m, a.poses + 12 * u.edges[e].n, o.R, o.t);
+      u.xf[e] = o;
+    }
+  }
 }
 
 }  // namespace
@@ -541,6 +682,33 @@ hipError_t launch_assemble(const SolveArgs& a, hipStream_t st) {
   const int64_t work = n * n + n;
   if (work > 0) k_assemble<<<dim3((unsigned)((work + 255) / 256), (unsigned)a.n_prob), 256, 0, st>>>(a);
   k_loss_only<<<a.n_prob, 64, 0, st>>>(a);
+  return hipGetLastError();
+}
+
+template <int MODE, typename TT>
+static void run_step(const SolveArgs& a, const StepArgs& u, int step, hipStream_t st) {
+  const unsigned nb = (unsigned)a.n_prob;
+  if (step == STEP_LOSS) k_step<MODE, STEP_LOSS, TT><<<nb, kSolveThreads, 0, st>>>(a, u);
+  else if constexpr (MODE == MODE_NORMAL) {
+    if (step == STEP_SYSTEM) k_step<MODE, STEP_SYSTEM, TT><<<nb, kSolveThreads, 0, st>>>(a, u);
+    else k_step<MODE, STEP_SOLVE, TT><<<nb, kSolveThreads, 0, st>>>(a, u);
+  }
+}
+
+bool small_step(const ProbSys& S, int64_t fin_blocks) {
+  return S.n <= kLdsSystem && S.E <= kStepEdges && fin_blocks <= kStepFinBlocks;
+}
+
+hipError_t launch_step(const SolveArgs& a, const StepArgs& u, int mode, int step, bool fp32_sums, hipStream_t st) {
+  if (a.n_prob <= 0) return hipSuccess;
+  if (step == STEP_NONE || (mode == MODE_LOSS && step > STEP_LOSS)) return hipErrorInvalidValue;
+  if (mode == MODE_LOSS) {
+    if (fp32_sums) run_step<MODE_LOSS, float>(a, u, step, st);
+    else run_step<MODE_LOSS, double>(a, u, step, st);
+  } else {
+    if (fp32_sums) run_step<MODE_NORMAL, float>(a, u, step, st);
+    else run_step<MODE_NORMAL, double>(a, u, step, st);
+  }
   return hipGetLastError();
 }
 
