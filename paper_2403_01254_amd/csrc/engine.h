@@ -286,8 +286,8 @@ class Engine {
   // device pointers) and keeps it resident.  Returns its id.
   int add_problem(const ProbParams& par, int K, const int64_t* n_points, const float* const* xyz, int kind, int D,
                   const void* const* feats, bool is_device);
-  // As add_problem; cell_subdiv == 0 picks the cell size from the occupancy
-  // of a first build with cells of edge r_c (tuned table, else a default rule).
+  // As add_problem; cell_subdiv == 0 or pass_points == 0 picks the cell or pass size from the occupancy of cells of
+  // edge r_c (tuned table, else a default rule).
   int add_problem_auto(const ProbParams& par, int K, const int64_t* n_points, const float* const* xyz, int kind,
                        int D, const void* const* feats, bool is_device);
   // (cell_subdiv, pass_points) for frames with this many points per occupied r_c-cube
@@ -375,6 +375,8 @@ class Engine {
   void prof_collect();
 
  private:
+  int build(ProbParams par, int K, const int64_t* n_points, const float* const* xyz, int kind, int D,
+            const void* const* feats, bool is_device, bool choose);
   void compute_constants(Problem* p);
   void record_iteration(SetLayout& lay, bool reuse_binning, bool xf_ready);
   void edge_setup(SetLayout& lay);
@@ -397,12 +399,12 @@ class Engine {
   DBuf<const void*> d_feat_ptrs_;
   DBuf<int64_t> d_in_off_;
   DBuf<FrameInfo> d_bframes_;
-  DBuf<int32_t> cell_, minmax_;
+  DBuf<int32_t> minmax_;
   DBuf<uint32_t> k1_, v1_, k2_, v2_, hist_scratch_;
   DBuf<SortTile> d_tiles_;
   DBuf<SortSeg> d_segs_;
   DBuf<uint32_t> row_sizes_, scan_tmp_;
-  DBuf<uint64_t> d_total_;
+  DBuf<uint64_t> d_totals_;
   DBuf<int64_t> d_lab_off_;
   DBuf<int32_t> d_lab_start_;
 

@@ -226,7 +226,7 @@ Problem* Engine::problem(int id) {
 int64_t Engine::device_bytes() const {
   int64_t b = (int64_t)(points_.bytes() + rows_.bytes() + xtab_.bytes() + slots_.bytes() + hist_.bytes() +
                         state_.bytes());
-  b += (int64_t)(raw_xyz_.bytes() + raw_feat_.bytes() + cell_.bytes() + k1_.bytes() + v1_.bytes() + k2_.bytes() +
+  b += (int64_t)(raw_xyz_.bytes() + raw_feat_.bytes() + k1_.bytes() + v1_.bytes() + k2_.bytes() +
                  v2_.bytes() + hist_scratch_.bytes() + row_sizes_.bytes() + scan_tmp_.bytes());
   const EvalScratch& o = own_sc_;
   b += (int64_t)(o.xf.bytes() + o.bk.bytes() + o.bv.bytes() + o.bk2.bytes() + o.bv2.bytes() + o.bhist.bytes() +
@@ -281,6 +281,26 @@ void Engine::compute_constants(Problem* p) {
 
 int Engine::add_problem(const ProbParams& par, int K, const int64_t* n_points, const float* const* xyz, int kind,
                         int Din, const void* const* feats, bool is_device) {
+  return build(par, K, n_points, xyz, kind, Din, feats, is_device, false);
+}
+
+int Engine::add_problem_auto(const ProbParams& par_in, int K, const int64_t* n_points, const float* const* xyz,
+                             int kind, int Din, const void* const* feats, bool is_device) {
+  ProbParams par = par_in;
+  if (par.top_k > 0) par.pass_points = 1;  // the top-k selection runs in the per-point walks
+  return build(par, K, n_points, xyz, kind, Din, feats, is_device, par.cell_subdiv == 0 || par.pass_points == 0);
+}
+
+// With `choose`, the points are first sorted into cells of one truncation radius; their occupancy picks what par
+// leaves open (choose_config), and where that is another cell size they are sorted again, before anything is
+// gathered.
+int Engine::build(ProbParams par_in, int K, const int64_t* n_points, const float* const* xyz, int kind, int Din,
+                  const void* const* feats, bool is_device, bool choose) {
+  ProbParams par = par_in;
+  if (choose) {
+    par.cell_subdiv = 1;
+    if (par.pass_points == 0) par.pass_points = 16;
+  }
   RK_REQUIRE(K >= 1 && n_points && xyz && feats, RKHSBA_EINVAL, "K >= 1 and non-NULL n_points/xyz/feats required");
   RK_REQUIRE(kind == RKHSBA_FEAT_CLASS_ID || kind == RKHSBA_FEAT_DENSE_F32 || kind == RKHSBA_FEAT_DENSE_BF16 ||
                  kind == RKHSBA_FEAT_DENSE_FP8,
@@ -325,8 +345,6 @@ int Engine::add_problem(const ProbParams& par, int K, const int64_t* n_points, c
   p->K = K;
   p->N = N;
   p->n_points.assign(n_points, n_points + K);
-  compute_constants(p);
-  const KConst kc0 = p->kc;
   const size_t fbytes = kind == RKHSBA_FEAT_CLASS_ID ? sizeof(uint16_t) : sizeof(float) * (size_t)Din;
 
   auto release = [&]() {
@@ -374,113 +392,30 @@ int Engine::add_problem(const ProbParams& par, int K, const int64_t* n_points, c
     RK_HIP(hipMemcpyAsync(d_feat_ptrs_.p, fp.data(), sizeof(void*) * K, hipMemcpyHostToDevice, bst));
     RK_HIP(hipMemcpyAsync(d_in_off_.p, off.data(), sizeof(int64_t) * (K + 1), hipMemcpyHostToDevice, bst));
 
-    // cell coordinates and per-frame bounds (and largest class ids)
+    // per-frame bounds (and largest class ids)
     const int n_dmin = kind == RKHSBA_FEAT_DENSE_F32 ? Dp : 0;  // per-dimension minima of FP32 features
     const bool class_ids = kind == RKHSBA_FEAT_CLASS_ID;
-    const int lab0 = 6 * K + 3 + n_dmin;                          // per-frame largest class id
+    const int lab0 = 6 * K + 2 + n_dmin;                          // per-frame largest class id
     std::vector<int32_t> mm(lab0 + (class_ids ? K : 0), -1);
     for (int f = 0; f < K; ++f)
       for (int a = 0; a < 3; ++a) {
-        mm[6 * f + a] = INT_MAX;
-        mm[6 * f + 3 + a] = INT_MIN;
+        mm[6 * f + a] = -1;
+        mm[6 * f + 3 + a] = 0;
       }
     mm[6 * K] = 0;      // bad coordinate flag
     mm[6 * K + 1] = 0;  // negative feature flag
-    mm[6 * K + 2] = 0;  // occupied cells
-    for (int d = 0; d < n_dmin; ++d) mm[6 * K + 3 + d] = 0x7f800000;  // feature minima (+inf until the build)
-    RK_HIP(cell_.reserve((size_t)N * 3));
+    for (int d = 0; d < n_dmin; ++d) mm[6 * K + 2 + d] = 0x7f800000;  // feature minima (+inf until the build)
     RK_HIP(minmax_.reserve(mm.size()));
     RK_HIP(hipMemcpyAsync(minmax_.p, mm.data(), sizeof(int32_t) * mm.size(), hipMemcpyHostToDevice, bst));
-    RK_HIP(launch_cell_coords(d_xyz_ptrs_.p, d_in_off_.p, K, N, kc0.inv_cell, d_feat_ptrs_.p, cell_.p, minmax_.p,
-                              class_ids ? minmax_.p + lab0 : nullptr, bst));
+    RK_HIP(launch_frame_bounds(d_xyz_ptrs_.p, d_in_off_.p, K, *std::max_element(n_points, n_points + K),
+                               d_feat_ptrs_.p, reinterpret_cast<uint32_t*>(minmax_.p), minmax_.p + 6 * K,
+                               class_ids ? minmax_.p + lab0 : nullptr, bst));
     RK_HIP(hipMemcpyAsync(mm.data(), minmax_.p, sizeof(int32_t) * mm.size(), hipMemcpyDeviceToHost, bst));
     RK_HIP(hipStreamSynchronize(bst));
     RK_REQUIRE(mm[6 * K] == 0, RKHSBA_EINVAL, "non-finite or out-of-range point coordinate");
 
-    // grids (frame-local offsets for the build)
-    std::vector<FrameInfo> fr(K);
-    int64_t rows_total = 0;
-    uint64_t max_cells = 1;
-    int bin_axis_bits = 1;
-    std::vector<int> frame_bits(K);  // per-axis bits of a frame's cell coordinates (negative: coarsened)
-    for (int f = 0; f < K; ++f) {
-      FrameInfo& F = fr[f];
-      F.pt_off = off[f];
-      F.n = (int32_t)n_points[f];
-      uint64_t cells = 1;
-      for (int a = 0; a < 3; ++a) {
-        F.org[a] = mm[6 * f + a];
-        const int64_t d = (int64_t)mm[6 * f + 3 + a] - mm[6 * f + a] + 1;
-        RK_REQUIRE(d >= 1 && d < (1 << 24), RKHSBA_ENOMEM, "frame extent too large for its cell grid");
-        F.dim[a] = (int32_t)d;
-        cells *= (uint64_t)d;
-      }
-      RK_REQUIRE(cells < 0xffffffffull, RKHSBA_ENOMEM,
-                 "frame spans more than 2^32 cells; raise ell or lower cell_subdiv");
-      max_cells = std::max(max_cells, cells);
-      F.xt_off = 0;
-      F.n_lab = 0;
-      F.key_sub = 0;
-      int ext_max = 0;
-      for (int a = 0; a < 3; ++a) ext_max = std::max(ext_max, F.dim[a] + 2 * kc0.reach_cells);
-      int shift = 0;
-      while (((ext_max - 1) >> shift) >= 1023) ++shift;
-      F.mort_shift = shift;
-      const int maxc = (ext_max - 1) >> shift;
-      int bits = 1;
-      while ((1 << bits) < maxc + 2) ++bits;
-      frame_bits[f] = shift == 0 ? bits : -bits;
-      bin_axis_bits = std::max(bin_axis_bits, bits);
-    }
-    // The binning keys order the source points of a cell by sub-cell (Morton order at a finer grid), as
-    // far as that fits the radix passes the cells already take: the passes' groups of consecutive points
-    // then span smaller boxes, whose walks hold fewer candidates that pair with none of the group.
-    {
-      const int axis_room = (8 * ((3 * bin_axis_bits + 7) / 8)) / 3;  // axis bits the same digit passes sort
-      for (int f = 0; f < K; ++f) {
-        if (frame_bits[f] < 0) continue;  // coarsened grid (mort_shift > 0)
-        fr[f].key_sub = std::max(0, std::min({3, axis_room - frame_bits[f], 10 - frame_bits[f]}));
-        bin_axis_bits = std::max(bin_axis_bits, frame_bits[f] + fr[f].key_sub);
-      }
-    }
-    // Class ids: every frame stacks one layer of its z extent per class id (0 .. its largest id) along z,
-    // so that points of one id are contiguous and the sweeps walk only the candidates that can pair.  Kept
-    // only while the keys fit 32 bits and the row table stays within 16 rows per point (+ 2^20).
-    bool stacked = class_ids;
-    {
-      int64_t rows_stacked = 0;
-      for (int f = 0; f < K && stacked; ++f) {
-        const int64_t n_lab = (int64_t)mm[lab0 + f] + 1;
-        const uint64_t cells = (uint64_t)fr[f].dim[0] * fr[f].dim[1] * fr[f].dim[2];
-        stacked = n_lab >= 1 && cells * (uint64_t)n_lab < 0xffffffffull;
-        rows_stacked += (int64_t)fr[f].dim[1] * fr[f].dim[2] * n_lab;
-      }
-      stacked = stacked && rows_stacked < (1LL << 31) && rows_stacked <= 16 * N + (1LL << 20);
-    }
-    for (int f = 0; f < K; ++f) {
-      FrameInfo& F = fr[f];
-      F.n_lab = stacked ? mm[lab0 + f] + 1 : 0;
-      F.row_off = rows_total;
-      rows_total += (int64_t)F.dim[1] * F.dim[2] * std::max(F.n_lab, 1);
-      max_cells = std::max(max_cells, (uint64_t)F.dim[0] * F.dim[1] * F.dim[2] * std::max(F.n_lab, 1));
-    }
-    p->stacked = stacked;
-    RK_REQUIRE(rows_total < (1LL << 31), RKHSBA_ENOMEM, "cell-row table too large");
-    p->bin_bits = 3 * bin_axis_bits;
+    // the frames' sort segments
     RK_HIP(d_bframes_.reserve(K));
-    RK_HIP(hipMemcpyAsync(d_bframes_.p, fr.data(), sizeof(FrameInfo) * K, hipMemcpyHostToDevice, bst));
-
-    // resident ranges
-    p->pbase = points_.alloc(N, bst);
-    p->n_rows = std::max<int64_t>(rows_total, 1);
-    p->rbase = rows_.alloc(p->n_rows, bst);
-    float4* d_pts = static_cast<float4*>(points_.ptr(0)) + p->pbase;
-    int32_t* d_perm = static_cast<int32_t*>(points_.ptr(1)) + p->pbase;
-    uint32_t* d_keys = static_cast<uint32_t*>(points_.ptr(2)) + p->pbase;
-    void* d_feat = static_cast<uint8_t*>(points_.ptr(3)) + p->pbase * feat_row_bytes();
-    int4* d_rows = static_cast<int4*>(rows_.ptr(0)) + p->rbase;
-
-    // keys, segmented sort by frame, gather
     RK_HIP(k1_.reserve(N));
     RK_HIP(v1_.reserve(N));
     RK_HIP(k2_.reserve(N));
@@ -492,30 +427,140 @@ int Engine::add_problem(const ProbParams& par, int K, const int64_t* n_points, c
     RK_HIP(d_tiles_.reserve(tiles.size()));
     RK_HIP(d_segs_.reserve(K));
     RK_HIP(hist_scratch_.reserve(tiles.size() * 256));
+    RK_HIP(d_totals_.reserve(2));
     if (!tiles.empty())
       RK_HIP(hipMemcpyAsync(d_tiles_.p, tiles.data(), sizeof(SortTile) * tiles.size(), hipMemcpyHostToDevice, bst));
     RK_HIP(hipMemcpyAsync(d_segs_.p, segs.data(), sizeof(SortSeg) * K, hipMemcpyHostToDevice, bst));
-    int key_bits = 1;
-    while (key_bits < 32 && (1ull << key_bits) < max_cells) ++key_bits;
-    const bool in_tmp = sort_ends_in_tmp(key_bits);
-    uint32_t* sk = in_tmp ? k2_.p : k1_.p;
-    uint32_t* sv = in_tmp ? v2_.p : v1_.p;
-    RK_HIP(launch_cell_sort(cell_.p, d_bframes_.p, d_feat_ptrs_.p, d_tiles_.p, d_segs_.p, plan, key_bits, k1_.p,
-                            v1_.p, hist_scratch_.p, sk, sv, bst));
-    RK_HIP(launch_radix_sort(k1_.p, v1_.p, k2_.p, v2_.p, hist_scratch_.p, d_tiles_.p, d_segs_.p, plan, key_bits, true,
-                             true, bst));
-    RK_HIP(launch_gather(d_xyz_ptrs_.p, d_feat_ptrs_.p, kind, D, std::max(Dp, 1),
-                         d_bframes_.p, d_in_off_.p, K, N, sv, d_pts, d_feat, d_perm, minmax_.p + 6 * K + 1, bst));
-    RK_HIP(hipMemcpyAsync(d_keys, sk, sizeof(uint32_t) * N, hipMemcpyDeviceToDevice, bst));
-    RK_HIP(launch_feature_min(static_cast<const float*>(d_feat), N, n_dmin,
-                              reinterpret_cast<uint32_t*>(minmax_.p + 6 * K + 3), bst));
 
-    // cell-row tables
-    RK_HIP(row_sizes_.reserve(rows_total));
-    RK_HIP(scan_tmp_.reserve(rows_total / kScanTileElems + 2));
-    RK_HIP(d_total_.reserve(1));
-    RK_HIP(launch_rows(d_keys, d_bframes_.p, d_in_off_.p, K, N, d_rows, rows_total, row_sizes_.p, scan_tmp_.p,
-                       d_total_.p, bst));
+    std::vector<FrameInfo> fr(K);
+    const uint32_t *sk = nullptr, *sv = nullptr;  // sorted keys and point indices
+    uint64_t totals[2];                           // x-table entries, occupied cells
+    bool stacked = false;
+    for (;;) {
+      compute_constants(p);
+      const KConst kc0 = p->kc;
+      // grids (frame-local offsets for the build)
+      int64_t rows_total = 0;
+      uint64_t max_cells = 1;
+      int bin_axis_bits = 1;
+      std::vector<int> frame_bits(K);  // per-axis bits of a frame's cell coordinates (negative: coarsened)
+      for (int f = 0; f < K; ++f) {
+        FrameInfo& F = fr[f];
+        F.pt_off = off[f];
+        F.n = (int32_t)n_points[f];
+        uint64_t cells = 1;
+        for (int a = 0; a < 3; ++a) {
+          const double lo = (double)float_of_ordered((uint32_t)mm[6 * f + a]) * kc0.inv_cell;
+          const double hi = (double)float_of_ordered((uint32_t)mm[6 * f + 3 + a]) * kc0.inv_cell;
+          RK_REQUIRE(std::fabs(lo) < 1.0e9 && std::fabs(hi) < 1.0e9, RKHSBA_EINVAL,
+                     "non-finite or out-of-range point coordinate");
+          F.org[a] = (int32_t)std::floor(lo);
+          const int64_t d = (int64_t)std::floor(hi) - F.org[a] + 1;
+          RK_REQUIRE(d >= 1 && d < (1 << 24), RKHSBA_ENOMEM, "frame extent too large for its cell grid");
+          F.dim[a] = (int32_t)d;
+          cells *= (uint64_t)d;
+        }
+        RK_REQUIRE(cells < 0xffffffffull, RKHSBA_ENOMEM,
+                   "frame spans more than 2^32 cells; raise ell or lower cell_subdiv");
+        max_cells = std::max(max_cells, cells);
+        F.xt_off = 0;
+        F.n_lab = 0;
+        F.key_sub = 0;
+        int ext_max = 0;
+        for (int a = 0; a < 3; ++a) ext_max = std::max(ext_max, F.dim[a] + 2 * kc0.reach_cells);
+        int shift = 0;
+        while (((ext_max - 1) >> shift) >= 1023) ++shift;
+        F.mort_shift = shift;
+        const int maxc = (ext_max - 1) >> shift;
+        int bits = 1;
+        while ((1 << bits) < maxc + 2) ++bits;
+        frame_bits[f] = shift == 0 ? bits : -bits;
+        bin_axis_bits = std::max(bin_axis_bits, bits);
+      }
+      // The binning keys order the source points of a cell by sub-cell (Morton order at a finer grid), as
+      // far as that fits the radix passes the cells already take: the passes' groups of consecutive points
+      // then span smaller boxes, whose walks hold fewer candidates that pair with none of the group.
+      {
+        const int axis_room = (8 * ((3 * bin_axis_bits + 7) / 8)) / 3;  // axis bits the same digit passes sort
+        for (int f = 0; f < K; ++f) {
+          if (frame_bits[f] < 0) continue;  // coarsened grid (mort_shift > 0)
+          fr[f].key_sub = std::max(0, std::min({3, axis_room - frame_bits[f], 10 - frame_bits[f]}));
+          bin_axis_bits = std::max(bin_axis_bits, frame_bits[f] + fr[f].key_sub);
+        }
+      }
+      // Class ids: every frame stacks one layer of its z extent per class id (0 .. its largest id) along z,
+      // so that points of one id are contiguous and the sweeps walk only the candidates that can pair.  Kept
+      // only while the keys fit 32 bits and the row table stays within 16 rows per point (+ 2^20).
+      stacked = class_ids;
+      {
+        int64_t rows_stacked = 0;
+        for (int f = 0; f < K && stacked; ++f) {
+          const int64_t n_lab = (int64_t)mm[lab0 + f] + 1;
+          const uint64_t cells = (uint64_t)fr[f].dim[0] * fr[f].dim[1] * fr[f].dim[2];
+          stacked = n_lab >= 1 && cells * (uint64_t)n_lab < 0xffffffffull;
+          rows_stacked += (int64_t)fr[f].dim[1] * fr[f].dim[2] * n_lab;
+        }
+        stacked = stacked && rows_stacked < (1LL << 31) && rows_stacked <= 16 * N + (1LL << 20);
+      }
+      for (int f = 0; f < K; ++f) {
+        FrameInfo& F = fr[f];
+        F.n_lab = stacked ? mm[lab0 + f] + 1 : 0;
+        F.row_off = rows_total;
+        rows_total += (int64_t)F.dim[1] * F.dim[2] * std::max(F.n_lab, 1);
+        max_cells = std::max(max_cells, (uint64_t)F.dim[0] * F.dim[1] * F.dim[2] * std::max(F.n_lab, 1));
+      }
+      p->stacked = stacked;
+      RK_REQUIRE(rows_total < (1LL << 31), RKHSBA_ENOMEM, "cell-row table too large");
+      p->bin_bits = 3 * bin_axis_bits;
+      RK_HIP(hipMemcpyAsync(d_bframes_.p, fr.data(), sizeof(FrameInfo) * K, hipMemcpyHostToDevice, bst));
+
+      // keys, segmented sort by frame, cell-row tables
+      int key_bits = 1;
+      while (key_bits < 32 && (1ull << key_bits) < max_cells) ++key_bits;
+      const bool in_tmp = sort_ends_in_tmp(key_bits);
+      sk = in_tmp ? k2_.p : k1_.p;
+      sv = in_tmp ? v2_.p : v1_.p;
+      RK_HIP(launch_cell_sort(d_xyz_ptrs_.p, kc0.inv_cell, d_bframes_.p, d_feat_ptrs_.p, d_tiles_.p, d_segs_.p, plan,
+                              key_bits, k1_.p, v1_.p, hist_scratch_.p, in_tmp ? k2_.p : k1_.p, in_tmp ? v2_.p : v1_.p,
+                              bst));
+      RK_HIP(launch_radix_sort(k1_.p, v1_.p, k2_.p, v2_.p, hist_scratch_.p, d_tiles_.p, d_segs_.p, plan, key_bits, true,
+                               true, bst));
+      p->n_rows = std::max<int64_t>(rows_total, 1);
+      p->rbase = rows_.alloc(p->n_rows, bst);
+      RK_HIP(row_sizes_.reserve(rows_total));
+      RK_HIP(scan_tmp_.reserve(rows_total / kScanTileElems + 2));
+      RK_HIP(launch_rows(sk, d_bframes_.p, d_in_off_.p, K, N, static_cast<int4*>(rows_.ptr(0)) + p->rbase, rows_total,
+                         row_sizes_.p, scan_tmp_.p, d_totals_.p, bst));
+      RK_HIP(hipMemcpyAsync(totals, d_totals_.p, sizeof(totals), hipMemcpyDeviceToHost, bst));
+      RK_HIP(hipStreamSynchronize(bst));
+      p->occupancy = (double)N / std::max<uint64_t>(totals[1], 1u);
+      if (p->par.cell_subdiv == 1) p->occupancy_r = p->occupancy;
+      if (!choose) break;
+      choose = false;
+      const std::pair<int, int> cfg = choose_config(p->occupancy);
+      p->par.cell_subdiv = par_in.cell_subdiv != 0 ? par_in.cell_subdiv : cfg.first;
+      p->par.pass_points = par_in.pass_points != 0 ? par_in.pass_points : cfg.second;
+      if (p->par.cell_subdiv == 1) break;
+      rows_.free(p->rbase, p->n_rows);
+      p->rbase = -1;
+    }
+    const uint64_t xt_total = totals[0];
+    RK_REQUIRE(xt_total < (1ull << 31), RKHSBA_ENOMEM, "cell table too large");
+
+    // resident ranges, gather
+    p->pbase = points_.alloc(N, bst);
+    p->n_xt = std::max<int64_t>((int64_t)xt_total, 1);
+    p->xbase = xtab_.alloc(p->n_xt, bst);
+    float4* d_pts = static_cast<float4*>(points_.ptr(0)) + p->pbase;
+    int32_t* d_perm = static_cast<int32_t*>(points_.ptr(1)) + p->pbase;
+    uint32_t* d_keys = static_cast<uint32_t*>(points_.ptr(2)) + p->pbase;
+    void* d_feat = static_cast<uint8_t*>(points_.ptr(3)) + p->pbase * feat_row_bytes();
+    RK_HIP(launch_gather(d_xyz_ptrs_.p, d_feat_ptrs_.p, kind, D, std::max(Dp, 1), d_in_off_.p, K, N, sk, sv, d_pts,
+                         d_feat, d_perm, d_keys, minmax_.p + 6 * K + 1, bst));
+    RK_HIP(launch_feature_min(static_cast<const float*>(d_feat), N, n_dmin,
+                              reinterpret_cast<uint32_t*>(minmax_.p + 6 * K + 2), bst));
+    RK_HIP(launch_xtab(sk, d_bframes_.p, d_in_off_.p, K, N, static_cast<const int4*>(rows_.ptr(0)) + p->rbase,
+                       static_cast<uint32_t*>(xtab_.ptr(0)) + p->xbase, bst));
     // first point of every label layer (pass segments of the edges that start in the frame)
     p->lab_off.assign(K, -1);
     p->lab_start.clear();
@@ -529,34 +574,14 @@ int Engine::add_problem(const ProbParams& par, int K, const int64_t* n_points, c
       RK_HIP(d_lab_off_.reserve(K));
       RK_HIP(d_lab_start_.reserve(n_ls));
       RK_HIP(hipMemcpyAsync(d_lab_off_.p, p->lab_off.data(), sizeof(int64_t) * K, hipMemcpyHostToDevice, bst));
-      RK_HIP(launch_label_starts(d_keys, d_bframes_.p, d_lab_off_.p, K, d_lab_start_.p, bst));
+      RK_HIP(launch_label_starts(sk, d_bframes_.p, d_lab_off_.p, K, d_lab_start_.p, bst));
       RK_HIP(hipMemcpyAsync(p->lab_start.data(), d_lab_start_.p, sizeof(int32_t) * n_ls, hipMemcpyDeviceToHost, bst));
     }
-    uint64_t xt_total = 0;
     int32_t neg = 0;
-    RK_HIP(hipMemcpyAsync(&xt_total, d_total_.p, sizeof(uint64_t), hipMemcpyDeviceToHost, bst));
     RK_HIP(hipMemcpyAsync(&neg, minmax_.p + 6 * K + 1, sizeof(int32_t), hipMemcpyDeviceToHost, bst));
     std::vector<uint32_t> dmin(std::max(n_dmin, 1));
     if (n_dmin > 0)
-      RK_HIP(hipMemcpyAsync(dmin.data(), minmax_.p + 6 * K + 3, sizeof(uint32_t) * n_dmin, hipMemcpyDeviceToHost, bst));
-    RK_HIP(hipStreamSynchronize(bst));
-    p->negative_features = neg != 0;
-    p->c_positive = false;
-    if (!p->negative_features)
-      for (int d = 0; d < n_dmin; ++d) {
-        float v;
-        std::memcpy(&v, &dmin[d], sizeof(v));
-        p->c_positive = p->c_positive || v >= 1e-18f;
-      }
-    compute_constants(p);
-    RK_REQUIRE(xt_total < (1ull << 31), RKHSBA_ENOMEM, "cell table too large");
-    p->n_xt = std::max<int64_t>((int64_t)xt_total, 1);
-    p->xbase = xtab_.alloc(p->n_xt, bst);
-    RK_HIP(launch_xtab(d_keys, d_bframes_.p, d_in_off_.p, K, N, d_rows,
-                       static_cast<uint32_t*>(xtab_.ptr(0)) + p->xbase,
-                       reinterpret_cast<uint32_t*>(minmax_.p + 6 * K + 2), bst));
-    uint32_t n_cells = 0;
-    RK_HIP(hipMemcpyAsync(&n_cells, minmax_.p + 6 * K + 2, sizeof(uint32_t), hipMemcpyDeviceToHost, bst));
+      RK_HIP(hipMemcpyAsync(dmin.data(), minmax_.p + 6 * K + 2, sizeof(uint32_t) * n_dmin, hipMemcpyDeviceToHost, bst));
 
     // frame table entries with pool offsets
     p->slot0 = slots_.alloc(K, bst);
@@ -571,15 +596,22 @@ int Engine::add_problem(const ProbParams& par, int K, const int64_t* n_points, c
     prof_end(RKHSBA_PROF_BUILD, tb);
     RK_HIP(hipStreamSynchronize(bst));
     prof_collect();
+    p->negative_features = neg != 0;
+    p->c_positive = false;
+    if (!p->negative_features)
+      for (int d = 0; d < n_dmin; ++d) {
+        float v;
+        std::memcpy(&v, &dmin[d], sizeof(v));
+        p->c_positive = p->c_positive || v >= 1e-18f;
+      }
+    compute_constants(p);
     p->frames = std::move(fr);
-    p->occupancy = (double)N / std::max<uint32_t>(n_cells, 1u);
     p->resident_bytes = N * (int64_t)(28 + feat_row_bytes()) + p->n_rows * 16 + p->n_xt * 4 +
                         (int64_t)K * (int64_t)(sizeof(FrameInfo) + 96) + 8;
   } catch (...) {
     release();
     throw;
   }
-  if (par.cell_subdiv == 1) p->occupancy_r = p->occupancy;
   p->id = next_id_++;
   probs_[p->id] = std::move(P);
   return p->id;
@@ -615,32 +647,6 @@ std::pair<int, int> Engine::choose_config(double occ_r) const {
   if (occ_r < 12.0) return {2, 16};
   if (occ_r < 48.0) return {4, 16};
   return {8, 16};
-}
-
-int Engine::add_problem_auto(const ProbParams& par_in, int K, const int64_t* n_points, const float* const* xyz,
-                             int kind, int Din, const void* const* feats, bool is_device) {
-  ProbParams par = par_in;
-  if (par.top_k > 0) par.pass_points = 1;  // the top-k selection runs in the per-point walks
-  if (par.cell_subdiv != 0 && par.pass_points != 0)
-    return add_problem(par, K, n_points, xyz, kind, Din, feats, is_device);
-  ProbParams probe = par;
-  probe.cell_subdiv = 1;  // cells of one truncation radius: occupancy probe
-  if (probe.pass_points == 0) probe.pass_points = 16;
-  const int id = add_problem(probe, K, n_points, xyz, kind, Din, feats, is_device);
-  const double occ = problem(id)->occupancy;
-  const std::pair<int, int> cfg = choose_config(occ);
-  ProbParams fine = par;
-  if (fine.cell_subdiv == 0) fine.cell_subdiv = cfg.first;
-  if (fine.pass_points == 0) fine.pass_points = cfg.second;
-  if (fine.cell_subdiv == 1) {
-    Problem* p = problem(id);
-    p->par.pass_points = fine.pass_points;  // same grid; only the sweep choice changes
-    return id;
-  }
-  remove_problem(id);
-  const int id2 = add_problem(fine, K, n_points, xyz, kind, Din, feats, is_device);
-  problem(id2)->occupancy_r = occ;
-  return id2;
 }
 
 void Engine::remove_problem(int id) {

@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cstring>
 #include <string>
 
 namespace rkhsba {
@@ -190,33 +191,43 @@ constexpr int kScanTileElems = 2048;
 // Padded feature row length: 8, 16, 24, 32 or 64 (FP32), 32 or 64 (bfloat16, fp8: whole 32-wide MFMA slices).
 int dense_pad(int D, int feat_path);
 
-// d_label_max (class ids, else null): per frame, the largest class id (max-combined; the caller sets -1).
-hipError_t launch_cell_coords(const float* const* d_xyz_ptrs, const int64_t* d_in_off, int K, int64_t n_total,
-                              double inv_cell, const void* const* d_class_ptrs, int32_t* d_cell, int32_t* d_minmax,
-                              int32_t* d_label_max, hipStream_t st);
+// Smallest and largest coordinate of every frame, [6 f + 0..2] and [6 f + 3..5] of d_bounds (which the caller sets to
+// all ones and zero), as the floats' bits in unsigned order; *d_bad is set where a coordinate is not finite.  n_max:
+// points of the largest frame.  d_label_max (class ids, else null): per frame, the largest class id (max-combined;
+// the caller sets -1).
+hipError_t launch_frame_bounds(const float* const* d_xyz_ptrs, const int64_t* d_in_off, int K, int64_t n_max,
+                               const void* const* d_class_ptrs, uint32_t* d_bounds, int32_t* d_bad,
+                               int32_t* d_label_max, hipStream_t st);
+inline float float_of_ordered(uint32_t o) {
+  const uint32_t u = (o & 0x80000000u) ? o & 0x7fffffffu : ~o;
+  float v;
+  std::memcpy(&v, &u, sizeof(v));
+  return v;
+}
 // Cell keys (frames with n_lab > 0 take the class ids, d_class_ptrs, into kz') and their sort by frame, stable.
 // Frames of at most kBlockSortMax points end in (d_sorted_keys, d_sorted_vals) at once; the keys and values of the
 // others are left in (d_keys, d_vals), with their tiles' counts of digit 0, for launch_radix_sort.
-hipError_t launch_cell_sort(const int32_t* d_cell, const FrameInfo* d_frames, const void* const* d_class_ptrs,
-                            const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan, int bits,
-                            uint32_t* d_keys, uint32_t* d_vals, uint32_t* d_hist, uint32_t* d_sorted_keys,
-                            uint32_t* d_sorted_vals, hipStream_t st);
+hipError_t launch_cell_sort(const float* const* d_xyz_ptrs, double inv_cell, const FrameInfo* d_frames,
+                            const void* const* d_class_ptrs, const SortTile* d_tiles, const SortSeg* d_segs,
+                            const SortPlan& plan, int bits, uint32_t* d_keys, uint32_t* d_vals, uint32_t* d_hist,
+                            uint32_t* d_sorted_keys, uint32_t* d_sorted_vals, hipStream_t st);
 // For every label-stacked frame f (frame-local key order) and class id l in [0, n_lab]: the first point
 // of layer l (l = n_lab: the frame's count), at d_out[d_lab_off[f] + l].
 hipError_t launch_label_starts(const uint32_t* d_keys, const FrameInfo* d_frames, const int64_t* d_lab_off, int K,
                                int32_t* d_out, hipStream_t st);
 hipError_t launch_gather(const float* const* d_xyz_ptrs, const void* const* d_feat_ptrs, int feat_kind, int D, int Dp,
-                         const FrameInfo* d_frames, const int64_t* d_in_off, int K, int64_t n_total,
+                         const int64_t* d_in_off, int K, int64_t n_total, const uint32_t* d_sorted_keys,
                          const uint32_t* d_sorted_vals, float4* d_pts, void* d_feat, int32_t* d_perm,
-                         int32_t* d_neg_flag, hipStream_t st);
+                         uint32_t* d_keys, int32_t* d_neg_flag, hipStream_t st);
 // Per feature dimension d < Dp (<= 64), the smallest stored FP32 value over n rows, as its bit pattern (values
 // >= 0; negative values count as 0), min-combined into d_min[d], which the caller sets to +inf first.
 hipError_t launch_feature_min(const float* d_feat, int64_t n, int Dp, uint32_t* d_min, hipStream_t st);
+// Row tables (x extents and x-table offsets) of sorted frames; d_totals[0] = x-table entries, [1] = occupied cells.
 hipError_t launch_rows(const uint32_t* d_keys, const FrameInfo* d_frames, const int64_t* d_in_off, int K,
                        int64_t n_total, int4* d_rows, int64_t n_rows, uint32_t* d_sizes, uint32_t* d_scan_tmp,
-                       uint64_t* d_total, hipStream_t st);
+                       uint64_t* d_totals, hipStream_t st);
 hipError_t launch_xtab(const uint32_t* d_keys, const FrameInfo* d_frames, const int64_t* d_in_off, int K,
-                       int64_t n_total, const int4* d_rows, uint32_t* d_xtab, uint32_t* d_n_cells, hipStream_t st);
+                       int64_t n_total, const int4* d_rows, uint32_t* d_xtab, hipStream_t st);
 
 // Mean of n points' xyz in FP64 (one workgroup, fixed summation order) -> out[3].
 hipError_t launch_frame_centroid(const float4* d_pts, int n, double* d_out, hipStream_t st);
