@@ -328,19 +328,16 @@ int rkhsba_eval_loss(rkhsba_ctx* c, const double* poses, int E, const int32_t* e
     Engine& g = *c->eng;
     g.prepare(c->lay_eval, {SetItem{p, edges, E, -1, 0}});
     g.upload_poses(p, poses);
-    g.reset_state(p);
     g.evaluate(c->lay_eval, MODE_LOSS);
-    std::vector<double> eo((size_t)E * kEdgeVals);
-    RK_HIP(hipMemcpyAsync(eo.data(), g.edge_out(), sizeof(double) * eo.size(), hipMemcpyDeviceToHost, c->stream));
-    RK_HIP(hipStreamSynchronize(c->stream));
+    std::vector<double> fe(E), pe(E);
+    g.read_loss(E, fe.data(), pe.data());
     g.prof_collect();
     const double s2 = c->opt.sigma * c->opt.sigma;
     double F = 0.0, np = 0.0;
     for (int e = 0; e < E; ++e) {
-      const double fe = s2 * eo[(size_t)e * kEdgeVals];
-      if (loss_per_edge) loss_per_edge[e] = fe;
-      F += eo[(size_t)e * kEdgeVals];
-      np += eo[(size_t)e * kEdgeVals + 91];
+      if (loss_per_edge) loss_per_edge[e] = s2 * fe[e];
+      F += fe[e];
+      np += pe[e];
     }
     if (loss_total) *loss_total = s2 * F;
     if (n_pairs) *n_pairs = (int64_t)np;
@@ -392,14 +389,13 @@ int rkhsba_accumulate_normal_eqs(rkhsba_ctx* c, const double* poses, int E, cons
     Engine& g = *c->eng;
     g.prepare(c->lay_eval, {SetItem{p, edges, E, -1, 0}});
     g.upload_poses(p, poses);
-    g.reset_state(p);
     const int n = 6 * p->K;
     g.evaluate(c->lay_eval, MODE_NORMAL, false, STEP_SYSTEM);
     const SolveArgs sa = g.solve_args(c->lay_eval);
     if (H) RK_HIP(hipMemcpyAsync(H, sa.H, sizeof(double) * n * n, hipMemcpyDeviceToHost, c->stream));
     if (b) RK_HIP(hipMemcpyAsync(b, sa.b, sizeof(double) * n, hipMemcpyDeviceToHost, c->stream));
     double F = 0.0, np = 0.0;
-    g.read_history(p, 1, &F, &np);
+    g.results(p, 1, nullptr, &F, &np);
     g.prof_collect();
     if (loss_total) *loss_total = F;
     if (n_pairs) *n_pairs = (int64_t)np;
@@ -416,13 +412,10 @@ int rkhsba_gn_step(rkhsba_ctx* c, double* poses, int E, const int32_t* edges, in
     RK_REQUIRE(c->opt.fixed_frame < p->K, RKHSBA_EINVAL, "fixed_frame out of range");
     g.prepare(c->lay_gn, {SetItem{p, edges, E, c->opt.fixed_frame, n_iter}});
     g.upload_poses(p, poses);
-    g.reset_state(p);
     g.iterate(c->lay_gn, n_iter);
     g.evaluate(c->lay_gn, MODE_LOSS, n_iter > 0, STEP_LOSS);  // the binning of this call's first iteration
     std::vector<double> lh(n_iter + 1), ph(n_iter + 1);
-    g.download_poses(p, poses);
-    g.read_history(p, n_iter + 1, lh.data(), ph.data());
-    const int32_t status = g.read_status(p);
+    const int32_t status = g.results(p, n_iter + 1, poses, lh.data(), ph.data());
     g.prof_collect();
     for (int i = 0; i <= n_iter; ++i) {
       if (loss_per_iter) loss_per_iter[i] = lh[i];
@@ -454,20 +447,20 @@ static void distance_terms(rkhsba_ctx* c, Problem* p, int E, const int32_t* edge
   it.allow_self = true;
   eng.prepare(c->lay_ell, {it});
   eng.evaluate(c->lay_ell, MODE_NORMAL);
-  std::vector<double> eo((size_t)Et * kEdgeVals);
-  RK_HIP(hipMemcpyAsync(eo.data(), eng.edge_out(), sizeof(double) * eo.size(), hipMemcpyDeviceToHost, c->stream));
-  RK_HIP(hipStreamSynchronize(c->stream));
+  std::vector<double> Fe(Et), We(Et);
+  eng.receive({{Fe.data(), eng.edge_out(), sizeof(double), (size_t)Et, sizeof(double) * kEdgeVals},
+               {We.data(), eng.edge_out() + 92, sizeof(double), (size_t)Et, sizeof(double) * kEdgeVals}}, c->stream);
   eng.prof_collect();
   std::vector<double> S(p->K, 0.0), SW(p->K, 0.0);
   for (size_t k = 0; k < frames.size(); ++k) {
-    S[frames[k]] = eo[(size_t)(E + k) * kEdgeVals];
-    SW[frames[k]] = eo[(size_t)(E + k) * kEdgeVals + 92];
+    S[frames[k]] = Fe[E + k];
+    SW[frames[k]] = We[E + k];
   }
   double dd = 0.0, gw = 0.0;
   for (int e = 0; e < E; ++e) {
     const int m = edges[2 * e], n = edges[2 * e + 1];
-    dd += S[m] + S[n] - 2.0 * eo[(size_t)e * kEdgeVals];
-    gw += SW[m] + SW[n] - 2.0 * eo[(size_t)e * kEdgeVals + 92];
+    dd += S[m] + S[n] - 2.0 * Fe[e];
+    gw += SW[m] + SW[n] - 2.0 * We[e];
   }
   const double s2 = p->par.sigma * p->par.sigma, ell = p->par.ell;
   *d = s2 * dd;
@@ -480,14 +473,13 @@ static double edge_value_and_b(rkhsba_ctx* c, Problem* p, const double* poses, i
   const int32_t edge[2] = {m, n};
   eng.prepare(c->lay_eval, {SetItem{p, edge, 1, -1, 0}});
   eng.upload_poses(p, poses);
-  std::vector<double> eo(kEdgeVals);
   if (bn) {
     eng.evaluate(c->lay_eval, MODE_NORMAL);
   } else {
     eng.evaluate(c->lay_eval, MODE_LOSS);
   }
-  RK_HIP(hipMemcpyAsync(eo.data(), eng.edge_out(), sizeof(double) * kEdgeVals, hipMemcpyDeviceToHost, c->stream));
-  RK_HIP(hipStreamSynchronize(c->stream));
+  double eo[13];
+  eng.read_edges(1, 0, 13, eo);
   eng.prof_collect();
   if (bn)
     for (int r = 0; r < 6; ++r) bn[r] = eo[7 + r];  // b_n of the edge: the 6-vector of its second frame
@@ -541,12 +533,10 @@ int rkhsba_cosine(rkhsba_ctx* c, const double* poses, int m, int n, double* cos_
     it.allow_self = true;
     c->eng->prepare(c->lay_ell, {it});
     c->eng->evaluate(c->lay_ell, MODE_LOSS);
-    std::vector<double> eo((size_t)3 * kEdgeVals);
-    RK_HIP(hipMemcpyAsync(eo.data(), c->eng->edge_out(), sizeof(double) * eo.size(), hipMemcpyDeviceToHost,
-                          c->stream));
-    RK_HIP(hipStreamSynchronize(c->stream));
+    double eo[3];
+    c->eng->read_edges(3, 0, 1, eo);
     c->eng->prof_collect();
-    const double Fmn = eo[0], Sm = eo[kEdgeVals], Sn = eo[2 * kEdgeVals];
+    const double Fmn = eo[0], Sm = eo[1], Sn = eo[2];
     if (cos_out) *cos_out = (Sm > 0.0 && Sn > 0.0) ? Fmn / std::sqrt(Sm * Sn) : 0.0;
     return RKHSBA_OK;
   });
@@ -650,12 +640,9 @@ int rkhsba_gn_lengthscale(rkhsba_ctx* c, double* poses, int E, const int32_t* ed
       g.set_ell(p, ell);
       g.prepare(c->lay_gn, {SetItem{p, edges, E, c->opt.fixed_frame, ni}});
       g.upload_poses(p, poses);
-      g.reset_state(p);
       g.iterate(c->lay_gn, ni);
       g.evaluate(c->lay_gn, MODE_LOSS, false, STEP_LOSS);
-      g.download_poses(p, poses);
-      g.read_history(p, ni + 1, lh.data(), nullptr);
-      status = g.read_status(p);
+      status = g.results(p, ni + 1, poses, lh.data(), nullptr);
       double d = 0.0, gr = 0.0;
       distance_terms(c, p, E, edges, &d, &gr);
       if (trace) {
@@ -742,17 +729,16 @@ int rkhsba_rotation_search(rkhsba_ctx* c, const double* poses, int m, int n, int
     }
     g.prepare(c->lay_rot, {SetItem{p, edges.data(), nr, -1, 0}});
     g.evaluate(c->lay_rot, MODE_LOSS);
-    std::vector<double> eo((size_t)nr * kEdgeVals);
-    RK_HIP(hipMemcpyAsync(eo.data(), g.edge_out(), sizeof(double) * eo.size(), hipMemcpyDeviceToHost, c->stream));
-    RK_HIP(hipStreamSynchronize(c->stream));
+    std::vector<double> eo(nr);
+    g.read_edges(nr, 0, 1, eo.data());
     g.prof_collect();
     g.clear_aliases(p);
     const double s2 = c->opt.sigma * c->opt.sigma;
     int kb = 0;
     for (int k = 0; k < nr; ++k) {
-      const double f = s2 * eo[(size_t)k * kEdgeVals];
+      const double f = s2 * eo[k];
       if (scores) scores[k] = f;
-      if (f > s2 * eo[(size_t)kb * kEdgeVals]) kb = k;
+      if (f > s2 * eo[kb]) kb = k;
     }
     if (best) *best = kb;
     if (best_pose) std::copy(&cand[(size_t)12 * kb], &cand[(size_t)12 * kb] + 12, best_pose);

@@ -230,6 +230,7 @@ struct SetLayout {
   bool small = false;               // every problem's step fits one workgroup (small_step)
   bool clamp = false;
   bool c_positive = false;          // every problem's inner products are > 0 (pair counts need no c != 0 test)
+  DBuf<uint8_t> d_tables;           // the host tables, which the views below are pieces of
   DBuf<EdgeInfo> d_edges;
   DBuf<int32_t> d_fin_off;
   DBuf<SortTile> d_etiles;
@@ -307,7 +308,12 @@ class Engine {
   // The resident (pool) part of estimate_bytes; a built problem's resident_bytes replaces it.
   static int64_t estimate_resident_bytes(int K, const int64_t* n_points, int64_t row_bytes);
 
-  void upload_poses(Problem* p, const double* poses);   // host K*12
+  // Small transfers.  Host to device, ordered on `s`; the host memory is free again on return.
+  void send(const std::vector<Upload>& up, hipStream_t s);
+  // Device to host, after the work queued on `s` (the engine's stream or its build stream); waits for it.
+  void receive(const std::vector<Download>& dn, hipStream_t s);
+  // The poses (host K*12), and with them iteration 0 and status 0.
+  void upload_poses(Problem* p, const double* poses);
   // count alias slots of `frame` with the given host poses (count*12); replaces earlier aliases
   void set_aliases(Problem* p, int frame, int count, const double* poses);
   void clear_aliases(Problem* p);
@@ -316,9 +322,7 @@ class Engine {
   void set_ell(Problem* p, double ell);
   // FP64 centroid of a frame's local coordinates (fixed summation order)
   void frame_centroid(Problem* p, int frame, double c[3]);
-  void download_poses(Problem* p, double* poses);       // host K*12 (synchronises the stream)
   void ensure_history(Problem* p, int n_iter);
-  void reset_state(Problem* p);                          // iter = 0, status = 0 (stream-ordered copy)
 
   // Set layout for the items (cached in `lay`; rebuilt when the items change).
   void prepare(SetLayout& lay, const std::vector<SetItem>& items);
@@ -339,14 +343,17 @@ class Engine {
   SolveArgs solve_args(SetLayout& lay);
 
   // results
-  void read_history(Problem* p, int count, double* loss, double* pairs);  // synchronises
-  // Queues copies of the poses (K*12), `count` history entries and the (iter, status) pair to host
-  // memory (pinned, for the copies to be asynchronous) on the engine's stream; does not wait.
-  void copy_results_async(Problem* p, int count, double* poses, double* loss, double* pairs, int32_t* state);
+  // Queues a copy of the poses (K*12), `count` losses and pair counts and the (iter, status) pair, one behind
+  // another, to pinned host memory on the engine's stream; does not wait.
+  void copy_results_async(Problem* p, int count, void* pinned);
   // After an evaluation with source_counts on, of a set whose first edge has source frame m of p:
   // every source point's pair count, by its original index (frame m's point count; synchronises).
   void read_source_counts(Problem* p, int m, int64_t* counts);
-  int32_t read_status(Problem* p);                                         // synchronises
+  // poses (host K*12), loss and pairs (count entries each; all nullable) and the status (waits for the stream)
+  int32_t results(Problem* p, int count, double* poses, double* loss, double* pairs);
+  // values first .. first + count - 1 of the first E edges of the last evaluation (waits for the stream)
+  void read_edges(int E, int first, int count, double* out);
+  void read_loss(int E, double* F, double* pairs);  // their F and pair counts
   const double* edge_out() const { return sc_->edge_out.p; }
 
   // device views
@@ -407,6 +414,8 @@ class Engine {
   DBuf<uint64_t> d_totals_;
   DBuf<int64_t> d_lab_off_;
   DBuf<int32_t> d_lab_start_;
+  DBuf<double> centroid_;
+  uint8_t* pinned_ = nullptr;  // receive(): kGetBytes each for the engine's stream and the build stream
 
   template <typename T>
   void need(DBuf<T>& b, size_t count, const char* what);

@@ -161,9 +161,13 @@ SetLayout::~SetLayout() {
 
 // ---------------------------------------------------------------- Engine
 
-Engine::Engine(int dev, hipStream_t stream, int mp) : device(dev), st(stream), moment_path(mp) {}
+Engine::Engine(int dev, hipStream_t stream, int mp) : device(dev), st(stream), moment_path(mp) {
+  // results of the engine's stream, and of its build stream
+  RK_HIP(hipHostMalloc(reinterpret_cast<void**>(&pinned_), 2 * kGetBytes, hipHostMallocDefault));
+}
 
 Engine::~Engine() {
+  (void)hipHostFree(pinned_);
   for (auto& s : stages)
     for (auto& pr : s.pending) {
       (void)hipEventDestroy(pr.first);
@@ -215,6 +219,61 @@ void Engine::prof_collect() {
       event_pool_.push_back(pr.second);
     }
     s.pending.clear();
+  }
+}
+
+// Up to 4 launches of arguments (3.2 us each) where copies take 3.5 us a piece and host memory that has to outlive
+// them; past that a copy's bandwidth tells.
+void Engine::send(const std::vector<Upload>& up, hipStream_t s) {
+  size_t total = 0;
+  for (const Upload& u : up) total += u.bytes;
+  if (total > 4 * kPutBytes) {
+    for (const Upload& u : up)
+      if (u.bytes) RK_HIP(hipMemcpyAsync(u.dst, u.src, u.bytes, hipMemcpyHostToDevice, s));
+    RK_HIP(hipStreamSynchronize(s));
+    return;
+  }
+  std::vector<Upload> run;  // pieces of one launch
+  size_t used = 0;
+  auto flush = [&]() {
+    RK_HIP(launch_put(run.data(), (int)run.size(), s));
+    run.clear();
+    used = 0;
+  };
+  for (const Upload& u : up)
+    for (size_t done = 0; done < u.bytes;) {
+      if (used == kPutBytes || (int)run.size() == kMaxPieces) flush();
+      const size_t part = std::min(u.bytes - done, kPutBytes - used);
+      run.push_back({static_cast<uint8_t*>(u.dst) + done, static_cast<const uint8_t*>(u.src) + done, part});
+      done += part;
+      used += part;
+    }
+  if (!run.empty()) flush();
+}
+
+void Engine::receive(const std::vector<Download>& dn, hipStream_t s) {
+  std::vector<Download> in;
+  size_t total = 0;
+  for (const Download& d : dn) {
+    if (!d.dst || d.item * d.count == 0) continue;
+    in.push_back(d);
+    total += d.item * d.count;
+  }
+  if (in.empty() || total > kGetBytes || (int)in.size() > kMaxPieces) {
+    for (const Download& d : in) {
+      if (d.count == 1) RK_HIP(hipMemcpyAsync(d.dst, d.src, d.item, hipMemcpyDeviceToHost, s));
+      else
+        RK_HIP(hipMemcpy2DAsync(d.dst, d.item, d.src, d.stride, d.item, d.count, hipMemcpyDeviceToHost, s));
+    }
+    RK_HIP(hipStreamSynchronize(s));
+    return;
+  }
+  uint8_t* out = pinned_ + (s == st ? 0 : kGetBytes);
+  RK_HIP(launch_get(in.data(), (int)in.size(), out, s));
+  RK_HIP(hipStreamSynchronize(s));
+  for (const Download& d : in) {
+    std::memcpy(d.dst, out, d.item * d.count);
+    out += d.item * d.count;
   }
 }
 
@@ -277,6 +336,23 @@ void Engine::compute_constants(Problem* p) {
   k.spread_limit = (float)(kSpreadFactor * rc);
   k.r_c = (float)rc;
   p->kc = k;
+}
+
+// Whether no value is an infinity or NaN: those have all exponent bits set, so adding 2^23 to the bits below the sign
+// carries into the sign bit.  (Blocks without an early exit, which the compiler vectorises.)
+static bool all_finite(const float* v, int64_t n) {
+  constexpr int64_t kBlock = 16384;
+  for (int64_t b = 0; b < n; b += kBlock) {
+    const int64_t e = std::min(n, b + kBlock);
+    uint32_t acc = 0;
+    for (int64_t i = b; i < e; ++i) {
+      uint32_t u;
+      std::memcpy(&u, v + i, sizeof(u));
+      acc |= (u & 0x7fffffffu) + 0x00800000u;
+    }
+    if (acc & 0x80000000u) return false;
+  }
+  return true;
 }
 
 int Engine::add_problem(const ProbParams& par, int K, const int64_t* n_points, const float* const* xyz, int kind,
@@ -365,14 +441,11 @@ int Engine::build(ProbParams par_in, int K, const int64_t* n_points, const float
       }
     } else {
       for (int f = 0; f < K; ++f)
-        for (int64_t i = 0; i < 3 * n_points[f]; ++i)
-          RK_REQUIRE(std::isfinite(xyz[f][i]), RKHSBA_EINVAL, "non-finite point coordinate");
+        RK_REQUIRE(all_finite(xyz[f], 3 * n_points[f]), RKHSBA_EINVAL, "non-finite point coordinate");
       if (kind != RKHSBA_FEAT_CLASS_ID)
-        for (int f = 0; f < K; ++f) {
-          const float* v = static_cast<const float*>(feats[f]);
-          for (int64_t i = 0; i < (int64_t)Din * n_points[f]; ++i)
-            RK_REQUIRE(std::isfinite(v[i]), RKHSBA_EINVAL, "non-finite feature value");
-        }
+        for (int f = 0; f < K; ++f)
+          RK_REQUIRE(all_finite(static_cast<const float*>(feats[f]), (int64_t)Din * n_points[f]), RKHSBA_EINVAL,
+                     "non-finite feature value");
       RK_HIP(raw_xyz_.reserve((size_t)N * 3));
       RK_HIP(raw_feat_.reserve((size_t)N * fbytes));
       for (int f = 0; f < K; ++f) {
@@ -388,9 +461,6 @@ int Engine::build(ProbParams par_in, int K, const int64_t* n_points, const float
     RK_HIP(d_xyz_ptrs_.reserve(K));
     RK_HIP(d_feat_ptrs_.reserve(K));
     RK_HIP(d_in_off_.reserve(K + 1));
-    RK_HIP(hipMemcpyAsync(d_xyz_ptrs_.p, xp.data(), sizeof(void*) * K, hipMemcpyHostToDevice, bst));
-    RK_HIP(hipMemcpyAsync(d_feat_ptrs_.p, fp.data(), sizeof(void*) * K, hipMemcpyHostToDevice, bst));
-    RK_HIP(hipMemcpyAsync(d_in_off_.p, off.data(), sizeof(int64_t) * (K + 1), hipMemcpyHostToDevice, bst));
 
     // per-frame bounds (and largest class ids)
     const int n_dmin = kind == RKHSBA_FEAT_DENSE_F32 ? Dp : 0;  // per-dimension minima of FP32 features
@@ -406,12 +476,14 @@ int Engine::build(ProbParams par_in, int K, const int64_t* n_points, const float
     mm[6 * K + 1] = 0;  // negative feature flag
     for (int d = 0; d < n_dmin; ++d) mm[6 * K + 2 + d] = 0x7f800000;  // feature minima (+inf until the build)
     RK_HIP(minmax_.reserve(mm.size()));
-    RK_HIP(hipMemcpyAsync(minmax_.p, mm.data(), sizeof(int32_t) * mm.size(), hipMemcpyHostToDevice, bst));
+    send({{d_xyz_ptrs_.p, xp.data(), sizeof(void*) * K},
+          {d_feat_ptrs_.p, fp.data(), sizeof(void*) * K},
+          {d_in_off_.p, off.data(), sizeof(int64_t) * (K + 1)},
+          {minmax_.p, mm.data(), sizeof(int32_t) * mm.size()}}, bst);
     RK_HIP(launch_frame_bounds(d_xyz_ptrs_.p, d_in_off_.p, K, *std::max_element(n_points, n_points + K),
                                d_feat_ptrs_.p, reinterpret_cast<uint32_t*>(minmax_.p), minmax_.p + 6 * K,
                                class_ids ? minmax_.p + lab0 : nullptr, bst));
-    RK_HIP(hipMemcpyAsync(mm.data(), minmax_.p, sizeof(int32_t) * mm.size(), hipMemcpyDeviceToHost, bst));
-    RK_HIP(hipStreamSynchronize(bst));
+    receive({{mm.data(), minmax_.p, sizeof(int32_t) * mm.size()}}, bst);
     RK_REQUIRE(mm[6 * K] == 0, RKHSBA_EINVAL, "non-finite or out-of-range point coordinate");
 
     // the frames' sort segments
@@ -428,9 +500,8 @@ int Engine::build(ProbParams par_in, int K, const int64_t* n_points, const float
     RK_HIP(d_segs_.reserve(K));
     RK_HIP(hist_scratch_.reserve(tiles.size() * 256));
     RK_HIP(d_totals_.reserve(2));
-    if (!tiles.empty())
-      RK_HIP(hipMemcpyAsync(d_tiles_.p, tiles.data(), sizeof(SortTile) * tiles.size(), hipMemcpyHostToDevice, bst));
-    RK_HIP(hipMemcpyAsync(d_segs_.p, segs.data(), sizeof(SortSeg) * K, hipMemcpyHostToDevice, bst));
+    std::vector<Upload> tables{{d_tiles_.p, tiles.data(), sizeof(SortTile) * tiles.size()},
+                               {d_segs_.p, segs.data(), sizeof(SortSeg) * K}};
 
     std::vector<FrameInfo> fr(K);
     const uint32_t *sk = nullptr, *sv = nullptr;  // sorted keys and point indices
@@ -512,7 +583,9 @@ int Engine::build(ProbParams par_in, int K, const int64_t* n_points, const float
       p->stacked = stacked;
       RK_REQUIRE(rows_total < (1LL << 31), RKHSBA_ENOMEM, "cell-row table too large");
       p->bin_bits = 3 * bin_axis_bits;
-      RK_HIP(hipMemcpyAsync(d_bframes_.p, fr.data(), sizeof(FrameInfo) * K, hipMemcpyHostToDevice, bst));
+      tables.push_back({d_bframes_.p, fr.data(), sizeof(FrameInfo) * K});
+      send(tables, bst);
+      tables.clear();
 
       // keys, segmented sort by frame, cell-row tables
       int key_bits = 1;
@@ -531,8 +604,7 @@ int Engine::build(ProbParams par_in, int K, const int64_t* n_points, const float
       RK_HIP(scan_tmp_.reserve(rows_total / kScanTileElems + 2));
       RK_HIP(launch_rows(sk, d_bframes_.p, d_in_off_.p, K, N, static_cast<int4*>(rows_.ptr(0)) + p->rbase, rows_total,
                          row_sizes_.p, scan_tmp_.p, d_totals_.p, bst));
-      RK_HIP(hipMemcpyAsync(totals, d_totals_.p, sizeof(totals), hipMemcpyDeviceToHost, bst));
-      RK_HIP(hipStreamSynchronize(bst));
+      receive({{totals, d_totals_.p, sizeof(totals)}}, bst);
       p->occupancy = (double)N / std::max<uint64_t>(totals[1], 1u);
       if (p->par.cell_subdiv == 1) p->occupancy_r = p->occupancy;
       if (!choose) break;
@@ -573,28 +645,25 @@ int Engine::build(ProbParams par_in, int K, const int64_t* n_points, const float
       p->lab_start.resize(n_ls);
       RK_HIP(d_lab_off_.reserve(K));
       RK_HIP(d_lab_start_.reserve(n_ls));
-      RK_HIP(hipMemcpyAsync(d_lab_off_.p, p->lab_off.data(), sizeof(int64_t) * K, hipMemcpyHostToDevice, bst));
-      RK_HIP(launch_label_starts(sk, d_bframes_.p, d_lab_off_.p, K, d_lab_start_.p, bst));
-      RK_HIP(hipMemcpyAsync(p->lab_start.data(), d_lab_start_.p, sizeof(int32_t) * n_ls, hipMemcpyDeviceToHost, bst));
     }
-    int32_t neg = 0;
-    RK_HIP(hipMemcpyAsync(&neg, minmax_.p + 6 * K + 1, sizeof(int32_t), hipMemcpyDeviceToHost, bst));
-    std::vector<uint32_t> dmin(std::max(n_dmin, 1));
-    if (n_dmin > 0)
-      RK_HIP(hipMemcpyAsync(dmin.data(), minmax_.p + 6 * K + 2, sizeof(uint32_t) * n_dmin, hipMemcpyDeviceToHost, bst));
-
     // frame table entries with pool offsets
     p->slot0 = slots_.alloc(K, bst);
     p->sbase = state_.alloc(1, bst);
+    std::vector<FrameInfo> pooled = fr;
     for (int f = 0; f < K; ++f) {
-      fr[f].pt_off += p->pbase;
-      fr[f].row_off += p->rbase;
-      fr[f].xt_off = p->xbase;
+      pooled[f].pt_off += p->pbase;
+      pooled[f].row_off += p->rbase;
+      pooled[f].xt_off = p->xbase;
     }
-    RK_HIP(hipMemcpyAsync(static_cast<FrameInfo*>(slots_.ptr(0)) + p->slot0, fr.data(), sizeof(FrameInfo) * K,
-                          hipMemcpyHostToDevice, bst));
+    send({{static_cast<FrameInfo*>(slots_.ptr(0)) + p->slot0, pooled.data(), sizeof(FrameInfo) * K},
+          {d_lab_off_.p, p->lab_off.data(), stacked ? sizeof(int64_t) * K : 0}}, bst);
+    if (stacked) RK_HIP(launch_label_starts(sk, d_bframes_.p, d_lab_off_.p, K, d_lab_start_.p, bst));
     prof_end(RKHSBA_PROF_BUILD, tb);
-    RK_HIP(hipStreamSynchronize(bst));
+    int32_t neg = 0;
+    std::vector<uint32_t> dmin(std::max(n_dmin, 1));
+    receive({{&neg, minmax_.p + 6 * K + 1, sizeof(int32_t)},
+             {dmin.data(), minmax_.p + 6 * K + 2, sizeof(uint32_t) * n_dmin},
+             {p->lab_start.data(), d_lab_start_.p, sizeof(int32_t) * p->lab_start.size()}}, bst);
     prof_collect();
     p->negative_features = neg != 0;
     p->c_positive = false;
@@ -605,7 +674,7 @@ int Engine::build(ProbParams par_in, int K, const int64_t* n_points, const float
         p->c_positive = p->c_positive || v >= 1e-18f;
       }
     compute_constants(p);
-    p->frames = std::move(fr);
+    p->frames = std::move(pooled);
     p->resident_bytes = N * (int64_t)(28 + feat_row_bytes()) + p->n_rows * 16 + p->n_xt * 4 +
                         (int64_t)K * (int64_t)(sizeof(FrameInfo) + 96) + 8;
   } catch (...) {
@@ -666,7 +735,9 @@ void Engine::remove_problem(int id) {
 void Engine::upload_poses(Problem* p, const double* poses) {
   RK_REQUIRE(poses != nullptr, RKHSBA_EINVAL, "poses is NULL");
   for (int i = 0; i < 12 * p->K; ++i) RK_REQUIRE(std::isfinite(poses[i]), RKHSBA_EINVAL, "non-finite pose entry");
-  RK_HIP(hipMemcpyAsync(poses_ptr(p), poses, sizeof(double) * 12 * p->K, hipMemcpyHostToDevice, st));
+  static const int32_t zero[2] = {0, 0};
+  send({{poses_ptr(p), poses, sizeof(double) * 12 * p->K},
+        {static_cast<int32_t*>(state_.ptr(0)) + 2 * p->sbase, zero, sizeof(zero)}}, st);
 }
 
 void Engine::set_aliases(Problem* p, int frame, int count, const double* alias_poses) {
@@ -679,11 +750,8 @@ void Engine::set_aliases(Problem* p, int frame, int count, const double* alias_p
   }
   p->alias_of = frame;
   std::vector<FrameInfo> fr(count, p->frames[frame]);
-  RK_HIP(hipMemcpyAsync(static_cast<FrameInfo*>(slots_.ptr(0)) + p->alias_slot0, fr.data(), sizeof(FrameInfo) * count,
-                        hipMemcpyHostToDevice, st));
-  RK_HIP(hipMemcpyAsync(poses() + 12 * p->alias_slot0, alias_poses, sizeof(double) * 12 * count, hipMemcpyHostToDevice,
-                        st));
-  RK_HIP(hipStreamSynchronize(st));  // the host FrameInfo copies go out of scope
+  send({{static_cast<FrameInfo*>(slots_.ptr(0)) + p->alias_slot0, fr.data(), sizeof(FrameInfo) * count},
+        {poses() + 12 * p->alias_slot0, alias_poses, sizeof(double) * 12 * count}}, st);
 }
 
 void Engine::set_ell(Problem* p, double ell) {
@@ -712,17 +780,10 @@ void Engine::clear_aliases(Problem* p) {
 
 void Engine::frame_centroid(Problem* p, int frame, double c[3]) {
   RK_REQUIRE(frame >= 0 && frame < p->K, RKHSBA_EINVAL, "frame out of range");
-  DBuf<double> d;
-  RK_HIP(d.reserve(3));
+  RK_HIP(centroid_.reserve(3));
   const FrameInfo& F = p->frames[frame];
-  RK_HIP(launch_frame_centroid(pts() + F.pt_off, F.n, d.p, st));
-  RK_HIP(hipMemcpyAsync(c, d.p, sizeof(double) * 3, hipMemcpyDeviceToHost, st));
-  RK_HIP(hipStreamSynchronize(st));
-}
-
-void Engine::download_poses(Problem* p, double* poses) {
-  RK_HIP(hipMemcpyAsync(poses, poses_ptr(p), sizeof(double) * 12 * p->K, hipMemcpyDeviceToHost, st));
-  RK_HIP(hipStreamSynchronize(st));
+  RK_HIP(launch_frame_centroid(pts() + F.pt_off, F.n, centroid_.p, st));
+  receive({{c, centroid_.p, sizeof(double) * 3}}, st);
 }
 
 void Engine::ensure_history(Problem* p, int n_iter) {
@@ -734,21 +795,23 @@ void Engine::ensure_history(Problem* p, int n_iter) {
   p->n_hist = need;
 }
 
-void Engine::reset_state(Problem* p) {
-  static const int32_t zero[2] = {0, 0};
-  RK_HIP(hipMemcpyAsync(static_cast<int32_t*>(state_.ptr(0)) + 2 * p->sbase, zero, sizeof(zero),
-                        hipMemcpyHostToDevice, st));
+int32_t Engine::results(Problem* p, int count, double* poses, double* loss, double* pairs) {
+  RK_REQUIRE(p->hbase >= 0 && count <= p->n_hist, RKHSBA_ESTATE, "no history of that length");
+  int32_t s[2] = {0, 0};
+  receive({{poses, poses_ptr(p), sizeof(double) * 12 * p->K},
+           {loss, static_cast<double*>(hist_.ptr(0)) + p->hbase, sizeof(double) * count},
+           {pairs, static_cast<double*>(hist_.ptr(1)) + p->hbase, sizeof(double) * count},
+           {s, static_cast<int32_t*>(state_.ptr(0)) + 2 * p->sbase, sizeof(s)}}, st);
+  return s[1];
 }
 
-void Engine::read_history(Problem* p, int count, double* loss, double* pairs) {
-  RK_REQUIRE(p->hbase >= 0 && count <= p->n_hist, RKHSBA_ESTATE, "no history of that length");
-  if (loss)
-    RK_HIP(hipMemcpyAsync(loss, static_cast<double*>(hist_.ptr(0)) + p->hbase, sizeof(double) * count,
-                          hipMemcpyDeviceToHost, st));
-  if (pairs)
-    RK_HIP(hipMemcpyAsync(pairs, static_cast<double*>(hist_.ptr(1)) + p->hbase, sizeof(double) * count,
-                          hipMemcpyDeviceToHost, st));
-  RK_HIP(hipStreamSynchronize(st));
+void Engine::read_edges(int E, int first, int count, double* out) {
+  receive({{out, sc_->edge_out.p + first, sizeof(double) * count, (size_t)E, sizeof(double) * kEdgeVals}}, st);
+}
+
+void Engine::read_loss(int E, double* F, double* pairs) {
+  receive({{F, sc_->edge_out.p, sizeof(double), (size_t)E, sizeof(double) * kEdgeVals},
+           {pairs, sc_->edge_out.p + 91, sizeof(double), (size_t)E, sizeof(double) * kEdgeVals}}, st);
 }
 
 void Engine::read_source_counts(Problem* p, int m, int64_t* counts) {
@@ -767,23 +830,23 @@ void Engine::read_source_counts(Problem* p, int m, int64_t* counts) {
   }
 }
 
-void Engine::copy_results_async(Problem* p, int count, double* poses, double* loss, double* pairs, int32_t* state) {
+void Engine::copy_results_async(Problem* p, int count, void* pinned) {
   RK_REQUIRE(p->hbase >= 0 && count <= p->n_hist, RKHSBA_ESTATE, "no history of that length");
-  RK_HIP(hipMemcpyAsync(poses, poses_ptr(p), sizeof(double) * 12 * p->K, hipMemcpyDeviceToHost, st));
-  RK_HIP(hipMemcpyAsync(loss, static_cast<double*>(hist_.ptr(0)) + p->hbase, sizeof(double) * count,
-                        hipMemcpyDeviceToHost, st));
-  RK_HIP(hipMemcpyAsync(pairs, static_cast<double*>(hist_.ptr(1)) + p->hbase, sizeof(double) * count,
-                        hipMemcpyDeviceToHost, st));
-  RK_HIP(hipMemcpyAsync(state, static_cast<int32_t*>(state_.ptr(0)) + 2 * p->sbase, 2 * sizeof(int32_t),
-                        hipMemcpyDeviceToHost, st));
-}
-
-int32_t Engine::read_status(Problem* p) {
-  int32_t s[2] = {0, 0};
-  RK_HIP(hipMemcpyAsync(s, static_cast<int32_t*>(state_.ptr(0)) + 2 * p->sbase, sizeof(s), hipMemcpyDeviceToHost,
-                        st));
-  RK_HIP(hipStreamSynchronize(st));
-  return s[1];
+  uint8_t* out = static_cast<uint8_t*>(pinned);
+  const Download dn[] = {{nullptr, poses_ptr(p), sizeof(double) * 12 * p->K},
+                         {nullptr, static_cast<double*>(hist_.ptr(0)) + p->hbase, sizeof(double) * count},
+                         {nullptr, static_cast<double*>(hist_.ptr(1)) + p->hbase, sizeof(double) * count},
+                         {nullptr, static_cast<int32_t*>(state_.ptr(0)) + 2 * p->sbase, 2 * sizeof(int32_t)}};
+  size_t total = 0;
+  for (const Download& d : dn) total += d.item;
+  if (total <= kGetBytes) {
+    RK_HIP(launch_get(dn, 4, out, st));
+    return;
+  }
+  for (const Download& d : dn) {
+    RK_HIP(hipMemcpyAsync(out, d.src, d.item, hipMemcpyDeviceToHost, st));
+    out += d.item;
+  }
 }
 
 // ---------------------------------------------------------------- set layout
@@ -966,10 +1029,6 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
              RKHSBA_EINVAL, "edge list too large");
   if (blist.empty()) blist.push_back(0);
   if (vlist.empty()) vlist.push_back(0);
-  need(lay.d_edges, E_total, "edges");
-  need(lay.d_fin_off, E_total, "fin_off");
-  need(lay.d_etiles, tiles.size(), "etiles");
-  need(lay.d_esegs, std::max<size_t>(segs.size(), 1), "esegs");
   // the pass table: the groups one after another, each edge's passes contiguous (filled on the device)
   std::vector<SetLayout::Group> groups;
   int64_t gbase[6], n_pass_table = 0;
@@ -995,50 +1054,53 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
       run[gi] += info[e].n_pass;
     }
   }
-  need(lay.d_kcs, items.size(), "kcs");
+  // The host tables, one behind another (256-byte aligned) in one array, which goes to the device in one piece: as
+  // kernel arguments where it is small, else through the layout's pinned staging buffer, whose previous upload must
+  // have completed before it is rewritten.  The host need not wait for the stream here either way.
   need(lay.d_passes, (size_t)n_pass_table, "passes");
-  need(lay.d_sys, items.size(), "sys");
-  need(lay.d_blk_start, bstart_all.size(), "blk_start");
-  need(lay.d_blk_list, blist.size(), "blk_list");
-  need(lay.d_vec_start, vstart_all.size(), "vec_start");
-  need(lay.d_vec_list, vlist.size(), "vec_list");
-  // The host tables go to the device through the layout's pinned staging buffer, whose previous uploads
-  // must have completed before it is rewritten (the host then need not wait for the stream here).
-  size_t stage_bytes = 0;
-  auto stage_size = [&](size_t bytes) { stage_bytes += (bytes + 255) & ~(size_t)255; };
-  stage_size(sizeof(EdgeInfo) * E_total);
-  stage_size(sizeof(int32_t) * E_total);
-  stage_size(sizeof(SortTile) * tiles.size());
-  stage_size(sizeof(SortSeg) * segs.size());
-  stage_size(sizeof(KConst) * kcs.size());
-  stage_size(sizeof(ProbSys) * sys.size());
-  stage_size(sizeof(int32_t) * bstart_all.size());
-  stage_size(sizeof(int32_t) * blist.size());
-  stage_size(sizeof(int32_t) * vstart_all.size());
-  stage_size(sizeof(int32_t) * vlist.size());
-  uint8_t* stage = lay.stage_for(stage_bytes, arena_ != nullptr);
-  size_t stage_off = 0;
-  auto up = [&](void* dst, const void* src, size_t bytes) {
-    if (!bytes) return;
-    if (!stage) {
-      RK_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st));
-      return;
-    }
-    std::memcpy(stage + stage_off, src, bytes);
-    RK_HIP(hipMemcpyAsync(dst, stage + stage_off, bytes, hipMemcpyHostToDevice, st));
-    stage_off += (bytes + 255) & ~(size_t)255;
+  std::vector<uint8_t> blob;
+  std::vector<size_t> at;
+  auto table = [&](const void* src, size_t bytes) {
+    at.push_back((blob.size() + 255) & ~(size_t)255);
+    blob.resize(at.back() + std::max<size_t>(bytes, 8));
+    if (bytes) std::memcpy(blob.data() + at.back(), src, bytes);
   };
-  up(lay.d_edges.p, info.data(), sizeof(EdgeInfo) * E_total);
-  up(lay.d_fin_off.p, foff.data(), sizeof(int32_t) * E_total);
-  up(lay.d_etiles.p, tiles.data(), sizeof(SortTile) * tiles.size());
-  up(lay.d_esegs.p, segs.data(), sizeof(SortSeg) * segs.size());
-  up(lay.d_kcs.p, kcs.data(), sizeof(KConst) * kcs.size());
+  table(info.data(), sizeof(EdgeInfo) * E_total);
+  table(foff.data(), sizeof(int32_t) * E_total);
+  table(tiles.data(), sizeof(SortTile) * tiles.size());
+  table(segs.data(), sizeof(SortSeg) * segs.size());
+  table(kcs.data(), sizeof(KConst) * kcs.size());
+  table(sys.data(), sizeof(ProbSys) * sys.size());
+  table(bstart_all.data(), sizeof(int32_t) * bstart_all.size());
+  table(blist.data(), sizeof(int32_t) * blist.size());
+  table(vstart_all.data(), sizeof(int32_t) * vstart_all.size());
+  table(vlist.data(), sizeof(int32_t) * vlist.size());
+  blob.resize((blob.size() + 3) & ~(size_t)3);
+  need(lay.d_tables, blob.size(), "tables");
+  size_t view = 0;
+  auto attach = [&](auto& buf, size_t count) {
+    using T = std::remove_reference_t<decltype(*buf.p)>;
+    buf.attach(reinterpret_cast<T*>(lay.d_tables.p + at[view++]), count);
+  };
+  attach(lay.d_edges, E_total);
+  attach(lay.d_fin_off, E_total);
+  attach(lay.d_etiles, tiles.size());
+  attach(lay.d_esegs, segs.size());
+  attach(lay.d_kcs, kcs.size());
+  attach(lay.d_sys, sys.size());
+  attach(lay.d_blk_start, bstart_all.size());
+  attach(lay.d_blk_list, blist.size());
+  attach(lay.d_vec_start, vstart_all.size());
+  attach(lay.d_vec_list, vlist.size());
+  uint8_t* stage = blob.size() <= 2 * kPutBytes ? nullptr : lay.stage_for(blob.size(), arena_ != nullptr);
+  if (stage) {
+    std::memcpy(stage, blob.data(), blob.size());
+    RK_HIP(hipMemcpyAsync(lay.d_tables.p, stage, blob.size(), hipMemcpyHostToDevice, st));
+    RK_HIP(hipEventRecord(lay.stage_ev, st));  // the staging buffer is free again once this completes
+  } else {
+    send({{lay.d_tables.p, blob.data(), blob.size()}}, st);
+  }
   RK_HIP(launch_fill_passes(lay.d_edges.p, E_total, frames(), lay.d_esegs.p, lay.d_passes.p, st));
-  up(lay.d_sys.p, sys.data(), sizeof(ProbSys) * sys.size());
-  up(lay.d_blk_start.p, bstart_all.data(), sizeof(int32_t) * bstart_all.size());
-  up(lay.d_blk_list.p, blist.data(), sizeof(int32_t) * blist.size());
-  up(lay.d_vec_start.p, vstart_all.data(), sizeof(int32_t) * vstart_all.size());
-  up(lay.d_vec_list.p, vlist.data(), sizeof(int32_t) * vlist.size());
 
   // per-evaluation scratch
   const void* before[] = {sc_->xf.p, sc_->bk.p, sc_->bv.p, sc_->bk2.p, sc_->bv2.p, sc_->bhist.p, sc_->mom.p, sc_->cnt.p, sc_->partial.p, sc_->edge_out.p,
@@ -1070,12 +1132,6 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   if (!arena_)
     for (size_t i = 0; i < sizeof(before) / sizeof(before[0]); ++i)
       if (before[i] != after[i]) ++scratch_gen_;
-  if (stage) {
-    RK_HIP(hipEventRecord(lay.stage_ev, st));  // the staging buffer is free again once this completes
-  } else {
-    RK_HIP(hipStreamSynchronize(st));  // host tables above go out of scope
-  }
-
   lay.uses = 0;
   lay.binned = false;
   lay.ids = std::move(ids);

@@ -229,6 +229,26 @@ hipError_t launch_rows(const uint32_t* d_keys, const FrameInfo* d_frames, const 
 hipError_t launch_xtab(const uint32_t* d_keys, const FrameInfo* d_frames, const int64_t* d_in_off, int K,
                        int64_t n_total, const int4* d_rows, uint32_t* d_xtab, hipStream_t st);
 
+// Small transfers (transfer.hip): up to kMaxPieces pieces of whole 32-bit words in one launch.
+constexpr int kMaxPieces = 6;
+constexpr size_t kPutBytes = 3584;   // an upload's payload (a kernel's arguments are at most 4 KB)
+constexpr size_t kGetBytes = 16384;  // a download's pieces together
+struct Upload {
+  void* dst;        // device
+  const void* src;  // host, free again on return
+  size_t bytes;
+};
+struct Download {
+  void* dst;        // host
+  const void* src;  // device
+  size_t item;      // bytes of an item
+  size_t count = 1;
+  size_t stride = 0;  // bytes from one item to the next
+};
+bool put_fits(const Upload* up, int n);
+hipError_t launch_put(const Upload* up, int n, hipStream_t st);
+hipError_t launch_get(const Download* dn, int n, void* pinned, hipStream_t st);
+
 // Mean of n points' xyz in FP64 (one workgroup, fixed summation order) -> out[3].
 hipError_t launch_frame_centroid(const float4* d_pts, int n, double* d_out, hipStream_t st);
 

@@ -201,9 +201,7 @@ struct rkhsba_server {
     try {
       q->loss.assign(q->n_iter + 1, 0.0);
       q->pairs.assign(q->n_iter + 1, 0.0);
-      L.eng->download_poses(p, q->poses.data());
-      L.eng->read_history(p, q->n_iter + 1, q->loss.data(), q->pairs.data());
-      if (L.eng->read_status(p) != 0) {
+      if (L.eng->results(p, q->n_iter + 1, q->poses.data(), q->loss.data(), q->pairs.data()) != 0) {
         status = RKHSBA_ENOTPD;
         msg = "Cholesky pivot not positive in a Gauss-Newton step";
       }
@@ -248,11 +246,7 @@ struct rkhsba_server {
     r.q = q;
     if (!r.ev) RK_HIP(hipEventCreateWithFlags(&r.ev, hipEventDisableTiming));
     uint8_t* dst = L.pinned + (size_t)r.slot * kRetireSlotBytes;
-    double* poses = reinterpret_cast<double*>(dst);
-    double* loss = poses + 12 * q->K;
-    double* pairs = loss + (q->n_iter + 1);
-    L.eng->copy_results_async(L.eng->problem(q->prob), q->n_iter + 1, poses, loss, pairs,
-                              reinterpret_cast<int32_t*>(pairs + q->n_iter + 1));
+    L.eng->copy_results_async(L.eng->problem(q->prob), q->n_iter + 1, dst);
     RK_HIP(hipEventRecord(r.ev, L.stream));
     {
       std::lock_guard<std::mutex> lk(L.rmu);
@@ -444,7 +438,6 @@ struct rkhsba_server {
             q->est_bytes += d;
           }
           L.eng->upload_poses(p, q->poses.data());
-          L.eng->reset_state(p);
           q->work = request_work(*q, p);
           q->timed = reorder;
           q->t_admit = Clock::now();
@@ -461,7 +454,6 @@ struct rkhsba_server {
           pre->prob = build_problem(L, *pre);
           Problem* p = L.eng->problem(pre->prob);
           L.eng->upload_poses(p, pre->poses.data());
-          L.eng->reset_state(p);
           pre->work = request_work(*pre, p);
           const int64_t d = p->resident_bytes - Engine::estimate_resident_bytes(pre->K, pre->n_points.data(),
                                                                                 row_bytes);
