@@ -35,6 +35,12 @@ __device__ inline int clamp_floor(double v, int lo, int hi) {
   return (int)v;
 }
 
+// a b, rounded before anything is added to it.
+__device__ inline float rounded_product(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
 // Walks the target frame's cell rows that a ball of radius `reach` around the
 // box [lo, hi] can touch and calls fn(j0, j1) with each contiguous range of
 // target points (frame-local sorted indices).  Every target point whose
@@ -66,6 +72,114 @@ __device__ inline void for_each_range(const FrameInfo& T, const int4* __restrict
       if (xa > xb) continue;
       const uint32_t* xt = xtab + T.xt_off + (uint32_t)R.z;
       fn(xt[xa - R.x], xt[xb + 1 - R.x]);
+    }
+  }
+}
+
+// The candidates of one source point per lane, in the order of for_each_range over its own ball: body(j, z, original)
+// for each, `original` (its original index) only with PERM.  Nested loops over rows, cells and candidates hold a
+// wavefront for the longest lane of every row, and every row costs three dependent reads, one after another.  Here the
+// rows' ranges are collected first, four rows' reads in flight, into kLocalRanges slots of LDS per lane, and each lane
+// then runs through its own ranges in steps of four candidates whose points are read one step ahead.  Latency bound:
+// one edge of 5,000 points 13.7 us nested, 11.3 so; 62 edges of 3,000 points 41 and 20; 12 LiDAR edges of 20,000
+// points with the 8 best kept 904 and 173 (with the cheaper list of TopK).
+constexpr int kLocalRanges = 12;
+template <bool PERM, typename Body>
+__device__ inline void local_walk(const FrameInfo& T, const int4* __restrict__ rows, const uint32_t* __restrict__ xtab,
+                                  const KConst& kc, float3 q, bool valid, int64_t lrow,
+                                  const float4* __restrict__ pts, const int32_t* __restrict__ perm,
+                                  uint2* __restrict__ slots, Body&& body) {
+  constexpr int U = 4;
+  const double inv = kc.inv_cell, cell = kc.cell, reach = kc.reach;
+  const double qx = q.x, qy = q.y, qz = q.z;
+  const int z0 = max(clamp_floor((qz - reach) * inv - T.org[2], -1, T.dim[2]), 0);
+  const int z1 = min(clamp_floor((qz + reach) * inv - T.org[2], -1, T.dim[2]), T.dim[2] - 1);
+  const int y0 = max(clamp_floor((qy - reach) * inv - T.org[1], -1, T.dim[1]), 0);
+  const int y1 = min(clamp_floor((qy + reach) * inv - T.org[1], -1, T.dim[1]), T.dim[1] - 1);
+  const int ny = y1 - y0 + 1;
+  int left = valid && lrow >= 0 && ny > 0 && z1 >= z0 ? ny * (z1 - z0 + 1) : 0;  // rows still to be read
+  int ky = y0, kz = z0;
+  const int4* __restrict__ frame_rows = rows + T.row_off + lrow;
+  const uint32_t* __restrict__ frame_xt = xtab + T.xt_off;
+  const float4* __restrict__ tp = pts + T.pt_off;
+  const int32_t* __restrict__ to = perm + T.pt_off;
+  while (__ballot(left > 0)) {
+    int n = 0;
+    for (int got = 0; got < kLocalRanges && __ballot(left > 0); got += U) {
+      int4 R[U];
+      double h[U];
+      bool live[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const double cz = (double)(kz + T.org[2]) * cell, cy = (double)(ky + T.org[1]) * cell;
+        const double bz = fmax(0.0, fmax(cz - qz, qz - (cz + cell)));
+        const double by = fmax(0.0, fmax(cy - qy, qy - (cy + cell)));
+        const double r2 = kc.reach2 - by * by - bz * bz;
+        live[u] = left > 0 && !(r2 < 0.0);
+        h[u] = r2;
+        R[u] = make_int4(1, 0, 0, 0);
+        if (live[u]) R[u] = frame_rows[(int64_t)kz * T.dim[1] + ky];
+        --left;
+        if (++ky > y1) {
+          ky = y0;
+          ++kz;
+        }
+      }
+      uint2 range[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        range[u] = make_uint2(0u, 0u);
+        if (R[u].y < R[u].x) continue;
+        const double w = sqrt(h[u]);
+        const int xa = max(clamp_floor((qx - w) * inv - T.org[0], -1, T.dim[0]), R[u].x);
+        const int xb = min(clamp_floor((qx + w) * inv - T.org[0], -1, T.dim[0]), R[u].y);
+        if (xa > xb) continue;
+        const uint32_t* xt = frame_xt + (uint32_t)R[u].z;
+        range[u] = make_uint2(xt[xa - R[u].x], xt[xb + 1 - R[u].x]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (range[u].x < range[u].y) slots[64 * n++] = range[u];
+    }
+    // the lane's own ranges, four candidates a step
+    uint32_t j = 0, end = 0;
+    int r = 0;
+    auto next = [&]() {
+      if (j >= end && r < n) {
+        const uint2 v = slots[64 * r++];
+        j = v.x;
+        end = v.y;
+      }
+    };
+    float4 z[U];
+    int32_t o[U];
+    auto load = [&]() {
+      if (j < end) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const uint32_t k = min(j + (uint32_t)u, end - 1u);
+          z[u] = tp[k];
+          if constexpr (PERM) o[u] = to[k];
+        }
+      }
+    };
+    next();
+    load();
+    while (__ballot(j < end)) {
+      float4 cz[U];
+      int32_t co[U];
+      const uint32_t cj = j, cend = end;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        cz[u] = z[u];
+        co[u] = PERM ? o[u] : 0;
+      }
+      j += U;
+      next();
+      load();
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (cj + (uint32_t)u < cend) body(cj + (uint32_t)u, cz[u], co[u]);
     }
   }
 }
@@ -201,9 +315,9 @@ __global__ __launch_bounds__(256) void k_fill_passes(const EdgeInfo* __restrict_
 // the cells around its own transformed point only (for sparse frames, where
 // a shared box would be much larger than one point's neighbourhood).
 // TOPK > 0 (with LOCAL): each source point keeps only its kc.topk (<= TOPK)
-// pairs with the largest kernel values c exp(-|d|^2 / 2 ell^2) (ranked in
-// FP64; ties: smaller squared distance, then smaller original index); the
-// moments and the pair count come from those pairs only.
+// pairs with the largest kernel values c exp(-|d|^2 / 2 ell^2) (TopK; ties:
+// smaller squared distance, then smaller original index); the moments and the
+// pair count come from those pairs only.
 template <int MODE, int FEAT, int G, int DP, bool LOCAL, int TOPK>
 __global__ __launch_bounds__(kThreads) void k_pairs(PairArgs a) {
   constexpr int P = 64 / G;
@@ -253,64 +367,71 @@ __global__ __launch_bounds__(kThreads) void k_pairs(PairArgs a) {
   uint32_t cnt = 0;
   const float4* __restrict__ tp = a.pts + Fn.pt_off;
 
-  if (LOCAL && !valid) {  // empty walk for this lane
-    lo = make_float3(FLT_MAX, FLT_MAX, FLT_MAX);
-    hi = make_float3(-FLT_MAX, -FLT_MAX, -FLT_MAX);
-  }
   // the label layer walked in a label-stacked target frame: each lane's own (LOCAL), or the pass's (its
   // sources share one class id: passes never straddle a class id of a stacked source frame)
   uint32_t wl = lbl;
   if constexpr (!LOCAL) wl = (uint32_t)__shfl((int)lbl, __builtin_ctzll(__ballot(valid)), 64);
   const int64_t lrow = label_rows(Fn, wl);
-  TopK<(TOPK > 0 ? TOPK : 1)> best;
+  constexpr bool NEAR = FEAT == FEAT_CLASS;
+  TopK<(TOPK > 0 ? TOPK : 1), NEAR> best;
   if constexpr (TOPK > 0) best.clear();
-  const int topk = kc.topk;
-  for_each_range(Fn, a.rows, a.xtab, kc, lo, hi, lrow, [&](uint32_t j0, uint32_t j1) {
-    for (uint32_t j = j0 + g; j < j1; j += G) {
-      const float4 z = tp[j];
-      float dx, dy, dz;
-      const float s2 = rule_s2(q, z.x, z.y, z.z, dx, dy, dz);
-      bool in = valid && s2 <= rc2;
-      if constexpr (FEAT == FEAT_CLASS) in = in && (__float_as_uint(z.w) == lbl);
-      if (in) {
-        float c = 1.0f;
-        if constexpr (FEAT != FEAT_CLASS) {
-          const float acc = dot_feature_row<FEAT, DP>(a.feat, Fn.pt_off + j, fs);
-          c = clamp ? fmaxf(acc, 0.f) : acc;
-        }
-        const float w = c * __builtin_amdgcn_exp2f(-alpha * s2);
-        if constexpr (TOPK > 0) {
-          if (c > 0.f) {
-            const double key = (double)c * exp(-(double)s2 * kc.inv2l2);
-            if (best.may_enter(topk, key, s2)) best.insert(topk, key, s2, a.perm[Fn.pt_off + j], w, dx, dy, dz);
-          }
-          continue;
-        }
-        A += w;
+  const int topk = __builtin_amdgcn_readfirstlane(kc.topk);
+  float lim = rc2;  // squared distance from which no candidate matters
+  auto accumulate = [&](float w, float s2, float dx, float dy, float dz) {
+    A += w;
+    if constexpr (MODE == MODE_NORMAL) {
+      const float wx = w * dx, wy = w * dy;
+      Bx += wx; By += wy; Bz = fmaf(w, dz, Bz);
+      Cxx = fmaf(wx, dx, Cxx); Cxy = fmaf(wx, dy, Cxy); Cxz = fmaf(wx, dz, Cxz);
+      Cyy = fmaf(wy, dy, Cyy); Cyz = fmaf(wy, dz, Cyz); Wr2 = fmaf(w, s2, Wr2);
+    }
+  };
+  auto inner = [&](uint32_t j) {
+    float c = 1.0f;
+    if constexpr (FEAT != FEAT_CLASS) {
+      const float acc = dot_feature_row<FEAT, DP>(a.feat, Fn.pt_off + j, fs);
+      c = clamp ? fmaxf(acc, 0.f) : acc;
+    }
+    return c;
+  };
+  auto candidate = [&](uint32_t j, const float4& z, int32_t original) {
+    float dx, dy, dz;
+    const float s2 = rule_s2(q, z.x, z.y, z.z, dx, dy, dz);
+    bool in = valid && s2 <= lim;
+    if constexpr (FEAT == FEAT_CLASS) in = in && (__float_as_uint(z.w) == lbl);
+    if (!in) return;
+    if constexpr (TOPK > 0 && NEAR) {
+      best.insert(0.0, best.rank_of(s2, original), j);
+      lim = fminf(rc2, best.last_s2(topk));
+    } else {
+      const float c = inner(j);
+      const float w = c * __builtin_amdgcn_exp2f(-alpha * s2);
+      if constexpr (TOPK > 0) {
+        if (c > 0.f) topk_offer(best, topk, c, w, s2, kc, j, original);
+      } else {
         cnt += (c != 0.f) ? 1u : 0u;
-        if constexpr (MODE == MODE_NORMAL) {
-          const float wx = w * dx, wy = w * dy;
-          Bx += wx; By += wy; Bz = fmaf(w, dz, Bz);
-          Cxx = fmaf(wx, dx, Cxx); Cxy = fmaf(wx, dy, Cxy); Cxz = fmaf(wx, dz, Cxz);
-          Cyy = fmaf(wy, dy, Cyy); Cyz = fmaf(wy, dz, Cyz); Wr2 = fmaf(w, s2, Wr2);
-        }
+        accumulate(w, s2, dx, dy, dz);
       }
     }
-  });
-
+  };
+  if constexpr (LOCAL) {
+    __shared__ uint2 slots[kThreads * kLocalRanges];
+    local_walk<(TOPK > 0)>(Fn, a.rows, a.xtab, kc, q, valid, lrow, a.pts, a.perm,
+                           slots + (threadIdx.x >> 6) * 64 * kLocalRanges + lane, candidate);
+  } else {
+    for_each_range(Fn, a.rows, a.xtab, kc, lo, hi, lrow, [&](uint32_t j0, uint32_t j1) {
+      for (uint32_t j = j0 + g; j < j1; j += G) candidate(j, tp[j], 0);
+    });
+  }
   if constexpr (TOPK > 0) {  // moments of the kept pairs
-#pragma unroll
-    for (int t = 0; t < TOPK; ++t) {
-      if (!(best.key[t] > 0.0)) continue;
-      const float w = best.w[t], dx = best.dx[t], dy = best.dy[t], dz = best.dz[t];
-      A += w;
+#pragma unroll 1
+    for (int t = 0; t < topk; ++t, best.pop()) {  // (rolled: the list moves up instead of the index)
+      if (!best.first_kept(kc.inv2l2)) continue;
+      const float4 z = tp[best.j[0]];
+      float dx, dy, dz;
+      const float s2 = rule_s2(q, z.x, z.y, z.z, dx, dy, dz);
       cnt += 1u;
-      if constexpr (MODE == MODE_NORMAL) {
-        const float wx = w * dx, wy = w * dy;
-        Bx += wx; By += wy; Bz = fmaf(w, dz, Bz);
-        Cxx = fmaf(wx, dx, Cxx); Cxy = fmaf(wx, dy, Cxy); Cxz = fmaf(wx, dz, Cxz);
-        Cyy = fmaf(wy, dy, Cyy); Cyz = fmaf(wy, dz, Cyz); Wr2 = fmaf(w, best.s2[t], Wr2);
-      }
+      accumulate(rounded_product(inner(best.j[0]), __builtin_amdgcn_exp2f(-alpha * s2)), s2, dx, dy, dz);
     }
   }
   // Sum the G lanes that share a source point (lanes s, s+P, s+2P, ...).
@@ -534,7 +655,8 @@ __global__ __launch_bounds__(kThreads) void k_export_pairs(const float4* __restr
   const int32_t oi = perm[Fm.pt_off + i];
   float fs[DP > 0 ? DP : 1];
   if constexpr (TOPK && FEAT != FEAT_CLASS) load_feature_row<FEAT, DP>(feat, Fm.pt_off + i, fs);
-  TopK<kMaxTopK> best;
+  constexpr bool NEAR = FEAT == FEAT_CLASS;
+  TopK<kMaxTopK, NEAR> best;
   if constexpr (TOPK) best.clear();
   for_each_range(Fn, rows, xtab, kc, q, q, label_rows(Fn, lbl), [&](uint32_t j0, uint32_t j1) {
     for (uint32_t j = j0; j < j1; ++j) {
@@ -544,16 +666,13 @@ __global__ __launch_bounds__(kThreads) void k_export_pairs(const float4* __restr
       bool in = s2 <= kc.rc2;
       if constexpr (FEAT == FEAT_CLASS) in = in && __float_as_uint(z.w) == lbl;
       if (!in) continue;
-      if constexpr (TOPK) {
-        float c = 1.0f;
-        if constexpr (FEAT != FEAT_CLASS) {
-          const float acc = dot_feature_row<FEAT, DP>(feat, Fn.pt_off + j, fs);
-          c = kc.clamp ? fmaxf(acc, 0.f) : acc;
-        }
-        if (c > 0.f) {
-          const double key = (double)c * exp(-(double)s2 * kc.inv2l2);
-          if (best.may_enter(kc.topk, key, s2)) best.insert(kc.topk, key, s2, perm[Fn.pt_off + j], 0.f, dx, dy, dz);
-        }
+      if constexpr (TOPK && NEAR) {
+        best.insert(0.0, best.rank_of(s2, perm[Fn.pt_off + j]), j);
+      } else if constexpr (TOPK) {
+        const float acc = dot_feature_row<FEAT, DP>(feat, Fn.pt_off + j, fs);
+        const float c = kc.clamp ? fmaxf(acc, 0.f) : acc;
+        if (c > 0.f)
+          topk_offer(best, kc.topk, c, c * __builtin_amdgcn_exp2f(-kc.alpha * s2), s2, kc, j, perm[Fn.pt_off + j]);
       } else {
         const unsigned long long k = atomicAdd(count, 1ull);
         if ((int64_t)k < cap) {
@@ -564,13 +683,12 @@ __global__ __launch_bounds__(kThreads) void k_export_pairs(const float4* __restr
     }
   });
   if constexpr (TOPK) {
-#pragma unroll
-    for (int t = 0; t < kMaxTopK; ++t) {
-      if (!(best.key[t] > 0.0)) continue;
+    for (int t = 0; t < kc.topk; ++t, best.pop()) {
+      if (!best.first_kept(kc.inv2l2)) continue;
       const unsigned long long k = atomicAdd(count, 1ull);
       if ((int64_t)k < cap) {
         out[2 * k] = oi;
-        out[2 * k + 1] = best.jo[t];
+        out[2 * k + 1] = (int32_t)(uint32_t)best.rank[0];
       }
     }
   }

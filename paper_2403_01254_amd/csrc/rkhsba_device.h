@@ -119,58 +119,89 @@ __device__ inline float dot_feature_row(const void* __restrict__ base, int64_t r
   return acc;
 }
 
-// The K best pairs of one source point: larger ranking key c exp(-s2 / 2 ell^2)
-// (FP64), then smaller FP32 squared distance s2, then smaller original index j.
-// Entries are kept best first; unused entries hold a sentinel (key -1) that
-// every real pair (key > 0) beats.  All indexing is static (registers).
-template <int K>
+// The K best pairs of one source point: larger kernel value c exp(-s2 / 2 ell^2) (FP64), then smaller FP32 squared
+// distance s2, then smaller original index.  Kept best first, by compare-and-exchange down the list (static indexing:
+// registers).  An entry is its rank (s2's bits above the original index: one integer comparison decides both ties) and
+// the target's sorted index j, from which the caller recomputes the pair's terms once the walk is done: entries that
+// carried them made an insertion 150 instructions and the kernel 158 registers.
+// NEAR (class ids, c = 1): exp falls with s2, so the rank alone orders the pairs and no FP64 value is needed.
+template <int K, bool NEAR>
 struct TopK {
-  double key[K];
-  float s2[K], w[K], dx[K], dy[K], dz[K];
-  int32_t jo[K];
+  static constexpr uint64_t kNone = 0x7f800000ffffffffull;  // unused entry: infinitely far
+  uint64_t rank[K];
+  double key[NEAR ? 1 : K];
+  uint32_t j[K];
   __device__ void clear() {
 #pragma unroll
     for (int t = 0; t < K; ++t) {
-      key[t] = -1.0;
-      s2[t] = 3.0e38f;
-      jo[t] = 0x7fffffff;
-      w[t] = dx[t] = dy[t] = dz[t] = 0.f;
+      rank[t] = kNone;
+      j[t] = 0u;
+      if constexpr (!NEAR) key[t] = -1.0;
     }
   }
-  __device__ static bool better(double k1, float a1, int32_t j1, double k2, float a2, int32_t j2) {
-    return k1 > k2 || (k1 == k2 && (a1 < a2 || (a1 == a2 && j1 < j2)));
+  __device__ static uint64_t rank_of(float s2, int32_t original) {
+    return (uint64_t)__float_as_uint(s2) << 32 | (uint32_t)original;
   }
-  // Could (key, s2) enter a list of the first k entries?  (The index tie-break is decided in insert.)
-  __device__ bool may_enter(int k, double kk, float ss) const {
-    double lk = -1.0;
-    float ls = 3.0e38f;
+  __device__ static float s2_of(uint64_t rank) { return __uint_as_float((uint32_t)(rank >> 32)); }
+  __device__ void insert(double kk, uint64_t rk, uint32_t jj) {
 #pragma unroll
-    for (int t = 0; t < K; ++t)
-      if (t == k - 1) {
-        lk = key[t];
-        ls = s2[t];
-      }
-    return kk > lk || (kk == lk && ss <= ls);
-  }
-  __device__ void insert(int k, double kk, float ss, int32_t j, float ww, float ax, float ay, float az) {
-    bool placed = false;
-#pragma unroll
-    for (int t = K - 1; t >= 0; --t) {
-      if (t >= k || placed) continue;
-      if (t == k - 1 && !better(kk, ss, j, key[t], s2[t], jo[t])) {  // not better than the last kept pair
-        placed = true;
-        continue;
-      }
-      if (t > 0 && better(kk, ss, j, key[t - 1], s2[t - 1], jo[t - 1])) {
-        key[t] = key[t - 1]; s2[t] = s2[t - 1]; jo[t] = jo[t - 1];
-        w[t] = w[t - 1]; dx[t] = dx[t - 1]; dy[t] = dy[t - 1]; dz[t] = dz[t - 1];
-      } else {
-        key[t] = kk; s2[t] = ss; jo[t] = j; w[t] = ww; dx[t] = ax; dy[t] = ay; dz[t] = az;
-        placed = true;
+    for (int t = 0; t < K; ++t) {
+      bool ahead = rk < rank[t];
+      if constexpr (!NEAR) ahead = kk > key[t] || (kk == key[t] && ahead);
+      const uint64_t r = ahead ? rank[t] : rk;
+      rank[t] = ahead ? rk : rank[t];
+      rk = r;
+      const uint32_t q = ahead ? j[t] : jj;
+      j[t] = ahead ? jj : j[t];
+      jj = q;
+      if constexpr (!NEAR) {
+        const double k = ahead ? key[t] : kk;
+        key[t] = ahead ? kk : key[t];
+        kk = k;
       }
     }
+  }
+  // The k-th entry's distance, and its kernel value (k >= 1, the same in every lane).
+  __device__ float last_s2(int k) const {
+    uint64_t r = kNone;
+#pragma unroll
+    for (int t = 0; t < K; ++t) r = t == k - 1 ? rank[t] : r;
+    return s2_of(r);
+  }
+  __device__ double last_key(int k) const {
+    double v = -1.0;
+#pragma unroll
+    for (int t = 0; t < K; ++t) v = t == k - 1 ? key[t] : v;
+    return v;
+  }
+  // Whether the first entry is a pair with a kernel value above 0.
+  __device__ bool first_kept(double inv2l2) const {
+    if (rank[0] == kNone) return false;
+    if constexpr (NEAR) return exp(-(double)s2_of(rank[0]) * inv2l2) > 0.0;
+    else return key[0] > 0.0;
+  }
+  __device__ void pop() {
+#pragma unroll
+    for (int t = 0; t + 1 < K; ++t) {
+      rank[t] = rank[t + 1];
+      j[t] = j[t + 1];
+      if constexpr (!NEAR) key[t] = key[t + 1];
+    }
+    rank[K - 1] = kNone;
   }
 };
+
+// Offers a dense pair with c > 0 to the list.  Most pairs are behind the last kept one: their FP32 kernel value w,
+// which is within 1e-5 of the FP64 one where exp2 is far from its ends, decides that without an FP64 exponential.
+template <int K>
+__device__ inline void topk_offer(TopK<K, false>& best, int k, float c, float w, float s2, const KConst& kc,
+                                  uint32_t j, int32_t original) {
+  const double last = best.last_key(k);
+  const float bound = (float)last;
+  if (bound > 1e-30f && kc.alpha * s2 < 100.f && w * 1.0001f < bound) return;
+  const double key = (double)c * exp(-(double)s2 * kc.inv2l2);
+  if (key >= last) best.insert(key, TopK<K, false>::rank_of(s2, original), j);
+}
 
 // The FP32 squared distance of the membership rule.
 __device__ inline float rule_s2(float3 q, float zx, float zy, float zz, float& dx, float& dy, float& dz) {
