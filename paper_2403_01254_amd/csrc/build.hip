@@ -125,27 +125,32 @@ __global__ __launch_bounds__(kSortThreads) void k_cell_keys(const float* const* 
   hist[(int64_t)blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
 }
 
-// One workgroup per frame of at most NT * IPT points: keys, and their sort in LDS.
-template <int NT, int IPT>
-__global__ __launch_bounds__(NT) void k_cell_sort(const float* const* __restrict__ xyz, double inv_cell,
-                                                  const FrameInfo* __restrict__ frames,
-                                                  const void* const* __restrict__ cls,
-                                                  const SortSeg* __restrict__ segs, int bits,
-                                                  uint32_t* __restrict__ sorted_keys,
-                                                  uint32_t* __restrict__ sorted_vals, int lo, int hi) {
-  __shared__ typename BlockSort<NT, IPT>::Shared sh;
-  const SortSeg S = segs[blockIdx.x];
-  if (S.count <= lo || S.count > hi) return;  // (uniform) sorted in tiles, or by another launch
-  const FrameInfo F = frames[S.owner];
-  const int base = (int)(threadIdx.x >> 6) * 64 * IPT + (int)(threadIdx.x & 63);
-  uint32_t key[IPT];
+// One workgroup per run: keys, and their sort in LDS; the only run of its frame is done, the others are merged.
+constexpr int kRunThreads = 512, kRunItems = 4;
+__global__ __launch_bounds__(kRunThreads) void k_cell_runs(const float* const* __restrict__ xyz, double inv_cell,
+                                                           const FrameInfo* __restrict__ frames,
+                                                           const void* const* __restrict__ cls,
+                                                           const SortTile* __restrict__ runs, int bits,
+                                                           uint32_t* __restrict__ run_keys,
+                                                           uint32_t* __restrict__ run_vals,
+                                                           uint32_t* __restrict__ sorted_keys,
+                                                           uint32_t* __restrict__ sorted_vals) {
+  static_assert(kRunThreads * kRunItems == kSortTile, "a run");
+  __shared__ typename BlockSort<kRunThreads, kRunItems>::Shared sh;
+  const SortTile T = runs[blockIdx.x];
+  const FrameInfo F = frames[T.edge];
+  const int64_t first = T.start - F.pt_off;
+  const int base = (int)(threadIdx.x >> 6) * 64 * kRunItems + (int)(threadIdx.x & 63);
+  uint32_t key[kRunItems];
 #pragma unroll
-  for (int r = 0; r < IPT; ++r)
-    key[r] = base + 64 * r < S.count ? cell_key(xyz, inv_cell, F, cls, S.owner, base + 64 * r) : 0u;
-  BlockSort<NT, IPT>::sort(key, S.count, bits, sh);
-  for (int i = threadIdx.x; i < S.count; i += NT) {
-    sorted_keys[S.start + i] = sh.key[i];
-    sorted_vals[S.start + i] = sh.val[i];
+  for (int r = 0; r < kRunItems; ++r)
+    key[r] = base + 64 * r < T.count ? cell_key(xyz, inv_cell, F, cls, T.edge, first + base + 64 * r) : 0u;
+  BlockSort<kRunThreads, kRunItems>::sort(key, T.count, bits, sh);
+  uint32_t* __restrict__ keys = T.runs == 1 ? sorted_keys : run_keys;
+  uint32_t* __restrict__ vals = T.runs == 1 ? sorted_vals : run_vals;
+  for (int i = threadIdx.x; i < T.count; i += kRunThreads) {
+    keys[T.start + i] = sh.key[i];
+    vals[T.start + i] = (uint32_t)first + sh.val[i];
   }
 }
 
@@ -463,20 +468,17 @@ hipError_t launch_frame_bounds(const float* const* d_xyz_ptrs, const int64_t* d_
 hipError_t launch_cell_sort(const float* const* d_xyz_ptrs, double inv_cell, const FrameInfo* d_frames,
                             const void* const* d_class_ptrs, const SortTile* d_tiles, const SortSeg* d_segs,
                             const SortPlan& plan, int bits, uint32_t* d_keys, uint32_t* d_vals, uint32_t* d_hist,
-                            uint32_t* d_sorted_keys, uint32_t* d_sorted_vals, hipStream_t st) {
+                            uint32_t* d_run_keys, uint32_t* d_run_vals, uint32_t* d_sorted_keys,
+                            uint32_t* d_sorted_vals, hipStream_t st) {
   if (plan.n_tiles > 0)
     k_cell_keys<<<(unsigned)plan.n_tiles, kSortThreads, 0, st>>>(d_xyz_ptrs, inv_cell, d_frames, d_class_ptrs,
                                                                  d_tiles, d_keys, d_vals, d_hist);
-  plan.block_launches([&](int c, int lo, int hi) {
-    const unsigned nb = (unsigned)plan.n_segs;
-    auto run = [&](auto kernel, int threads) {
-      kernel<<<nb, threads, 0, st>>>(d_xyz_ptrs, inv_cell, d_frames, d_class_ptrs, d_segs, bits, d_sorted_keys,
-                                     d_sorted_vals, lo, hi);
-    };
-    if (c == 0) run(k_cell_sort<512, 4>, 512);
-    else if (c == 1) run(k_cell_sort<1024, 8>, 1024);
-    else run(k_cell_sort<1024, 16>, 1024);
-  });
+  if (plan.n_runs > 0)
+    k_cell_runs<<<(unsigned)plan.n_runs, kRunThreads, 0, st>>>(d_xyz_ptrs, inv_cell, d_frames, d_class_ptrs,
+                                                               d_tiles + plan.n_tiles, bits, d_run_keys, d_run_vals,
+                                                               d_sorted_keys, d_sorted_vals);
+  hipError_t e = launch_merge(d_run_keys, d_run_vals, d_tiles, d_segs, plan, d_sorted_keys, d_sorted_vals, st);
+  if (e != hipSuccess) return e;
   return hipGetLastError();
 }
 

@@ -392,10 +392,8 @@ int rkhsba_accumulate_normal_eqs(rkhsba_ctx* c, const double* poses, int E, cons
     const int n = 6 * p->K;
     g.evaluate(c->lay_eval, MODE_NORMAL, false, STEP_SYSTEM);
     const SolveArgs sa = g.solve_args(c->lay_eval);
-    if (H) RK_HIP(hipMemcpyAsync(H, sa.H, sizeof(double) * n * n, hipMemcpyDeviceToHost, c->stream));
-    if (b) RK_HIP(hipMemcpyAsync(b, sa.b, sizeof(double) * n, hipMemcpyDeviceToHost, c->stream));
     double F = 0.0, np = 0.0;
-    g.results(p, 1, nullptr, &F, &np);
+    g.results(p, 1, nullptr, &F, &np, {{H, sa.H, sizeof(double) * n * n}, {b, sa.b, sizeof(double) * n}});
     g.prof_collect();
     if (loss_total) *loss_total = F;
     if (n_pairs) *n_pairs = (int64_t)np;

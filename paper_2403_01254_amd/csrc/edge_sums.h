@@ -59,7 +59,7 @@ __device__ __forceinline__ int wave_sum_spread(T (&v)[N]) {
   return held > 0 ? idx : N;
 }
 
-__device__ inline void sym_row_col(int k, int& r, int& c) {  // k-th entry of a 6x6 upper triangle, row-major
+__device__ __forceinline__ void sym_row_col(int k, int& r, int& c) {  // k-th entry of a 6x6 upper triangle, row-major
   r = 0;
   int len = 6;
   while (k >= len) {
@@ -72,7 +72,7 @@ __device__ inline void sym_row_col(int k, int& r, int& c) {  // k-th entry of a 
 
 // Entry (i, j) of the cross-product matrix of a.
 template <typename T>
-__device__ inline T skew_at(const T* a, int i, int j) {
+__device__ __forceinline__ T skew_at(const T* a, int i, int j) {
   if (i == j) return (T)0;
   const T v = a[3 - i - j];
   return (j - i + 3) % 3 == 1 ? -v : v;
@@ -80,7 +80,7 @@ __device__ inline T skew_at(const T* a, int i, int j) {
 
 // Value k of an edge (F, b_m, b_n, H_mm, H_nn, H_mn, pairs, sum w r^2; kEdgeVals) from its sums T.
 template <typename TT>
-__device__ inline double edge_value(const TT* T, const EdgeXf& X, double n_pairs, int k) {
+__device__ __forceinline__ double edge_value(const TT* T, const EdgeXf& X, double n_pairs, int k) {
   auto Rmn = [&](int r, int c) { return (TT)X.R[3 * c + r]; };
   const TT A = T[kStA];
   const TT* B = T + kStB;
@@ -139,26 +139,35 @@ struct EdgeSums {  // LDS of one wavefront
 
 // One wavefront: the edge's sums over its finalisation blocks in block order, expanded into out[kEdgeVals].  The
 // values are spread over the lanes: one thread wrote all 93 of them before, 10 us of serial FP64 for 28 edges that
-// now take 3.
+// now take 3.  Inlined by force, with its helpers: in a function of its own, LDS is reached through generic pointers,
+// and the constant part of an index can be folded into the instruction so that the base lies before the LDS aperture,
+// which faults.
 template <typename TT>
-__device__ inline void reduce_edge(const double* __restrict__ partial, const EdgeInfo& ed, const EdgeXf& X, int mode,
-                                   EdgeSums<TT>& sh, double* __restrict__ out) {
+__device__ __forceinline__ void reduce_edge(const double* __restrict__ partial, const EdgeInfo& ed, const EdgeXf& X,
+                                            int mode, EdgeSums<TT>& sh, double* __restrict__ out) {
   const int lane = threadIdx.x & 63;
   const int ns = mode == MODE_LOSS ? 2 : kFinStats;
   const double* p = partial + (int64_t)ed.fin_off * kFinStats + lane;
-  if (lane == ns - 1) {  // the pair counts
-    double c = 0.0;
-#pragma unroll 8
-    for (int b = 0; b < ed.n_fin; ++b) c += p[(int64_t)b * kFinStats];
-    sh.n_pairs = c;
-    sh.T[lane] = (TT)0;
-  } else if (lane < kFinStats) {
+  if (lane < kFinStats) {
+    // 16 blocks' values in flight at a time, added in block order
+    constexpr int U = 16;
+    const bool count = lane == ns - 1;  // the pair counts, summed in FP64
     Acc<TT> s;
-    if (lane < ns) {
-#pragma unroll 8
-      for (int b = 0; b < ed.n_fin; ++b) s.add((TT)p[(int64_t)b * kFinStats]);
-    }
-    sh.T[lane] = s.value();
+    double c = 0.0;
+    if (lane < ns)
+      for (int b = 0; b < ed.n_fin; b += U) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = b + u < ed.n_fin ? p[(int64_t)(b + u) * kFinStats] : 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (b + u < ed.n_fin) {
+            if (count) c += v[u];
+            else s.add((TT)v[u]);
+          }
+      }
+    if (count) sh.n_pairs = c;
+    sh.T[lane] = count ? (TT)0 : s.value();
   }
   wave_sync();
   for (int k = lane; k < kEdgeVals; k += 64)

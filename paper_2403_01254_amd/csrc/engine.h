@@ -227,7 +227,8 @@ struct SetLayout {
   };
   std::vector<Group> groups;        // contiguous runs of the pass table, one sweep launch each
   uint32_t item_cap = 0;            // room for the items of spread passes (0: passes are not split)
-  bool small = false;               // every problem's step fits one workgroup (small_step)
+  bool small = false;               // every problem's step fits one workgroup (small_step),
+  bool sum_in_step = false;         // and the sums of its edges too
   bool clamp = false;
   bool c_positive = false;          // every problem's inner products are > 0 (pair counts need no c != 0 test)
   DBuf<uint8_t> d_tables;           // the host tables, which the views below are pieces of
@@ -349,8 +350,9 @@ class Engine {
   // After an evaluation with source_counts on, of a set whose first edge has source frame m of p:
   // every source point's pair count, by its original index (frame m's point count; synchronises).
   void read_source_counts(Problem* p, int m, int64_t* counts);
-  // poses (host K*12), loss and pairs (count entries each; all nullable) and the status (waits for the stream)
-  int32_t results(Problem* p, int count, double* poses, double* loss, double* pairs);
+  // poses (host K*12), loss and pairs (count entries each; all nullable), up to two pieces more, and the status
+  // (waits for the stream)
+  int32_t results(Problem* p, int count, double* poses, double* loss, double* pairs, std::vector<Download> more = {});
   // values first .. first + count - 1 of the first E edges of the last evaluation (waits for the stream)
   void read_edges(int E, int first, int count, double* out);
   void read_loss(int E, double* F, double* pairs);  // their F and pair counts

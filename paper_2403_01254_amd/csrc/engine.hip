@@ -492,13 +492,14 @@ int Engine::build(ProbParams par_in, int K, const int64_t* n_points, const float
     RK_HIP(v1_.reserve(N));
     RK_HIP(k2_.reserve(N));
     RK_HIP(v2_.reserve(N));
-    std::vector<SortTile> tiles;
-    std::vector<SortSeg> segs;
-    SortPlan plan;
-    for (int f = 0; f < K; ++f) plan.add(segs, tiles, off[f], n_points[f], f);
+    SortTables sorts;
+    for (int f = 0; f < K; ++f) sorts.add(off[f], n_points[f], f);
+    const SortPlan& plan = sorts.plan;
+    const std::vector<SortTile> tiles = sorts.pieces();
+    const std::vector<SortSeg>& segs = sorts.segs;
     RK_HIP(d_tiles_.reserve(tiles.size()));
     RK_HIP(d_segs_.reserve(K));
-    RK_HIP(hist_scratch_.reserve(tiles.size() * 256));
+    RK_HIP(hist_scratch_.reserve((size_t)plan.n_tiles * 256));
     RK_HIP(d_totals_.reserve(2));
     std::vector<Upload> tables{{d_tiles_.p, tiles.data(), sizeof(SortTile) * tiles.size()},
                                {d_segs_.p, segs.data(), sizeof(SortSeg) * K}};
@@ -594,8 +595,8 @@ int Engine::build(ProbParams par_in, int K, const int64_t* n_points, const float
       sk = in_tmp ? k2_.p : k1_.p;
       sv = in_tmp ? v2_.p : v1_.p;
       RK_HIP(launch_cell_sort(d_xyz_ptrs_.p, kc0.inv_cell, d_bframes_.p, d_feat_ptrs_.p, d_tiles_.p, d_segs_.p, plan,
-                              key_bits, k1_.p, v1_.p, hist_scratch_.p, in_tmp ? k2_.p : k1_.p, in_tmp ? v2_.p : v1_.p,
-                              bst));
+                              key_bits, k1_.p, v1_.p, hist_scratch_.p, in_tmp ? k1_.p : k2_.p, in_tmp ? v1_.p : v2_.p,
+                              in_tmp ? k2_.p : k1_.p, in_tmp ? v2_.p : v1_.p, bst));
       RK_HIP(launch_radix_sort(k1_.p, v1_.p, k2_.p, v2_.p, hist_scratch_.p, d_tiles_.p, d_segs_.p, plan, key_bits, true,
                                true, bst));
       p->n_rows = std::max<int64_t>(rows_total, 1);
@@ -795,13 +796,15 @@ void Engine::ensure_history(Problem* p, int n_iter) {
   p->n_hist = need;
 }
 
-int32_t Engine::results(Problem* p, int count, double* poses, double* loss, double* pairs) {
+int32_t Engine::results(Problem* p, int count, double* poses, double* loss, double* pairs,
+                        std::vector<Download> more) {
   RK_REQUIRE(p->hbase >= 0 && count <= p->n_hist, RKHSBA_ESTATE, "no history of that length");
   int32_t s[2] = {0, 0};
-  receive({{poses, poses_ptr(p), sizeof(double) * 12 * p->K},
-           {loss, static_cast<double*>(hist_.ptr(0)) + p->hbase, sizeof(double) * count},
-           {pairs, static_cast<double*>(hist_.ptr(1)) + p->hbase, sizeof(double) * count},
-           {s, static_cast<int32_t*>(state_.ptr(0)) + 2 * p->sbase, sizeof(s)}}, st);
+  more.push_back({poses, poses_ptr(p), sizeof(double) * 12 * p->K});
+  more.push_back({loss, static_cast<double*>(hist_.ptr(0)) + p->hbase, sizeof(double) * count});
+  more.push_back({pairs, static_cast<double*>(hist_.ptr(1)) + p->hbase, sizeof(double) * count});
+  more.push_back({s, static_cast<int32_t*>(state_.ptr(0)) + 2 * p->sbase, sizeof(s)});
+  receive(more, st);
   return s[1];
 }
 
@@ -909,10 +912,9 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   for (const SetItem& it : items) E_total += it.E;
   std::vector<EdgeInfo> info(E_total);
   std::vector<int32_t> foff(E_total);
-  std::vector<SortTile> tiles;
-  std::vector<SortSeg> segs;
-  SortPlan plan;
-  segs.reserve(E_total);
+  SortTables sorts;
+  const SortPlan& plan = sorts.plan;
+  const std::vector<SortSeg>& segs = sorts.segs;
   std::vector<KConst> kcs(items.size());
   bool all_stacked = !items.empty();
   // one launch per group of equal pass size; group 4: per-point walks with top-k selection
@@ -923,7 +925,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   std::vector<int32_t> bstart_all, blist, vstart_all, vlist;
   int64_t entries = 0, passes = 0, fins = 0, h_total = 0, v_total = 0;
   int bin_bits = 3, n_max = 0;
-  bool clamp = false, positive = true, many_rows = false, small = true;
+  bool clamp = false, positive = true, many_rows = false, small = true, in_step = true;
   int e_glob = 0;
   for (size_t pi = 0; pi < items.size(); ++pi) {
     const SetItem& it = items[pi];
@@ -985,7 +987,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
           parts.emplace_back(0, I.n_src);
         }
         for (const auto& pr : parts) {
-          plan.add(segs, tiles, entries + pr.first, pr.second, e_glob);
+          sorts.add(entries + pr.first, pr.second, e_glob);
           I.n_pass += (int32_t)((pr.second + P - 1) / P);
         }
       }
@@ -1011,7 +1013,8 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
         vec[n].push_back(e_glob * 2 + 1);
       }
     }
-    small = small && small_step(S, fin_blocks);
+    small = small && small_step(S);
+    in_step = in_step && sum_in_step(it.E, fin_blocks);
     S.blk0 = (int32_t)bstart_all.size();
     for (size_t k = 0; k < blk.size(); ++k) {
       bstart_all.push_back((int32_t)blist.size());
@@ -1065,6 +1068,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
     blob.resize(at.back() + std::max<size_t>(bytes, 8));
     if (bytes) std::memcpy(blob.data() + at.back(), src, bytes);
   };
+  const std::vector<SortTile> tiles = sorts.pieces();
   table(info.data(), sizeof(EdgeInfo) * E_total);
   table(foff.data(), sizeof(int32_t) * E_total);
   table(tiles.data(), sizeof(SortTile) * tiles.size());
@@ -1110,7 +1114,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   need(sc_->bv, entries, "bv");
   need(sc_->bk2, entries, "bk2");
   need(sc_->bv2, entries, "bv2");
-  need(sc_->bhist, tiles.size() * 256, "bhist");
+  need(sc_->bhist, (size_t)plan.n_tiles * 256, "bhist");
   need(sc_->mom, (size_t)entries * (arena_ ? arena_->mom_components : 10), "mom");
   need(sc_->cnt, entries, "cnt");
   need(sc_->partial, (size_t)fins * kFinStats, "partial");
@@ -1149,6 +1153,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   lay.bin_bits = bin_bits;
   lay.clamp = clamp;
   lay.small = small;
+  lay.sum_in_step = in_step;
   lay.item_cap = item_cap;
   lay.c_positive = positive && !items.empty();
   lay.h_total = h_total;
@@ -1181,7 +1186,8 @@ void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning, int step, bo
   } else {
     uint32_t* sorted = sort_ends_in_tmp(lay.bin_bits) ? sc_->bv2.p : sc_->bv.p;
     RK_HIP(launch_bin(pts(), frames(), lay.d_edges.p, lay.d_etiles.p, lay.d_esegs.p, lay.plan, sc_->xf.p, lay.d_kcs.p,
-                      lay.bin_bits, sc_->bk.p, sc_->bv.p, sc_->bhist.p, sorted, st));
+                      lay.bin_bits, sc_->bk.p, sc_->bv.p, sc_->bhist.p, sorted == sc_->bv.p ? sc_->bv2.p : sc_->bv.p,
+                      sorted, st));
     RK_HIP(launch_radix_sort(sc_->bk.p, sc_->bv.p, sc_->bk2.p, sc_->bv2.p, sc_->bhist.p, lay.d_etiles.p,
                              lay.d_esegs.p, lay.plan, lay.bin_bits, true, false, st));
     sorted_v_ = sorted;
@@ -1248,10 +1254,13 @@ void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning, int step, bo
   fa.n_fin_total = lay.n_fin_total;
   hipEvent_t t2 = prof_begin();
   RK_HIP(launch_finalize(fa, lay.d_fin_off.p, mode, fp32_sums, st));
-  if (lay.small && step != STEP_NONE) {
-    prof_end(RKHSBA_PROF_FINALIZE, t2);
+  const bool fused = lay.small && step != STEP_NONE;
+  if (!fused || !lay.sum_in_step)
+    RK_HIP(launch_edge_reduce(sc_->partial.p, lay.d_edges.p, sc_->xf.p, lay.E, mode, fp32_sums, sc_->edge_out.p, st));
+  prof_end(RKHSBA_PROF_FINALIZE, t2);
+  if (fused) {
     StepArgs u{};
-    u.partial = sc_->partial.p;
+    u.partial = lay.sum_in_step ? sc_->partial.p : nullptr;
     u.edges = lay.d_edges.p;
     u.xf = sc_->xf.p;
     u.edge_out = sc_->edge_out.p;
@@ -1261,8 +1270,6 @@ void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning, int step, bo
     prof_end(step == STEP_SOLVE ? RKHSBA_PROF_SOLVE : RKHSBA_PROF_FINALIZE, t3);
     return;
   }
-  RK_HIP(launch_edge_reduce(sc_->partial.p, lay.d_edges.p, sc_->xf.p, lay.E, mode, fp32_sums, sc_->edge_out.p, st));
-  prof_end(RKHSBA_PROF_FINALIZE, t2);
   if (step == STEP_NONE) return;
   hipEvent_t t3 = step == STEP_SOLVE ? prof_begin() : nullptr;
   if (step == STEP_LOSS) RK_HIP(launch_loss_only(solve_args(lay), st));

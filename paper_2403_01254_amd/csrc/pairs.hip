@@ -250,31 +250,44 @@ __global__ __launch_bounds__(kSortThreads) void k_bin(const float4* __restrict__
   hist[(int64_t)blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
 }
 
-// One workgroup per segment of at most NT * IPT entries: keys, and their sort in LDS.  All digits take one launch
-// and no pass over memory, where the tiled sort takes two launches per digit: latency bound either way (2 frames x
-// 1,000 points, three digits: 10 launches, 40 us of kernels -> 1 launch, 9 us).
-template <int NT, int IPT>
-__global__ __launch_bounds__(NT) void k_bin_sort(const float4* __restrict__ pts, const FrameInfo* __restrict__ frames,
-                                                 const EdgeInfo* __restrict__ edges,
-                                                 const SortSeg* __restrict__ segs, const EdgeXf* __restrict__ xf,
-                                                 const KConst* __restrict__ kcs, int bits,
-                                                 uint32_t* __restrict__ sorted, int lo, int hi) {
-  __shared__ typename BlockSort<NT, IPT>::Shared sh;
-  const SortSeg S = segs[blockIdx.x];
-  if (S.count <= lo || S.count > hi) return;  // (uniform) sorted in tiles, or by another launch
-  const EdgeInfo ed = edges[S.owner];
+// One workgroup per run: keys, and their sort in LDS; the only run of its segment is done, the others are merged.  All
+// digits take one launch and no pass over memory, where the tiled sort takes two launches per digit: latency bound
+// either way (2 frames x 1,000 points, three digits: 10 launches, 40 us of kernels -> 1 launch, 9 us).
+constexpr int kRunThreads = 512, kRunItems = 4;
+__global__ __launch_bounds__(kRunThreads) void k_bin_runs(const float4* __restrict__ pts,
+                                                          const FrameInfo* __restrict__ frames,
+                                                          const EdgeInfo* __restrict__ edges,
+                                                          const SortTile* __restrict__ runs,
+                                                          const EdgeXf* __restrict__ xf,
+                                                          const KConst* __restrict__ kcs, int bits,
+                                                          uint32_t* __restrict__ run_keys,
+                                                          uint32_t* __restrict__ run_vals,
+                                                          uint32_t* __restrict__ sorted) {
+  static_assert(kRunThreads * kRunItems == kSortTile, "a run");
+  __shared__ typename BlockSort<kRunThreads, kRunItems>::Shared sh;
+  const SortTile T = runs[blockIdx.x];
+  const EdgeInfo ed = edges[T.edge];
   const KConst kc = kcs[ed.prob];
   const FrameInfo Fm = frames[ed.m];
   const FrameInfo Fn = frames[ed.n];
-  const EdgeXf X = xf[S.owner];
-  const uint32_t src0 = (uint32_t)(S.start - ed.ent_off);
-  const int base = (int)(threadIdx.x >> 6) * 64 * IPT + (int)(threadIdx.x & 63);
-  uint32_t key[IPT];
+  const EdgeXf X = xf[T.edge];
+  const uint32_t src0 = (uint32_t)(T.start - ed.ent_off);
+  const int base = (int)(threadIdx.x >> 6) * 64 * kRunItems + (int)(threadIdx.x & 63);
+  uint32_t key[kRunItems];
 #pragma unroll
-  for (int r = 0; r < IPT; ++r)
-    key[r] = base + 64 * r < S.count ? bin_key(pts, Fm, Fn, X, kc, src0 + (uint32_t)(base + 64 * r)) : 0u;
-  BlockSort<NT, IPT>::sort(key, S.count, bits, sh);
-  for (int i = threadIdx.x; i < S.count; i += NT) sorted[S.start + i] = src0 + sh.val[i];
+  for (int r = 0; r < kRunItems; ++r)
+    key[r] = base + 64 * r < T.count ? bin_key(pts, Fm, Fn, X, kc, src0 + (uint32_t)(base + 64 * r)) : 0u;
+  BlockSort<kRunThreads, kRunItems>::sort(key, T.count, bits, sh);
+  const uint32_t digits = bits > 24 ? ~0u : (1u << ((bits + 7) & ~7)) - 1u;  // the key bits that the sort looks at
+  for (int i = threadIdx.x; i < T.count; i += kRunThreads) {
+    const uint32_t val = src0 + sh.val[i];
+    if (T.runs == 1) {
+      sorted[T.start + i] = val;
+    } else {
+      run_keys[T.start + i] = sh.key[i] & digits;
+      run_vals[T.start + i] = val;
+    }
+  }
 }
 
 // ---------------------------------------------------------------- pass table
@@ -745,16 +758,15 @@ hipError_t launch_edge_setup(const double* d_poses, const EdgeInfo* d_edges, int
 hipError_t launch_bin(const float4* d_pts, const FrameInfo* d_frames, const EdgeInfo* d_edges,
                       const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan, const EdgeXf* d_xf,
                       const KConst* d_kcs, int bits, uint32_t* d_keys, uint32_t* d_vals, uint32_t* d_hist,
-                      uint32_t* d_sorted, hipStream_t st) {
+                      uint32_t* d_run_vals, uint32_t* d_sorted, hipStream_t st) {
   if (plan.n_tiles > 0)
     k_bin<<<(unsigned)plan.n_tiles, kSortThreads, 0, st>>>(d_pts, d_frames, d_edges, d_tiles, d_xf, d_kcs, d_keys,
                                                            d_vals, d_hist);
-  plan.block_launches([&](int c, int lo, int hi) {
-    const unsigned nb = (unsigned)plan.n_segs;
-    if (c == 0) k_bin_sort<512, 4><<<nb, 512, 0, st>>>(d_pts, d_frames, d_edges, d_segs, d_xf, d_kcs, bits, d_sorted, lo, hi);
-    else if (c == 1) k_bin_sort<1024, 8><<<nb, 1024, 0, st>>>(d_pts, d_frames, d_edges, d_segs, d_xf, d_kcs, bits, d_sorted, lo, hi);
-    else k_bin_sort<1024, 16><<<nb, 1024, 0, st>>>(d_pts, d_frames, d_edges, d_segs, d_xf, d_kcs, bits, d_sorted, lo, hi);
-  });
+  if (plan.n_runs > 0)
+    k_bin_runs<<<(unsigned)plan.n_runs, kRunThreads, 0, st>>>(d_pts, d_frames, d_edges, d_tiles + plan.n_tiles, d_xf,
+                                                              d_kcs, bits, d_keys, d_run_vals, d_sorted);
+  hipError_t e = launch_merge(d_keys, d_run_vals, d_tiles, d_segs, plan, nullptr, d_sorted, st);
+  if (e != hipSuccess) return e;
   return hipGetLastError();
 }
 

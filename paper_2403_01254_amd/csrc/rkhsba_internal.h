@@ -15,6 +15,7 @@
 
 #include <cstring>
 #include <string>
+#include <vector>
 
 namespace rkhsba {
 
@@ -105,83 +106,91 @@ struct KConst {
 };
 constexpr int kMaxTopK = 8;
 
-// Segmented LSD radix sort: tiles never straddle a segment.
+// A piece of a segment to be sorted: a tile of the LSD radix sort, or a run that one workgroup sorts in LDS.
 struct SortTile {
   int64_t start;     // first element
   int32_t count;     // elements (<= kSortTile)
   int32_t seg;       // segment id
   int32_t edge;      // edge of the binning entries (edge sorts), or the frame (point sorts)
-  int32_t pad_;
+  int32_t runs;      // runs of the segment (tiles: 0)
 };
 struct SortSeg {
   int64_t start;
   int32_t count;     // elements (a frame's or a class id's points, < 2^31)
   int32_t owner;     // edge of the binning entries (edge sorts), or the frame (point sorts)
   int32_t tile0;     // first tile
-  int32_t n_tiles;   // 0: sorted by one workgroup in LDS (at most kBlockSortMax elements)
+  int32_t n_tiles;   // 0: sorted in runs (at most kMergeMax elements)
 };
 constexpr int kSortThreads = 256;
 constexpr int kSortItems = 8;
 constexpr int kSortTile = kSortThreads * kSortItems;
-// Segments of at most this many elements are sorted by one workgroup in LDS, in one launch for all digits; larger
-// ones in tiles, two launches per digit.  The limit is what one workgroup's 160 KB hold (6 B per element and the
-// digit counters).
-constexpr int kBlockSortMax = 16384;
+// Segments of at most this many elements are sorted in runs of kSortTile, all digits in one launch, and the runs of a
+// segment of several are merged by a second.  Larger ones take two launches per digit.  The merge reads a segment's
+// keys once per run and searches every other run: 12 segments of 16,000 elements 12.8 + 12 us, and 28 of 30,000 18 + 55,
+// where the tiles take 63.
+constexpr int kMergeMax = 16384;
 
-// How the segments of one launch are sorted (host-side counts of a segment table).
+// How the segments of one launch are sorted.
 struct SortPlan {
   int n_segs = 0;
-  int n_tiles = 0;        // tiles of the segments above kBlockSortMax
+  int n_tiles = 0;        // tiles of the segments above kMergeMax
   int max_seg_tiles = 0;  // most tiles of one segment
-  int max_block = 0;      // largest segment sorted by one workgroup (0: none)
-  int n_class[3] = {0, 0, 0};  // segments per workgroup size (block_class)
-  // Workgroups of 512 threads x 4 elements, 1024 x 8 and 1024 x 16.
-  static int block_class(int count) { return count <= 2048 ? 0 : count <= 8192 ? 1 : 2; }
-  // Runs launch(class, lo, hi) for the segments of lo < count <= hi.  A few segments (up to one per CU) take one
-  // launch of the largest segment's workgroup: they run side by side, and a launch costs more than a workgroup
-  // larger than its segment.  Many take one launch per workgroup size, so that the small ones do not hold the
-  // large ones' LDS.  (LiDAR, 64 x 100,000 points, 7,680 class-id segments: build and binning sorts 1.72 ms per
-  // solve in tiles, 1.26 ms with these.)
-  template <typename Launch>
-  void block_launches(Launch&& launch) const {
-    const int hi[3] = {2048, 8192, kBlockSortMax};
-    if (max_block <= 0) return;
-    if (n_segs <= 256) return launch(block_class(max_block), 0, kBlockSortMax);
-    for (int c = 0; c < 3; ++c)
-      if (n_class[c] > 0) launch(c, c > 0 ? hi[c - 1] : 0, hi[c]);
-  }
-  // Adds a segment of `count` elements; fills its tile range and appends its tiles.
-  template <typename Tiles, typename Segs>
-  void add(Segs& segs, Tiles& tiles, int64_t start, int64_t count, int32_t owner) {
+  int n_multi = 0;        // runs of the segments of several runs
+  int n_runs = 0;         // those and the segments of one run
+  int max_multi = 0;      // largest segment of several runs
+};
+// The tables of a plan: segments, and pieces in the order tiles, runs of several, single runs.
+struct SortTables {
+  SortPlan plan;
+  std::vector<SortSeg> segs;
+  void add(int64_t start, int64_t count, int32_t owner) {
     SortSeg S{};
     S.start = start;
     S.count = (int32_t)count;
     S.owner = owner;
-    S.tile0 = n_tiles;
-    if (count > kBlockSortMax) {
-      for (int64_t s = 0; s < count; s += kSortTile)
-        tiles.push_back(SortTile{start + s, (int32_t)(count - s < kSortTile ? count - s : kSortTile), n_segs, owner, 0});
-      S.n_tiles = (int32_t)((count + kSortTile - 1) / kSortTile);
-      n_tiles += S.n_tiles;
-      if (S.n_tiles > max_seg_tiles) max_seg_tiles = S.n_tiles;
+    S.tile0 = plan.n_tiles;
+    const int pieces = (int)((count + kSortTile - 1) / kSortTile);
+    const bool tiled = count > kMergeMax;
+    std::vector<SortTile>& list = tiled ? tiles_ : pieces > 1 ? multi_ : single_;
+    for (int64_t s = 0; s < count; s += kSortTile)
+      list.push_back(SortTile{start + s, (int32_t)(count - s < kSortTile ? count - s : kSortTile), plan.n_segs, owner,
+                              tiled ? 0 : pieces});
+    if (tiled) {
+      S.n_tiles = pieces;
+      plan.n_tiles += pieces;
+      if (pieces > plan.max_seg_tiles) plan.max_seg_tiles = pieces;
     } else {
-      if (S.count > max_block) max_block = S.count;
-      ++n_class[block_class(S.count)];
+      plan.n_runs += pieces;
+      if (pieces > 1) plan.n_multi += pieces;
+      if (pieces > 1 && S.count > plan.max_multi) plan.max_multi = S.count;
     }
     segs.push_back(S);
-    ++n_segs;
+    ++plan.n_segs;
   }
+  std::vector<SortTile> pieces() const {
+    std::vector<SortTile> all(tiles_);
+    all.insert(all.end(), multi_.begin(), multi_.end());
+    all.insert(all.end(), single_.begin(), single_.end());
+    return all;
+  }
+
+ private:
+  std::vector<SortTile> tiles_, multi_, single_;
 };
 
 // ---------------------------------------------------------------- launchers
 // Each returns hipSuccess or the first HIP error.  All run on `st`.
 
 // Digit passes of the tiled segments, over key bits [0, bits).  hist0: the tiles' counts of digit 0 are in
-// `hist` already.  keep_keys: the sorted keys are wanted too, not only the values.  The result ends in (keys, vals) or, for an odd number of digits, in (keys_tmp, vals_tmp):
+// `hist` already.  keep_keys: the sorted keys are wanted too, not only the values.  The result ends in (keys, vals)
+// or, for an odd number of digits, in (keys_tmp, vals_tmp):
 // sort_ends_in_tmp(bits).
 hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp,
                              uint32_t* hist, const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan,
                              int bits, bool hist0, bool keep_keys, hipStream_t st);
+// Merges the sorted runs of the segments of several, from (keys, vals) to (out_keys, out_vals); out_keys may be null.
+hipError_t launch_merge(const uint32_t* keys, const uint32_t* vals, const SortTile* d_pieces, const SortSeg* d_segs,
+                        const SortPlan& plan, uint32_t* out_keys, uint32_t* out_vals, hipStream_t st);
 inline bool sort_ends_in_tmp(int bits) { return (((bits + 7) / 8) & 1) != 0; }
 
 hipError_t launch_exclusive_scan(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* tmp, uint64_t* d_total,
@@ -205,12 +214,14 @@ inline float float_of_ordered(uint32_t o) {
   return v;
 }
 // Cell keys (frames with n_lab > 0 take the class ids, d_class_ptrs, into kz') and their sort by frame, stable.
-// Frames of at most kBlockSortMax points end in (d_sorted_keys, d_sorted_vals) at once; the keys and values of the
-// others are left in (d_keys, d_vals), with their tiles' counts of digit 0, for launch_radix_sort.
+// Frames of at most kMergeMax points end in (d_sorted_keys, d_sorted_vals), by way of (d_run_keys, d_run_vals); the
+// keys and values of the others are left in (d_keys, d_vals), with their tiles' counts of digit 0, for
+// launch_radix_sort.
 hipError_t launch_cell_sort(const float* const* d_xyz_ptrs, double inv_cell, const FrameInfo* d_frames,
                             const void* const* d_class_ptrs, const SortTile* d_tiles, const SortSeg* d_segs,
                             const SortPlan& plan, int bits, uint32_t* d_keys, uint32_t* d_vals, uint32_t* d_hist,
-                            uint32_t* d_sorted_keys, uint32_t* d_sorted_vals, hipStream_t st);
+                            uint32_t* d_run_keys, uint32_t* d_run_vals, uint32_t* d_sorted_keys,
+                            uint32_t* d_sorted_vals, hipStream_t st);
 // For every label-stacked frame f (frame-local key order) and class id l in [0, n_lab]: the first point
 // of layer l (l = n_lab: the frame's count), at d_out[d_lab_off[f] + l].
 hipError_t launch_label_starts(const uint32_t* d_keys, const FrameInfo* d_frames, const int64_t* d_lab_off, int K,
@@ -259,13 +270,13 @@ hipError_t launch_fill_passes(const EdgeInfo* d_edges, int E, const FrameInfo* d
 // d_n_items (nullable): the sweep's item counter, cleared here.
 hipError_t launch_edge_setup(const double* d_poses, const EdgeInfo* d_edges, int E, EdgeXf* d_xf, uint32_t* d_n_items,
                              hipStream_t st);
-// Source binning.  Segments of at most kBlockSortMax entries: keys and sort in one workgroup each, their sorted
-// source indices written to d_sorted.  The others: keys and source indices of every entry, one block per tile,
+// Source binning.  Segments of at most kMergeMax entries: their sorted source indices written to d_sorted, by way of
+// (d_keys, d_run_vals), d_run_vals another array than d_sorted.  The others: keys and source indices of every entry, one block per tile,
 // with the tile's counts of digit 0, for launch_radix_sort.
 hipError_t launch_bin(const float4* d_pts, const FrameInfo* d_frames, const EdgeInfo* d_edges,
                       const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan, const EdgeXf* d_xf,
                       const KConst* d_kcs, int bits, uint32_t* d_keys, uint32_t* d_vals, uint32_t* d_hist,
-                      uint32_t* d_sorted, hipStream_t st);
+                      uint32_t* d_run_vals, uint32_t* d_sorted, hipStream_t st);
 
 // Passes whose box spans more rows than this skip the batches of rows that no source of theirs is near.  The
 // sources of such a pass lie in a few places far apart (a jump of the Morton order), and most rows of the box
@@ -398,17 +409,18 @@ struct SolveArgs {
 // entry, also H and b, or the whole Gauss-Newton step.
 enum Step { STEP_NONE = 0, STEP_LOSS = 1, STEP_SYSTEM = 2, STEP_SOLVE = 3 };
 struct StepArgs {
-  const double* partial;   // finalisation partial sums
+  const double* partial;   // finalisation partial sums (null: edge_out holds the edges' values already)
   const EdgeInfo* edges;
   EdgeXf* xf;              // STEP_SOLVE leaves those of the moved poses
   double* edge_out;
   uint32_t* n_items;       // cleared (nullable)
 };
-// Whether one workgroup takes a problem's whole step: the system fits in LDS, and its edges and their finalisation
-// blocks are few enough for 16 wavefronts (4 edges each, 2 us an edge; the reduction of more spreads over the chip).
+// Whether one workgroup takes a problem's whole step: the system fits in LDS, and assembling it reads few edges.  It
+// takes their sums too where each wavefront has one edge and few finalisation blocks (sum_in_step; 2 edges each: 7 us
+// of one CU, as much as a launch that spreads them; 28 edges of 118 blocks: 1 MB through one CU, 30 us).
 constexpr int kStepEdges = 64;
-constexpr int64_t kStepFinBlocks = 4096;
-bool small_step(const ProbSys& S, int64_t fin_blocks);
+bool small_step(const ProbSys& S);
+inline bool sum_in_step(int edges, int64_t fin_blocks) { return edges <= 16 && fin_blocks <= 512; }
 // The step of every problem of a set of small ones.
 hipError_t launch_step(const SolveArgs& a, const StepArgs& u, int mode, int step, bool fp32_sums, hipStream_t st);
 // Writes H, b of every problem (and the loss / pair-count history entry of the

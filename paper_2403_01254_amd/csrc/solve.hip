@@ -612,7 +612,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_update(SolveArgs a) {
 }
 
 // What follows an evaluation's finalisation, for sets of small problems (small_step): one workgroup per problem sums
-// and expands its edges, one wavefront each, records the loss, and then writes H and b as well (STEP_SYSTEM), or
+// and expands its edges, one wavefront each (unless k_edge_reduce has), records the loss, and then writes H and b as well (STEP_SYSTEM), or
 // (STEP_SOLVE) assembles the system in LDS, solves it, moves the poses and prepares the next evaluation's edge
 // transforms.  The same operations in the same order as k_edge_reduce, k_assemble, k_loss_only,
 // k_solve_update and k_edge_setup, which a large set needs more than one workgroup for: launches and the gaps
@@ -626,8 +626,9 @@ __global__ __launch_bounds__(kSolveThreads) void k_step(SolveArgs a, StepArgs u)
   const ProbSys S = a.sys[blockIdx.x];
   const int t = threadIdx.x, w = t >> 6;
   if (blockIdx.x == 0 && t == 0 && u.n_items) *u.n_items = 0u;  // of the next evaluation's sweep
-  for (int e = S.e0 + w; e < S.e0 + S.E; e += kSolveThreads / 64)
-    reduce_edge<TT>(u.partial, u.edges[e], u.xf[e], MODE, sums[w], u.edge_out + (int64_t)e * kEdgeVals);
+  if (u.partial)
+    for (int e = S.e0 + w; e < S.e0 + S.E; e += kSolveThreads / 64)
+      reduce_edge<TT>(u.partial, u.edges[e], u.xf[e], MODE, sums[w], u.edge_out + (int64_t)e * kEdgeVals);
   __threadfence_block();
   __syncthreads();
   if (w == 0) record_loss(a, S);
@@ -695,9 +696,7 @@ static void run_step(const SolveArgs& a, const StepArgs& u, int step, hipStream_
   }
 }
 
-bool small_step(const ProbSys& S, int64_t fin_blocks) {
-  return S.n <= kLdsSystem && S.E <= kStepEdges && fin_blocks <= kStepFinBlocks;
-}
+bool small_step(const ProbSys& S) { return S.n <= kLdsSystem && S.E <= kStepEdges; }
 
 hipError_t launch_step(const SolveArgs& a, const StepArgs& u, int mode, int step, bool fp32_sums, hipStream_t st) {
   if (a.n_prob <= 0) return hipSuccess;
