@@ -240,6 +240,8 @@ struct SetLayout {
   DBuf<PassInfo> d_passes;
   DBuf<ProbSys> d_sys;
   DBuf<int32_t> d_blk_start, d_blk_list, d_vec_start, d_vec_list;
+  DBuf<uint16_t> d_plans;           // block-sparse elimination plans
+  bool need_h = true;               // some problem's solve reads the assembled H
   std::vector<ProbSys> sys;         // host copy
   int64_t h_total = 0, v_total = 0;
   // graph of one Gauss-Newton iteration over the set

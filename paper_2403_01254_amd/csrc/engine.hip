@@ -1,6 +1,7 @@
 // Engine: resident problem storage, set layouts and the launch sequences of
 // the voxel build, the evaluation and the Gauss-Newton iteration.
 #include "engine.h"
+#include "solve_plan.h"
 
 #include <algorithm>
 #include <climits>
@@ -923,6 +924,8 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   std::vector<int8_t> egroup(E_total);
   std::vector<ProbSys> sys(items.size());
   std::vector<int32_t> bstart_all, blist, vstart_all, vlist;
+  std::vector<uint16_t> plans;
+  bool need_h = false;
   int64_t entries = 0, passes = 0, fins = 0, h_total = 0, v_total = 0;
   int bin_bits = 3, n_max = 0;
   bool clamp = false, positive = true, many_rows = false, small = true, in_step = true;
@@ -1013,6 +1016,21 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
         vec[n].push_back(e_glob * 2 + 1);
       }
     }
+    // systems too large for a dense triangle in LDS: a sparse plan, where its blocks fit
+    S.plan0 = -1;
+    if (S.n > kLdsSystem && it.n_iter > 0 && S.n / 6 <= kSparseMaxFrames) {
+      const int nf = S.n / 6;
+      auto frame = [&](int k) { return it.fixed >= 0 && k >= it.fixed ? k + 1 : k; };
+      std::vector<uint8_t> adj((size_t)nf * nf, 0);
+      for (int r = 0; r < nf; ++r)
+        for (int c = 0; c < nf; ++c) adj[(size_t)r * nf + c] = r != c && !blk[(size_t)frame(r) * K + frame(c)].empty();
+      const std::vector<uint16_t> plan = sparse_plan(nf, std::move(adj));
+      if (!plan.empty()) {
+        S.plan0 = (int32_t)plans.size();
+        plans.insert(plans.end(), plan.begin(), plan.end());
+      }
+    }
+    need_h = need_h || S.plan0 < 0;
     small = small && small_step(S);
     in_step = in_step && sum_in_step(it.E, fin_blocks);
     S.blk0 = (int32_t)bstart_all.size();
@@ -1079,6 +1097,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   table(blist.data(), sizeof(int32_t) * blist.size());
   table(vstart_all.data(), sizeof(int32_t) * vstart_all.size());
   table(vlist.data(), sizeof(int32_t) * vlist.size());
+  table(plans.data(), sizeof(uint16_t) * plans.size());
   blob.resize((blob.size() + 3) & ~(size_t)3);
   need(lay.d_tables, blob.size(), "tables");
   size_t view = 0;
@@ -1096,6 +1115,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   attach(lay.d_blk_list, blist.size());
   attach(lay.d_vec_start, vstart_all.size());
   attach(lay.d_vec_list, vlist.size());
+  attach(lay.d_plans, plans.size());
   uint8_t* stage = blob.size() <= 2 * kPutBytes ? nullptr : lay.stage_for(blob.size(), arena_ != nullptr);
   if (stage) {
     std::memcpy(stage, blob.data(), blob.size());
@@ -1154,6 +1174,7 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   lay.clamp = clamp;
   lay.small = small;
   lay.sum_in_step = in_step;
+  lay.need_h = need_h;
   lay.item_cap = item_cap;
   lay.c_positive = positive && !items.empty();
   lay.h_total = h_total;
@@ -1272,7 +1293,7 @@ void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning, int step, bo
   }
   if (step == STEP_NONE) return;
   hipEvent_t t3 = step == STEP_SOLVE ? prof_begin() : nullptr;
-  if (step == STEP_LOSS) RK_HIP(launch_loss_only(solve_args(lay), st));
+  if (step == STEP_LOSS || (step == STEP_SOLVE && !lay.need_h)) RK_HIP(launch_loss_only(solve_args(lay), st));
   else RK_HIP(launch_assemble(solve_args(lay), st));
   if (step == STEP_SOLVE) RK_HIP(launch_solve_update(solve_args(lay), st));
   prof_end(RKHSBA_PROF_SOLVE, t3);
@@ -1295,6 +1316,7 @@ SolveArgs Engine::solve_args(SetLayout& lay) {
   s.blk_list = lay.d_blk_list.p;
   s.vec_start = lay.d_vec_start.p;
   s.vec_list = lay.d_vec_list.p;
+  s.plans = lay.d_plans.p;
   return s;
 }
 

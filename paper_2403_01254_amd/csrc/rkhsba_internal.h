@@ -383,6 +383,8 @@ struct ProbSys {
   int64_t state_off;  // offset of its (iter, status) pair
   double sigma2;
   double damping_rel;
+  int32_t plan0;      // first word of its block-sparse elimination plan in the set's plans (-1: none)
+  int32_t pad_;
 };
 
 struct SolveArgs {
@@ -404,6 +406,7 @@ struct SolveArgs {
   // contributors of each frame's 6-vector of b, CSR over vec0 + a: entries e*2 + role, role 0 b_m, 1 b_n
   const int32_t* vec_start;
   const int32_t* vec_list;
+  const uint16_t* plans;   // block-sparse elimination plans (solve_plan.h)
 };
 // What follows an evaluation's finalisation: nothing but the per-edge values, the loss and pair-count history
 // entry, also H and b, or the whole Gauss-Newton step.

@@ -6,11 +6,13 @@
 // Assembly is one thread per entry of the system, summing that entry's
 // contributing edge blocks in edge order (host-built lists, deterministic).
 // The solve is one workgroup per problem: systems up to 128 unknowns are
-// eliminated in LDS, one frame's columns at a time; larger ones run a blocked
-// right-looking Cholesky with 32-wide panels, the panel kept in LDS for the
-// trailing update.  Sets of small problems run the whole step, from the
+// eliminated in LDS, one frame's columns at a time, and so are the blocks of
+// larger ones where few frames share an edge (solve_plan.h); the others run a
+// blocked right-looking Cholesky with 32-wide panels, the panel kept in LDS for
+// the trailing update.  Sets of small problems run the whole step, from the
 // finalisation's partial sums to the moved poses, in one kernel (k_step).
 #include "edge_sums.h"
+#include "solve_plan.h"
 
 namespace rkhsba {
 namespace {
@@ -152,7 +154,6 @@ __device__ inline double lane_value(double v, int lane) {
 // column per barrier and a separate forward solve took 0.7 us per unknown (n = 42: 32 us a solve; now the whole step
 // around it takes 17).
 constexpr int kSolveThreads = 1024;
-constexpr int kLdsSystem = 128;
 constexpr int kLdsDoubles = kLdsSystem * (kLdsSystem + 1);  // shared buffer of both paths
 
 struct SmallShared {
@@ -170,9 +171,28 @@ __device__ inline double reciprocal(double d) {
   return fma(fma(-d, r, 1.0), r, r);
 }
 
+// L D L^T of a diagonal block in d (lower triangle; d[r][c] * rd[c] is L below the diagonal, rd the reciprocal
+// pivots), column by column, and a row x of the columns' rest in step with it.
+__device__ __forceinline__ void eliminate_block(double (&d)[6][6], double (&x)[6], double (&rd)[6], bool& ok) {
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    ok = ok && d[j][j] > 0.0;
+    rd[j] = reciprocal(d[j][j]);
+#pragma unroll
+    for (int r = j + 1; r < 6; ++r) {
+      const double l = d[r][j] * rd[j];
+#pragma unroll
+      for (int c = j + 1; c <= r; ++c) d[r][c] = fma(-l, d[c][j], d[r][c]);
+    }
+    const double l = x[j] * rd[j];
+#pragma unroll
+    for (int c = j + 1; c < 6; ++c) x[c] = fma(-l, d[c][j], x[c]);
+  }
+}
+
 // S.A holds the lower triangle of H + mu I and -b; all threads of the block.  Solution in y (global, n); false (in
 // every thread) when a pivot is not positive.
-__device__ bool solve_small(int n, SmallShared& S, double* __restrict__ y) {
+__device__ __forceinline__ bool solve_small(int n, SmallShared& S, double* __restrict__ y) {
   const int t = threadIdx.x, tx = t & 31, ty = t >> 5, ld = n + 1;
   double* A = S.A;
   if (t == 0) S.bad = 0;
@@ -190,21 +210,7 @@ __device__ bool solve_small(int n, SmallShared& S, double* __restrict__ y) {
         for (int c = 0; c <= r; ++c) d[r][c] = A[(p + r) * ld + p + c];
 #pragma unroll
       for (int c = 0; c < 6; ++c) x[c] = A[i * ld + p + c];
-      // the block's L (below the diagonal of d) and pivots, column by column; the row in step with it
-#pragma unroll
-      for (int j = 0; j < 6; ++j) {
-        ok = ok && d[j][j] > 0.0;
-        rd[j] = reciprocal(d[j][j]);
-#pragma unroll
-        for (int r = j + 1; r < 6; ++r) {
-          const double l = d[r][j] * rd[j];
-#pragma unroll
-          for (int c = j + 1; c <= r; ++c) d[r][c] = fma(-l, d[c][j], d[r][c]);
-        }
-        const double l = x[j] * rd[j];
-#pragma unroll
-        for (int c = j + 1; c < 6; ++c) x[c] = fma(-l, d[c][j], x[c]);
-      }
+      eliminate_block(d, x, rd, ok);
       if (!ok) S.bad = 1;
 #pragma unroll
       for (int c = 0; c < 6; ++c) {
@@ -297,7 +303,7 @@ constexpr int kPanelCols = (kLdsDoubles - NB * (NB + 1) - 2 * NB) / NB;  // rows
 constexpr int kFlagRows = NB + kPanelCols;  // the largest system every panel of which is solved in LDS
 constexpr int kFlagWords = ((kFlagRows + 31) / 32) * ((kFlagRows + 31) / 32);
 
-__device__ void solve_blocked(const ProbSys& S, const SolveArgs& a, double mu, double* buf, int32_t* status,
+__device__ __forceinline__ void solve_blocked(const ProbSys& S, const SolveArgs& a, double mu, double* buf, int32_t* status,
                               uint32_t* flags) {
   const int n = S.n, t = threadIdx.x, tx = t & 31, ty = t >> 5;
   const int W = (n + 31) / 32;
@@ -562,7 +568,133 @@ __device__ void solve_blocked(const ProbSys& S, const SolveArgs& a, double mu, d
   }
 }
 
+// ---- larger sparse systems: block elimination in LDS by the host's plan (solve_plan.h)
+//
+// As solve_small, one frame's 6 columns a step and -b as one more row, but only the blocks that the plan holds, and
+// the system assembled from the edges' values straight into them.  A chain of latencies: 63 steps of 2 us and their
+// way back for 64 LiDAR frames with 6 edges each, 0.18 ms, where the blocked dense elimination took 0.52 (12 panels
+// of 32 columns through global memory) and the assembly of H before it 0.01.
+struct SparseShared {
+  double d[kSparseLds / sizeof(double)];
+};
+
+// Solution in y (global, n, in frame order).  0: moved; 1: no pair touches a free frame; -4: a pivot is not positive
+// (the same in every thread).
+__device__ __forceinline__ int solve_sparse(const SolveArgs& a, const ProbSys& S, SparseShared& sh, double* __restrict__ red,
+                            int* __restrict__ bad, double* __restrict__ y) {
+  const int t = threadIdx.x;
+  const uint16_t* __restrict__ plan = a.plans + S.plan0;
+  const int words = sparse_words(plan[0], plan[1], plan[2]);
+  const int doubles = (int)sparse_doubles(plan[0], plan[1], plan[3]);
+  double* L = sh.d;
+  uint16_t* local = reinterpret_cast<uint16_t*>(sh.d + doubles);
+  for (int i = t; i < words; i += kSolveThreads) local[i] = plan[i];
+  if (t == 0) *bad = 0;
+  __syncthreads();
+  const int nf = local[0], n_off = local[1], n = 6 * nf;
+  // (index arithmetic on the one LDS array; no pointers of their own into it)
+  const int o_order = kSparseHeader, o_col = o_order + nf, o_upd = o_col + nf + 1, o_row = o_upd + nf + 1;
+  const int o_cols = o_row + n_off, o_list = o_cols + n_off;
+  double* rhs = L + 36 * (nf + n_off);
+  double* T = rhs + n;                          // a column's rows before the division by the pivots; last: the right side
+  double* dl = T + 6 * (6 * (int)local[3] + 1);  // the diagonal block's L
+  double tr = 0.0;
+  for (int e = t; e < 36 * (nf + n_off); e += kSolveThreads) {
+    const int blk = e / 36, q = e - 36 * blk, r = q / 6, c = q - 6 * r;
+    const int row = blk < nf ? blk : local[o_row + blk - nf], col = blk < nf ? blk : local[o_cols + blk - nf];
+    const double v = h_entry(a, S, 6 * local[o_order + row] + r, 6 * local[o_order + col] + c);
+    L[e] = v;
+    if (blk < nf && r == c) tr += v;
+  }
+  for (int i = t; i < n; i += kSolveThreads) rhs[i] = -b_entry(a, S, 6 * local[o_order + i / 6] + i % 6);
+  tr = block_sum(tr, red);
+  if (!(tr > 0.0)) return 1;
+  const double mu = S.damping_rel * tr / n;
+  for (int i = t; i < n; i += kSolveThreads) L[36 * (i / 6) + 7 * (i % 6)] += mu;
+  __syncthreads();
+  for (int p = 0; p < nf; ++p) {
+    const int c0 = local[o_col + p], rows = local[o_col + p + 1] - c0;
+    if (t <= 6 * rows) {
+      double d[6][6], x[6], rd[6];
+      bool ok = true;
+      const int at = t < 6 * rows ? 36 * (nf + c0) + 6 * t : (int)(rhs - L) + 6 * p;  // row t, or the right side
+#pragma unroll
+      for (int r = 0; r < 6; ++r)
+#pragma unroll
+        for (int c = 0; c <= r; ++c) d[r][c] = L[36 * p + 6 * r + c];
+#pragma unroll
+      for (int c = 0; c < 6; ++c) x[c] = L[at + c];
+      eliminate_block(d, x, rd, ok);
+      if (!ok) *bad = 1;
+#pragma unroll
+      for (int c = 0; c < 6; ++c) {
+        T[6 * t + c] = x[c];
+        L[at + c] = x[c] * rd[c];
+      }
+      if (t == 6 * rows) {
+#pragma unroll
+        for (int r = 1; r < 6; ++r)
+#pragma unroll
+          for (int c = 0; c < r; ++c) dl[r * (r - 1) / 2 + c] = d[r][c] * rd[c];
+      }
+    }
+    __syncthreads();
+    if (*bad) return -4;
+    const int u0 = local[o_upd + p], n_entries = 36 * (local[o_upd + p + 1] - u0);
+    for (int e = t; e < n_entries + 6 * rows; e += kSolveThreads) {
+      if (e < n_entries) {
+        const int u = e / 36, q = e - 36 * u, r = q / 6, c = q - 6 * r;
+        const int bi = local[o_list + 3 * (u0 + u)] - c0, bk = local[o_list + 3 * (u0 + u) + 1];
+        const int target = 36 * local[o_list + 3 * (u0 + u) + 2] + q;
+        double v = L[target];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) v = fma(-T[6 * (6 * bi + r) + k], L[36 * (nf + bk) + 6 * c + k], v);
+        L[target] = v;
+      } else {
+        const int i = e - n_entries, r = i % 6;
+        const int target = 6 * local[o_row + c0 + i / 6] + r;
+        double v = rhs[target];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) v = fma(-T[6 * 6 * rows + k], L[36 * (nf + c0) + 6 * i + k], v);
+        rhs[target] = v;
+      }
+    }
+    if (t < 36 && t % 6 < t / 6) L[36 * p + t] = dl[(t / 6) * (t / 6 - 1) / 2 + t % 6];
+    __syncthreads();
+  }
+  if (t < 64) {  // L^T x = y, one frame a step: lanes 8 g + c sum column c over the blocks g, g + 8, ..
+    const int g = t >> 3, c = t & 7;
+    for (int p = nf - 1; p >= 0; --p) {
+      const int c0 = local[o_col + p], rows = local[o_col + p + 1] - c0;
+      double v = 0.0;
+      if (c < 6)
+        for (int i = g; i < rows; i += 8) {
+          const int xr = 6 * local[o_row + c0 + i];
+#pragma unroll
+          for (int r = 0; r < 6; ++r) v = fma(L[36 * (nf + c0 + i) + 6 * r + c], rhs[xr + r], v);
+        }
+      v += __shfl_xor(v, 8, 64);
+      v += __shfl_xor(v, 16, 64);
+      v += __shfl_xor(v, 32, 64);
+      double u = c < 6 ? rhs[6 * p + c] - v : 0.0;
+#pragma unroll
+      for (int j = 5; j > 0; --j) {
+        const double xj = lane_value(u, j);
+        if (c < j) u = fma(-L[36 * p + 6 * j + c], xj, u);
+      }
+      if (t < 6) {
+        rhs[6 * p + t] = u;
+        y[6 * local[o_order + p] + t] = u;
+      }
+      wave_sync();
+    }
+  }
+  __syncthreads();
+  return 0;
+}
+
 union SolveShared {
+  SparseShared sparse;
   SmallShared small;
   struct {
     double buf[kLdsDoubles];
@@ -576,6 +708,7 @@ union SolveShared {
 __global__ __launch_bounds__(kSolveThreads) void k_solve_update(SolveArgs a) {
   __shared__ SolveShared sh;
   __shared__ double red[kSolveThreads / 64];
+  __shared__ int bad;
   const ProbSys S = a.sys[blockIdx.x];
   int32_t* st = a.state + S.state_off;
   const int iter = st[0];
@@ -583,28 +716,38 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_update(SolveArgs a) {
   __syncthreads();
   if (run) {
     const int n = S.n, t = threadIdx.x;
-    const double* H = a.H + S.h_off;
-    double tr = 0.0;
-    for (int i = t; i < n; i += kSolveThreads) tr += H[(int64_t)i * n + i];
-    tr = block_sum(tr, red);
-    if (tr > 0.0) {  // otherwise no pair touches a free frame: nothing moves
-      const double mu = S.damping_rel * tr / n;
-      if (n <= kLdsSystem) {
-        for (int idx = t; idx < n * n; idx += kSolveThreads) {
-          const int i = idx / n, k = idx - i * n;
-          if (k <= i) sh.small.A[i * (n + 1) + k] = H[idx] + (i == k ? mu : 0.0);
+    bool moved = false;
+    if (S.plan0 >= 0) {
+      const int e = solve_sparse(a, S, sh.sparse, red, &bad, a.delta + S.v_off);
+      if (e == -4 && t == 0) st[1] = -4;
+      moved = e == 0;
+    } else {
+      const double* H = a.H + S.h_off;
+      double tr = 0.0;
+      for (int i = t; i < n; i += kSolveThreads) tr += H[(int64_t)i * n + i];
+      tr = block_sum(tr, red);
+      if (tr > 0.0) {  // otherwise no pair touches a free frame: nothing moves
+        const double mu = S.damping_rel * tr / n;
+        if (n <= kLdsSystem) {
+          for (int idx = t; idx < n * n; idx += kSolveThreads) {
+            const int i = idx / n, k = idx - i * n;
+            if (k <= i) sh.small.A[i * (n + 1) + k] = H[idx] + (i == k ? mu : 0.0);
+          }
+          for (int i = t; i < n; i += kSolveThreads) sh.small.A[n * (n + 1) + i] = -a.b[S.v_off + i];
+          moved = solve_small(n, sh.small, a.delta + S.v_off);
+          if (!moved && t == 0) st[1] = -4;
+        } else {
+          solve_blocked(S, a, mu, sh.blocked.buf, st + 1, sh.blocked.zflags);
+          __syncthreads();
+          moved = st[1] == 0;
         }
-        for (int i = t; i < n; i += kSolveThreads) sh.small.A[n * (n + 1) + i] = -a.b[S.v_off + i];
-        if (!solve_small(n, sh.small, a.delta + S.v_off) && t == 0) st[1] = -4;
-      } else {
-        solve_blocked(S, a, mu, sh.blocked.buf, st + 1, sh.blocked.zflags);
       }
-      __syncthreads();
-      if (st[1] == 0) {
-        const double* y = a.delta + S.v_off;
-        for (int k = t; k < n / 6; k += kSolveThreads)
-          right_update(a.poses + 12 * (S.slot0 + frame_of_reduced(k, S.fixed)), y + 6 * k);
-      }
+    }
+    __syncthreads();
+    if (moved) {
+      const double* y = a.delta + S.v_off;
+      for (int k = t; k < n / 6; k += kSolveThreads)
+        right_update(a.poses + 12 * (S.slot0 + frame_of_reduced(k, S.fixed)), y + 6 * k);
     }
   }
   __syncthreads();
