@@ -85,9 +85,8 @@ __global__ __launch_bounds__(64) void k_loss_only(SolveArgs a) { record_loss(a, 
 
 // T <- T exp(xi^): closed-form SE(3) exponential (Rodrigues for the rotation,
 // V = I + B K + C K^2 for the translation), series for small angles.
-__device__ __noinline__ void right_update(double* T, const double* xi) {
-  const double* rho = xi;
-  const double* phi = xi + 3;
+__device__ __noinline__ void right_update(double* T, double r0, double r1, double r2, double p0, double p1, double p2) {
+  const double rho[3] = {r0, r1, r2}, phi[3] = {p0, p1, p2};
   const double th2 = phi[0] * phi[0] + phi[1] * phi[1] + phi[2] * phi[2];
   const double th = sqrt(th2);
   double A, B, C;
@@ -190,9 +189,9 @@ __device__ __forceinline__ void eliminate_block(double (&d)[6][6], double (&x)[6
   }
 }
 
-// S.A holds the lower triangle of H + mu I and -b; all threads of the block.  Solution in y (global, n); false (in
-// every thread) when a pivot is not positive.
-__device__ __forceinline__ bool solve_small(int n, SmallShared& S, double* __restrict__ y) {
+// S.A holds the lower triangle of H and -b; all threads of the block.  Solution in row n; false (in every thread) when
+// a pivot is not positive.
+__device__ __forceinline__ bool solve_small(int n, double mu, SmallShared& S) {
   const int t = threadIdx.x, tx = t & 31, ty = t >> 5, ld = n + 1;
   double* A = S.A;
   if (t == 0) S.bad = 0;
@@ -207,7 +206,7 @@ __device__ __forceinline__ bool solve_small(int n, SmallShared& S, double* __res
 #pragma unroll
       for (int r = 0; r < 6; ++r)
 #pragma unroll
-        for (int c = 0; c <= r; ++c) d[r][c] = A[(p + r) * ld + p + c];
+        for (int c = 0; c <= r; ++c) d[r][c] = A[(p + r) * ld + p + c] + (r == c ? mu : 0.0);
 #pragma unroll
       for (int c = 0; c < 6; ++c) x[c] = A[i * ld + p + c];
       eliminate_block(d, x, rd, ok);
@@ -249,8 +248,8 @@ __device__ __forceinline__ bool solve_small(int n, SmallShared& S, double* __res
       u0 = fma(-l0, xj, u0);
       u1 = fma(-l1, xj, u1);
     }
-    if (t < n) y[t] = u0;
-    if (t + 64 < n) y[t + 64] = u1;
+    if (t < n) A[n * ld + t] = u0;
+    if (t + 64 < n) A[n * ld + t + 64] = u1;
   }
   __syncthreads();
   return true;
@@ -731,11 +730,12 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_update(SolveArgs a) {
         if (n <= kLdsSystem) {
           for (int idx = t; idx < n * n; idx += kSolveThreads) {
             const int i = idx / n, k = idx - i * n;
-            if (k <= i) sh.small.A[i * (n + 1) + k] = H[idx] + (i == k ? mu : 0.0);
+            if (k <= i) sh.small.A[i * (n + 1) + k] = H[idx];
           }
           for (int i = t; i < n; i += kSolveThreads) sh.small.A[n * (n + 1) + i] = -a.b[S.v_off + i];
-          moved = solve_small(n, sh.small, a.delta + S.v_off);
+          moved = solve_small(n, mu, sh.small);
           if (!moved && t == 0) st[1] = -4;
+          if (moved && t < n) a.delta[S.v_off + t] = sh.small.A[n * (n + 1) + t];
         } else {
           solve_blocked(S, a, mu, sh.blocked.buf, st + 1, sh.blocked.zflags);
           __syncthreads();
@@ -746,8 +746,10 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_update(SolveArgs a) {
     __syncthreads();
     if (moved) {
       const double* y = a.delta + S.v_off;
-      for (int k = t; k < n / 6; k += kSolveThreads)
-        right_update(a.poses + 12 * (S.slot0 + frame_of_reduced(k, S.fixed)), y + 6 * k);
+      for (int k = t; k < n / 6; k += kSolveThreads) {
+        const double* xi = y + 6 * k;
+        right_update(a.poses + 12 * (S.slot0 + frame_of_reduced(k, S.fixed)), xi[0], xi[1], xi[2], xi[3], xi[4], xi[5]);
+      }
     }
   }
   __syncthreads();
@@ -760,12 +762,13 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_update(SolveArgs a) {
 // transforms.  The same operations in the same order as k_edge_reduce, k_assemble, k_loss_only,
 // k_solve_update and k_edge_setup, which a large set needs more than one workgroup for: launches and the gaps
 // between them are most of a small iteration (2 frames x 5,000 points: 57 us an iteration, now
-// 36, of which this kernel 12.4; 8 frames and 28 edges of 2,000 points: 17 us).
+// 28, of which this kernel 11.3; 8 frames and 28 edges of 2,000 points: 15).  One chain of reads after another,
+// and its code, 15 KB, is fetched anew every iteration; with the loss, H and b read one after the other by the
+// same wavefront the two took 12.4 and 17.
 template <int MODE, int STEP, typename TT>
 __global__ __launch_bounds__(kSolveThreads) void k_step(SolveArgs a, StepArgs u) {
   __shared__ SmallShared sh;
   __shared__ EdgeSums<TT> sums[kSolveThreads / 64];
-  __shared__ double red[kSolveThreads / 64];
   const ProbSys S = a.sys[blockIdx.x];
   const int t = threadIdx.x, w = t >> 6;
   if (blockIdx.x == 0 && t == 0 && u.n_items) *u.n_items = 0u;  // of the next evaluation's sweep
@@ -774,11 +777,12 @@ __global__ __launch_bounds__(kSolveThreads) void k_step(SolveArgs a, StepArgs u)
       reduce_edge<TT>(u.partial, u.edges[e], u.xf[e], MODE, sums[w], u.edge_out + (int64_t)e * kEdgeVals);
   __threadfence_block();
   __syncthreads();
-  if (w == 0) record_loss(a, S);
-  const int n = S.n;
+  // the loss, H and b by different wavefronts: each is a chain of dependent reads
+  const int n = S.n, back = kSolveThreads - 1 - t;
+  if (w == 8) record_loss(a, S);
   if constexpr (STEP == STEP_SYSTEM) {
     for (int idx = t; idx < n * n; idx += kSolveThreads) a.H[S.h_off + idx] = h_entry(a, S, idx / n, idx % n);
-    for (int i = t; i < n; i += kSolveThreads) a.b[S.v_off + i] = b_entry(a, S, i);
+    if (back < n) a.b[S.v_off + back] = b_entry(a, S, back);
   }
   if constexpr (STEP == STEP_SOLVE) {
     int32_t* st = a.state + S.state_off;
@@ -786,22 +790,26 @@ __global__ __launch_bounds__(kSolveThreads) void k_step(SolveArgs a, StepArgs u)
     const bool run = iter < S.n_iter && st[1] == 0 && n > 0;
     if (run) {
       double* A = sh.A;
-      for (int idx = t; idx < n * n; idx += kSolveThreads) {
-        const int i = idx / n, k = idx - i * n;
-        if (k <= i) A[i * (n + 1) + k] = h_entry(a, S, i, k);
+      for (int e = t; e < n * (n + 1) / 2; e += kSolveThreads) {  // the lower triangle
+        int i = (int)((sqrtf(8.0f * (float)e + 1.0f) - 1.0f) * 0.5f);
+        i += (i + 1) * (i + 2) / 2 <= e ? 1 : 0;
+        i -= i * (i + 1) / 2 > e ? 1 : 0;
+        const int k = e - i * (i + 1) / 2;
+        A[i * (n + 1) + k] = h_entry(a, S, i, k);
       }
-      for (int i = t; i < n; i += kSolveThreads) A[n * (n + 1) + i] = -b_entry(a, S, i);
+      if (back < n) A[n * (n + 1) + back] = -b_entry(a, S, back);
       __syncthreads();
-      double tr = 0.0;
-      for (int i = t; i < n; i += kSolveThreads) tr += A[i * (n + 1) + i];
-      tr = block_sum(tr, red);
+      // every wavefront for itself, in block_sum's order
+      const int lane = t & 63;
+      double tr = wave_sum(lane < n ? A[lane * (n + 2)] : 0.0);
+      if (n > 64) tr += wave_sum(lane + 64 < n ? A[(lane + 64) * (n + 2)] : 0.0);
       if (tr > 0.0) {  // otherwise no pair touches a free frame: nothing moves
-        const double mu = S.damping_rel * tr / n;
-        for (int i = t; i < n; i += kSolveThreads) A[i * (n + 1) + i] += mu;
-        if (solve_small(n, sh, a.delta + S.v_off)) {
-          const double* y = a.delta + S.v_off;
-          for (int k = t; k < n / 6; k += kSolveThreads)
-            right_update(a.poses + 12 * (S.slot0 + frame_of_reduced(k, S.fixed)), y + 6 * k);
+        if (solve_small(n, S.damping_rel * tr / n, sh)) {
+          for (int k = t; k < n / 6; k += kSolveThreads) {
+            const int at = n * (n + 1) + 6 * k;
+            right_update(a.poses + 12 * (S.slot0 + frame_of_reduced(k, S.fixed)), A[at], A[at + 1], A[at + 2],
+                         A[at + 3], A[at + 4], A[at + 5]);
+          }
         } else if (t == 0) {
           st[1] = -4;
         }
