@@ -163,12 +163,15 @@ SetLayout::~SetLayout() {
 // ---------------------------------------------------------------- Engine
 
 Engine::Engine(int dev, hipStream_t stream, int mp) : device(dev), st(stream), moment_path(mp) {
-  // results of the engine's stream, and of its build stream
-  RK_HIP(hipHostMalloc(reinterpret_cast<void**>(&pinned_), 2 * kGetBytes, hipHostMallocDefault));
+  // results of the engine's stream, and of its build stream; without it (the allocation is refused) they are copied
+  if (hipHostMalloc(reinterpret_cast<void**>(&pinned_), 2 * kGetBytes, hipHostMallocDefault) != hipSuccess) {
+    pinned_ = nullptr;
+    (void)hipGetLastError();
+  }
 }
 
 Engine::~Engine() {
-  (void)hipHostFree(pinned_);
+  if (pinned_) (void)hipHostFree(pinned_);
   for (auto& s : stages)
     for (auto& pr : s.pending) {
       (void)hipEventDestroy(pr.first);
@@ -260,7 +263,7 @@ void Engine::receive(const std::vector<Download>& dn, hipStream_t s) {
     in.push_back(d);
     total += d.item * d.count;
   }
-  if (in.empty() || total > kGetBytes || (int)in.size() > kMaxPieces) {
+  if (!pinned_ || in.empty() || total > kGetBytes || (int)in.size() > kMaxPieces) {
     for (const Download& d : in) {
       if (d.count == 1) RK_HIP(hipMemcpyAsync(d.dst, d.src, d.item, hipMemcpyDeviceToHost, s));
       else

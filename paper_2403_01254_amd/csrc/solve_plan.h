@@ -57,32 +57,31 @@ inline std::vector<uint16_t> sparse_plan(int n, std::vector<uint8_t> adj) {
   if (n < 1 || n > kSparseMaxFrames) return plan;
   const size_t max_blocks = kSparseLds / (36 * sizeof(double));
   // greedy minimum degree (ties: the earlier frame); eliminating a frame joins its remaining neighbours
-  std::vector<int> order, position(n, -1);
+  std::vector<int> order, position(n, -1), degree(n, 0);
+  auto count = [&](int f) {
+    degree[f] = 0;
+    for (int g = 0; g < n; ++g) degree[f] += position[g] < 0 && g != f && adj[(size_t)f * n + g];
+  };
+  for (int f = 0; f < n; ++f) count(f);
   std::vector<std::vector<int>> below(n);  // frames of column p's off-diagonal blocks
   size_t blocks = n, updates = 0;
   size_t rows_max = 0;
   for (int p = 0; p < n; ++p) {
-    int best = -1, best_degree = 0;
-    for (int f = 0; f < n; ++f) {
-      if (position[f] >= 0) continue;
-      int degree = 0;
-      for (int g = 0; g < n; ++g) degree += position[g] < 0 && g != f && adj[(size_t)f * n + g];
-      if (best < 0 || degree < best_degree) {
-        best = f;
-        best_degree = degree;
-      }
-    }
+    int best = -1;
+    for (int f = 0; f < n; ++f)
+      if (position[f] < 0 && (best < 0 || degree[f] < degree[best])) best = f;
     position[best] = p;
     order.push_back(best);
     for (int g = 0; g < n; ++g)
       if (position[g] < 0 && adj[(size_t)best * n + g]) below[p].push_back(g);
-    for (int g : below[p])
-      for (int h : below[p])
-        if (g != h) adj[(size_t)g * n + h] = 1;
     blocks += below[p].size();
     updates += below[p].size() * (below[p].size() + 1) / 2;
     rows_max = std::max(rows_max, below[p].size());
     if (blocks > max_blocks || updates > 60000) return plan;
+    for (int g : below[p])
+      for (int h : below[p])
+        if (g != h) adj[(size_t)g * n + h] = 1;
+    for (int g : below[p]) count(g);
   }
   const int n_off = (int)blocks - n, n_upd = (int)updates;
   const size_t words = (size_t)sparse_words(n, n_off, n_upd);
