@@ -78,17 +78,18 @@ __device__ __forceinline__ T skew_at(const T* a, int i, int j) {
   return (j - i + 3) % 3 == 1 ? -v : v;
 }
 
-// Value k of an edge (F, b_m, b_n, H_mm, H_nn, H_mn, pairs, sum w r^2; kEdgeVals) from its sums T.
+// Value k of an edge (F, b_m, b_n, H_mm, H_nn, H_mn, pairs, sum w r^2; kEdgeVals) from its sums T.  The fused
+// multiply-adds are written out: a solve in a direction that the view leaves nearly free multiplies the last bits of H
+// and b by 1e8, so their rounding is part of the results and is not left to the compiler.
 template <typename TT>
 __device__ __forceinline__ double edge_value(const TT* T, const EdgeXf& X, double n_pairs, int k) {
   auto Rmn = [&](int r, int c) { return (TT)X.R[3 * c + r]; };
   const TT A = T[kStA];
   const TT* B = T + kStB;
+  // row r of R_mn times a vector
+  auto Rmn_dot = [&](int r, TT v0, TT v1, TT v2) { return fma(Rmn(r, 2), v2, fma(Rmn(r, 0), v0, Rmn(r, 1) * v1)); };
   if (k == 0) return (double)T[kStF];
-  if (k < 4) {
-    const int r = k - 1;
-    return (double)(Rmn(r, 0) * B[0] + Rmn(r, 1) * B[1] + Rmn(r, 2) * B[2]);
-  }
+  if (k < 4) return (double)Rmn_dot(k - 1, B[0], B[1], B[2]);
   if (k < 7) return (double)T[kStXBm + k - 4];
   if (k < 10) return (double)-B[k - 7];
   if (k < 13) return (double)-T[kStQB + k - 10];
@@ -110,13 +111,10 @@ __device__ __forceinline__ double edge_value(const TT* T, const EdgeXf& X, doubl
   // H_mn: [[-A R_mn, R_mn [S]], [-[A x] R_mn, sum [x] R_mn [S]]]
   const int r = (k - 55) / 6, c = (k - 55) % 6;
   if (r < 3 && c < 3) return (double)(-A * Rmn(r, c));
+  if (r < 3) return (double)Rmn_dot(r, skew_at(S, 0, c - 3), skew_at(S, 1, c - 3), skew_at(S, 2, c - 3));
   TT v = 0;
-  if (r < 3) {
-    for (int a = 0; a < 3; ++a) v += Rmn(r, a) * skew_at(S, a, c - 3);
-    return (double)v;
-  }
   if (c < 3) {
-    for (int a = 0; a < 3; ++a) v += skew_at(T + kStAx, r - 3, a) * Rmn(a, c);
+    for (int a = 0; a < 3; ++a) v = fma(skew_at(T + kStAx, r - 3, a), Rmn(a, c), v);
     return (double)-v;
   }
   // sum_p [x_p] R_mn [S_p]: the sums of x_i S_j under the two cross products' signs
@@ -126,7 +124,7 @@ __device__ __forceinline__ double edge_value(const TT* T, const EdgeXf& X, doubl
       if (a == rr || b == cc) continue;
       const TT m = T[kStXS + 3 * (3 - rr - a) + (3 - b - cc)];
       const bool neg = ((a - rr + 3) % 3 == 1) != ((cc - b + 3) % 3 == 1);
-      v += (neg ? -m : m) * Rmn(a, b);
+      v = fma(neg ? -m : m, Rmn(a, b), v);
     }
   return (double)v;
 }
