@@ -152,6 +152,11 @@ __device__ inline double lane_value(double v, int lane) {
 // of the rows below each factor the 6 x 6 diagonal block for themselves (it is short, and a barrier less).  One
 // column per barrier and a separate forward solve took 0.7 us per unknown (n = 42: 32 us a solve; now the whole step
 // around it takes 17).
+//
+// The rounding is that of the elimination column by column: mu joins the diagonal before any update, an update takes
+// the later row divided by the pivot and the earlier one undivided, one fused multiply-add per column in their order,
+// and the reciprocals are correctly rounded.  A view that leaves a direction nearly free (a reduced H with eigenvalues
+// below mu) makes 1e-8 of pose out of another order's last bits, and other pair counts out of that.
 constexpr int kSolveThreads = 1024;
 constexpr int kLdsDoubles = kLdsSystem * (kLdsSystem + 1);  // shared buffer of both paths
 
@@ -161,11 +166,12 @@ struct SmallShared {
   int bad;                                        // a pivot was not positive
 };
 
-// 1 / d to within an ulp: the hardware estimate and two Newton steps, a third of a division's chain.  The ends of
-// the range, where the estimate or a step could leave it, divide.
+// 1 / d, correctly rounded: the hardware estimate, two Newton steps, and a last one from the exact residual, a division's
+// own chain without the scaling of its operands' exponents.  The ends of the range, where a step could leave it, divide.
 __device__ inline double reciprocal(double d) {
   if (!(d > 1e-290 && d < 1e290)) return 1.0 / d;
   double r = __builtin_amdgcn_rcp(d);
+  r = fma(fma(-d, r, 1.0), r, r);
   r = fma(fma(-d, r, 1.0), r, r);
   return fma(fma(-d, r, 1.0), r, r);
 }
@@ -206,7 +212,7 @@ __device__ __forceinline__ bool solve_small(int n, double mu, SmallShared& S) {
 #pragma unroll
       for (int r = 0; r < 6; ++r)
 #pragma unroll
-        for (int c = 0; c <= r; ++c) d[r][c] = A[(p + r) * ld + p + c] + (r == c ? mu : 0.0);
+        for (int c = 0; c <= r; ++c) d[r][c] = A[(p + r) * ld + p + c] + (r == c && p == 0 ? mu : 0.0);
 #pragma unroll
       for (int c = 0; c < 6; ++c) x[c] = A[i * ld + p + c];
       eliminate_block(d, x, rd, ok);
@@ -228,9 +234,9 @@ __device__ __forceinline__ bool solve_small(int n, double mu, SmallShared& S) {
     // trailing rows and columns, row n included; the block's L moves to its place
     for (int i = m0 + ty; i <= n; i += 32)
       for (int k = m0 + tx; k <= min(i, n - 1); k += 32) {
-        double v = A[i * ld + k];
+        double v = A[i * ld + k] + (i == k && p == 0 ? mu : 0.0);
 #pragma unroll
-        for (int c = 0; c < 6; ++c) v = fma(-S.t[c][i], A[k * ld + p + c], v);
+        for (int c = 0; c < 6; ++c) v = fma(-A[i * ld + p + c], S.t[c][k], v);
         A[i * ld + k] = v;
       }
     if (t < 36) {
