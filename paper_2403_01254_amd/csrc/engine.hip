@@ -1146,10 +1146,9 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   need(sc_->b, v_total, "b");
   need(sc_->delta, v_total, "delta");
   // Spread passes of dense features are split where a box can have that many rows; up to one item per pass of the
-  // set (passes beyond that are walked whole).  The allocation-free scratch has no room for the list.
-  uint32_t item_cap = 0;
-  if (!arena_ && many_rows && gcount[0] > 0) {
-    item_cap = (uint32_t)std::min<int64_t>(gcount[0] + 64, INT_MAX - gcount[0]);
+  // set (max_items; passes beyond that are walked whole).  The allocation-free scratch has no room for the list.
+  const uint32_t item_cap = !arena_ && many_rows ? max_items(gcount[0]) : 0;
+  if (item_cap > 0) {
     need(sc_->items, item_cap, "items");
     need(sc_->n_items, 1, "n_items");
     need(sc_->split, (size_t)gcount[0], "split");

@@ -297,6 +297,13 @@ constexpr int kManyRows = 512;
 // batches) are walked faster than they are split: 5 x 12,345 fp8 102 from 256 rows on, 111 from 128.
 constexpr int kSplitRows = 256;
 inline float split_factor(int64_t n_pass) { return n_pass <= 16384 ? 2.f : 4.f; }
+// Room for the items of a launch of n_pass passes.  The sweep's grid holds a workgroup for every pass and every item
+// that could be listed, so the list of a large set, which is bound by its work and not by its longest passes, ends at
+// 65,536; and it leaves the grid below 2^26 workgroups of 64, the most that a launch takes.
+inline uint32_t max_items(int64_t n_pass) {
+  const int64_t room = (1ll << 26) - 1 - n_pass, most = n_pass + 64 < 65536 ? n_pass + 64 : 65536;
+  return n_pass <= 0 || room <= 0 ? 0u : (uint32_t)(most < room ? most : room);
+}
 
 struct PairArgs {
   const float4* pts;

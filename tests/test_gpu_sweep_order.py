@@ -36,3 +36,20 @@ def test_items_and_passes(n, spread):
 @pytest.mark.parametrize("feat", ["bf16", "fp8"])
 def test_items_of_many_edges(feat):
     check((9001, 6000, 4000), [(0, 1), (1, 0), (0, 2), (2, 0), (1, 2), (2, 1), (0, 1)], "half", feat)
+
+
+def test_more_items_than_the_list_ends_at():
+    """70,032 passes, nearly all of them spread: a list of 65,536 items, the other passes whole."""
+    from paper_2403_01254_amd import rkhsba
+    rng = np.random.default_rng(7)
+    x = rng.uniform(0.0, 40.0, size=(31120, 3))
+    pts = [(x[:n] + rng.uniform(-0.1, 0.1, size=(n, 3))).astype(np.float32) for n in (31120, 4000)]
+    feats = [rng.uniform(0.1, 1.0, size=(len(p), 4)).astype(np.float32) for p in pts]
+    poses = np.stack([ident(), ident()])
+    with rkhsba.Context(ell=0.1, cell_subdiv=3, pass_points=16) as ctx:
+        ctx.build_neighbors(pts, feats, "dense")
+        _, one, n_one = ctx.eval_loss_noalloc(poses, [(0, 1)])
+        for E in (1, 36):
+            _, Fe, n = ctx.eval_loss(poses, [(0, 1)] * E)
+            assert n == E * n_one and n > 0
+            np.testing.assert_array_equal(Fe, np.repeat(one, E))
