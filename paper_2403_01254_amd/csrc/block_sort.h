@@ -1,5 +1,9 @@
 // Stable LSD radix sort inside one workgroup, and the wave and block scans that it and the tiled radix sort
 // share.
+//
+// Here and in the other sources, helpers that take pointers or references to LDS are inlined by force: in a function
+// of its own, LDS is reached through generic pointers, and the constant part of an index can be folded into the
+// instruction so that the base lies before the LDS aperture, which faults.
 #pragma once
 
 #include "rkhsba_device.h"
@@ -29,7 +33,7 @@ __device__ inline uint32_t wave_inclusive_scan(uint32_t v) {
 
 // Exclusive scan of the 256 digit totals held by threads 0..255 (four wavefronts); every thread of the block
 // takes part in the barrier.  wtot: 4 words of LDS.
-__device__ inline uint32_t digit_exclusive_scan(uint32_t v, uint32_t* wtot) {
+__device__ __forceinline__ uint32_t digit_exclusive_scan(uint32_t v, uint32_t* wtot) {
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const uint32_t incl = wave_inclusive_scan(v);
   if (t < 256 && lane == 63) wtot[w] = incl;
@@ -45,7 +49,7 @@ __device__ inline uint32_t digit_exclusive_scan(uint32_t v, uint32_t* wtot) {
 // cnt[256] (LDS, this wavefront's own) ends with the wavefront's digit counts.  Lanes sharing a digit find each
 // other with one ballot per digit bit, so a round costs no LDS atomics and no barrier.
 template <int IPT>
-__device__ inline void wave_digit_ranks(const uint32_t (&digit)[IPT], const bool (&valid)[IPT], uint32_t* cnt,
+__device__ __forceinline__ void wave_digit_ranks(const uint32_t (&digit)[IPT], const bool (&valid)[IPT], uint32_t* cnt,
                                         uint32_t (&rank)[IPT]) {
   const int lane = threadIdx.x & 63;
   const uint64_t lt = (1ull << lane) - 1ull;
@@ -87,7 +91,7 @@ struct BlockSort {
     uint32_t dig[256];
     uint32_t wtot[4];
   };
-  __device__ static void sort(uint32_t (&key)[IPT], int count, int bits, Shared& S) {
+  __device__ static __forceinline__ void sort(uint32_t (&key)[IPT], int count, int bits, Shared& S) {
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int base = w * 64 * IPT + lane;
     uint32_t idx[IPT];

@@ -137,9 +137,7 @@ struct EdgeSums {  // LDS of one wavefront
 
 // One wavefront: the edge's sums over its finalisation blocks in block order, expanded into out[kEdgeVals].  The
 // values are spread over the lanes: one thread wrote all 93 of them before, 10 us of serial FP64 for 28 edges that
-// now take 3.  Inlined by force, with its helpers: in a function of its own, LDS is reached through generic pointers,
-// and the constant part of an index can be folded into the instruction so that the base lies before the LDS aperture,
-// which faults.
+// now take 3.  (Inlined by force, with its helpers, as all that take LDS: block_sort.h.)
 template <typename TT>
 __device__ __forceinline__ void reduce_edge(const double* __restrict__ partial, const EdgeInfo& ed, const EdgeXf& X,
                                             int mode, EdgeSums<TT>& sh, double* __restrict__ out) {

@@ -125,7 +125,7 @@ __device__ __noinline__ void right_update(double* T, double r0, double r1, doubl
   }
 }
 
-__device__ double block_sum(double v, double* sh) {
+__device__ __forceinline__ double block_sum(double v, double* sh) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   v = wave_sum(v);
   __syncthreads();
@@ -268,7 +268,7 @@ __device__ __forceinline__ bool solve_small(int n, double mu, SmallShared& S) {
 // with D = diag(d)), and rd[j] = 1 / d_j.  One barrier per step; threads form a
 // 32 x 32 grid over the trailing rows and columns.  Returns false (in every
 // thread) when a pivot is not positive.
-__device__ bool eliminate_lds(double* A, int n, int ld, double* rd) {
+__device__ __forceinline__ bool eliminate_lds(double* A, int n, int ld, double* rd) {
   const int t = threadIdx.x, tx = t & 31, ty = t >> 5;
   for (int j = 0; j < n; ++j) {
     const double d = A[j * ld + j];
@@ -513,7 +513,7 @@ __device__ __forceinline__ void solve_blocked(const ProbSys& S, const SolveArgs&
   __syncthreads();
   // L y = -b: each diagonal block staged in LDS (with the reciprocals of its diagonal) and solved in
   // wavefront 0, then the rows below updated by all threads
-  auto stage_diag = [&](int kb, int nb) {
+  auto stage_diag = [&](int kb, int nb) __attribute__((always_inline)) {
     for (int idx = t; idx < nb * nb; idx += kSolveThreads) {
       const int i = idx / nb, k = idx - i * nb;
       if (k <= i) Dg[i * (NB + 1) + k] = H[(int64_t)(kb + i) * n + kb + k];

@@ -36,7 +36,7 @@ namespace {
 // source points: D[cand 4(l/16)+r][source l%16] += F_cand[., 4k + l/16] *
 // F_src[4k + l/16][.], accumulated over the DP/4 slices of 4 dimensions.
 template <int DP, int FS>
-__device__ inline floatx4 tile_products(const float* __restrict__ tfeat, int s, int g, int sub,
+__device__ __forceinline__ floatx4 tile_products(const float* __restrict__ tfeat, int s, int g, int sub,
                                         const float (&fsrc)[DP / 4]) {
   floatx4 acc = {0.f, 0.f, 0.f, 0.f};
   const float* arow = tfeat + (16 * sub + s) * FS + g * (DP / 4);  // (stored column by column, feat_slot)
@@ -57,7 +57,7 @@ __device__ inline floatx4 tile_products(const float* __restrict__ tfeat, int s, 
 typedef short shortx8 __attribute__((ext_vector_type(8)));
 
 template <int FEAT, int DP, int RB>
-__device__ inline floatx4 tile_products_lp(const uint8_t* __restrict__ tl, int s, int g, int sub,
+__device__ __forceinline__ floatx4 tile_products_lp(const uint8_t* __restrict__ tl, int s, int g, int sub,
                                            const uint64_t (&src)[FEAT == FEAT_BF16 ? DP / 16 : DP / 32]) {
   floatx4 acc = {0.f, 0.f, 0.f, 0.f};
   const uint8_t* row = tl + (16 * sub + s) * RB;
