@@ -579,12 +579,19 @@ __device__ __forceinline__ void solve_blocked(const ProbSys& S, const SolveArgs&
 // the system assembled from the edges' values straight into them.  A chain of latencies: 63 steps of 2 us and their
 // way back for 64 LiDAR frames with 6 edges each, 0.18 ms, where the blocked dense elimination took 0.52 (12 panels
 // of 32 columns through global memory) and the assembly of H before it 0.01.
+//
+// Its order is the plan's, so its last bits are not the dense elimination's.  Where the system leaves a direction nearly
+// free, they would become poses and pair counts: a pivot that elimination leaves below kWellPosed of its diagonal entry
+// sends the system to the dense elimination.  LiDAR maps of 23 to 64 frames have smallest pivots of 3e-3 and more of
+// their diagonal (poses then agree to 1e-13), depth frames in front of one wall 3e-6 and less.
+constexpr double kWellPosed = 1e-3;
+
 struct SparseShared {
   double d[kSparseLds / sizeof(double)];
 };
 
-// Solution in y (global, n, in frame order).  0: moved; 1: no pair touches a free frame; -4: a pivot is not positive
-// (the same in every thread).
+// Solution in y (global, n, in frame order).  0: moved; 1: no pair touches a free frame; -1: a pivot is too small, for the
+// dense elimination to look at (the same in every thread).
 __device__ __forceinline__ int solve_sparse(const SolveArgs& a, const ProbSys& S, SparseShared& sh, double* __restrict__ red,
                             int* __restrict__ bad, double* __restrict__ y) {
   const int t = threadIdx.x;
@@ -601,7 +608,8 @@ __device__ __forceinline__ int solve_sparse(const SolveArgs& a, const ProbSys& S
   const int o_order = kSparseHeader, o_col = o_order + nf, o_upd = o_col + nf + 1, o_row = o_upd + nf + 1;
   const int o_cols = o_row + n_off, o_list = o_cols + n_off;
   double* rhs = L + 36 * (nf + n_off);
-  double* T = rhs + n;                          // a column's rows before the division by the pivots; last: the right side
+  double* diag = rhs + n;                       // the diagonal before the elimination
+  double* T = diag + n;                         // a column's rows before the division by the pivots; last: the right side
   double* dl = T + 6 * (6 * (int)local[3] + 1);  // the diagonal block's L
   double tr = 0.0;
   for (int e = t; e < 36 * (nf + n_off); e += kSolveThreads) {
@@ -615,7 +623,10 @@ __device__ __forceinline__ int solve_sparse(const SolveArgs& a, const ProbSys& S
   tr = block_sum(tr, red);
   if (!(tr > 0.0)) return 1;
   const double mu = S.damping_rel * tr / n;
-  for (int i = t; i < n; i += kSolveThreads) L[36 * (i / 6) + 7 * (i % 6)] += mu;
+  for (int i = t; i < n; i += kSolveThreads) {
+    diag[i] = L[36 * (i / 6) + 7 * (i % 6)];
+    L[36 * (i / 6) + 7 * (i % 6)] += mu;
+  }
   __syncthreads();
   for (int p = 0; p < nf; ++p) {
     const int c0 = local[o_col + p], rows = local[o_col + p + 1] - c0;
@@ -630,7 +641,6 @@ __device__ __forceinline__ int solve_sparse(const SolveArgs& a, const ProbSys& S
 #pragma unroll
       for (int c = 0; c < 6; ++c) x[c] = L[at + c];
       eliminate_block(d, x, rd, ok);
-      if (!ok) *bad = 1;
 #pragma unroll
       for (int c = 0; c < 6; ++c) {
         T[6 * t + c] = x[c];
@@ -638,13 +648,16 @@ __device__ __forceinline__ int solve_sparse(const SolveArgs& a, const ProbSys& S
       }
       if (t == 6 * rows) {
 #pragma unroll
+        for (int j = 0; j < 6; ++j) ok = ok && d[j][j] > kWellPosed * diag[6 * p + j];
+        if (!ok) *bad = 1;
+#pragma unroll
         for (int r = 1; r < 6; ++r)
 #pragma unroll
           for (int c = 0; c < r; ++c) dl[r * (r - 1) / 2 + c] = d[r][c] * rd[c];
       }
     }
     __syncthreads();
-    if (*bad) return -4;
+    if (*bad) return -1;
     const int u0 = local[o_upd + p], n_entries = 36 * (local[o_upd + p + 1] - u0);
     for (int e = t; e < n_entries + 6 * rows; e += kSolveThreads) {
       if (e < n_entries) {
@@ -721,12 +734,20 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve_update(SolveArgs a) {
   __syncthreads();
   if (run) {
     const int n = S.n, t = threadIdx.x;
-    bool moved = false;
-    if (S.plan0 >= 0) {
+    bool moved = false, dense = S.plan0 < 0;
+    if (!dense) {
       const int e = solve_sparse(a, S, sh.sparse, red, &bad, a.delta + S.v_off);
-      if (e == -4 && t == 0) st[1] = -4;
       moved = e == 0;
-    } else {
+      dense = e < 0;
+      if (dense) {  // (the lower triangle is what the elimination reads)
+        for (int i = t >> 6; i < n; i += kSolveThreads / 64)
+          for (int k = t & 63; k <= i; k += 64) a.H[S.h_off + (int64_t)i * n + k] = h_entry(a, S, i, k);
+        for (int i = t; i < n; i += kSolveThreads) a.b[S.v_off + i] = b_entry(a, S, i);
+        __threadfence_block();
+        __syncthreads();
+      }
+    }
+    if (dense) {
       const double* H = a.H + S.h_off;
       double tr = 0.0;
       for (int i = t; i < n; i += kSolveThreads) tr += H[(int64_t)i * n + i];

@@ -45,10 +45,10 @@ RKHSBA_HD inline SparsePlanView sparse_view(const uint16_t* w) {
 RKHSBA_HD inline int sparse_words(int n_frames, int n_off, int n_upd) {
   return kSparseHeader + 3 * n_frames + 2 + 2 * n_off + 3 * n_upd;
 }
-// LDS bytes: the doubles (blocks; right side; products of a column's rows and of the right side; a diagonal block's L)
-// and the plan.
+// LDS bytes: the doubles (blocks; right side; the system's diagonal; products of a column's rows and of the right side;
+// a diagonal block's L) and the plan.
 RKHSBA_HD inline size_t sparse_doubles(int n_frames, int n_off, int rows_max) {
-  return 36 * (size_t)(n_frames + n_off) + 6 * (size_t)n_frames + 6 * (size_t)(6 * rows_max + 1) + 16;
+  return 36 * (size_t)(n_frames + n_off) + 12 * (size_t)n_frames + 6 * (size_t)(6 * rows_max + 1) + 16;
 }
 
 // The plan of n frames with the given adjacency (n x n, symmetric), or nothing where it would not fit.

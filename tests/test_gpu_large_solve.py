@@ -1,0 +1,83 @@
+"""Gauss-Newton steps of graphs of more than 128 unknowns by the block-sparse elimination and by the dense one that it
+hands nearly free directions to; which graphs have a plan (solve_plan.h) is asked on the host."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle
+from helpers import ROOT
+
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("oracle_lib")]
+
+MAIN = r"""
+#include "solve_plan.h"
+#include <cstdio>
+int main() {
+  int n, E;
+  if (std::scanf("%d %d", &n, &E) != 2) return 1;
+  std::vector<uint8_t> adj((size_t)n * n, 0);
+  for (int k = 0, a, b; k < E; ++k) {
+    if (std::scanf("%d %d", &a, &b) != 2) return 1;
+    if (a >= 0 && b >= 0) adj[(size_t)a * n + b] = adj[(size_t)b * n + a] = 1;
+  }
+  std::printf("%zu\n", n > rkhsba::kSparseMaxFrames ? (size_t)0 : rkhsba::sparse_plan(n, adj).size());
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def has_plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "main.cpp").write_text(MAIN)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_2403_01254_amd", "csrc"),
+                    str(d / "main.cpp"), "-o", str(d / "main")], check=True)
+
+    def ask(K, edges):  # frame 0 fixed
+        text = f"{K - 1} {len(edges)}\n" + "\n".join(f"{m - 1} {n - 1}" for m, n in edges)
+        return int(subprocess.run([str(d / "main")], input=text, check=True, capture_output=True, text=True).stdout) > 0
+
+    return ask
+
+
+def near(K, reach):
+    return [(k, k + d) for k in range(K) for d in range(1, reach + 1) if k + d < K]
+
+
+@pytest.mark.parametrize("line", [True, False])
+@pytest.mark.parametrize("K", [32, 48])
+def test_nearly_free_directions_go_to_the_dense_elimination(K, line, has_plan):
+    """A chain, and the same chain with edges between frames too far apart for a pair: they add exact zeros to the same
+    H and b, and take the plan away.  Clouds along one line leave the rotation about it nearly free; there both
+    eliminations are the dense one, and poses and pair counts the same bits.  Well-posed chains keep their plan, and
+    their poses agree to rounding."""
+    from paper_2403_01254_amd import rkhsba
+    rng = np.random.default_rng(K)
+    chain = near(K, 2)
+    far = [(m, n) for m in range(K) for n in range(m + 5, K)]
+    assert has_plan(K, chain) and not has_plan(K, chain + far)
+    pts = []
+    for k in range(K):
+        s = rng.uniform(0.5 * k, 0.5 * k + 1.2, size=40)
+        if line:
+            pts.append(np.outer(s, [0.48, 0.6, 0.64]) + rng.normal(scale=3e-5, size=(40, 3)))
+        else:
+            pts.append(np.c_[s, rng.uniform(0.0, 0.4, size=(40, 2))])
+    pts = [p.astype(np.float32) for p in pts]
+    feats = [rng.uniform(0.1, 1.0, size=(40, 3)).astype(np.float32) for _ in range(K)]
+    poses = np.stack([oracle.se3_exp(np.r_[rng.normal(scale=0.01, size=3), np.zeros(3)]) for _ in range(K)])
+    with rkhsba.Context(ell=0.15) as ctx:
+        ctx.build_neighbors(pts, feats, "dense")
+        Hc, bc, Fc, nc = ctx.accumulate_normal_eqs(poses, chain)
+        Hf, bf, Ff, nf = ctx.accumulate_normal_eqs(poses, chain + far)
+        np.testing.assert_array_equal(Hc, Hf)
+        np.testing.assert_array_equal(bc, bf)
+        assert nc == nf > 0
+        a = ctx.gn_step(poses, chain, 3)
+        b = ctx.gn_step(poses, chain + far, 3)
+    if line:
+        np.testing.assert_array_equal(a[0], b[0])
+    else:
+        np.testing.assert_allclose(a[0], b[0], rtol=0.0, atol=1e-10)
+    np.testing.assert_array_equal(a[2], b[2])
