@@ -1,5 +1,6 @@
-"""Gauss-Newton steps of graphs of more than 128 unknowns by the block-sparse elimination and by the dense one that it
-hands nearly free directions to; which graphs have a plan (solve_plan.h) is asked on the host."""
+"""Gauss-Newton steps of graphs of more than 128 unknowns by each route: the block-sparse elimination, the dense one that
+it hands nearly free directions to, and the dense one for graphs without a plan (solve_plan.h, asked on the host): panels
+too tall for LDS (more than 513 unknowns), and smaller systems with whole 32-row chunks of zeros."""
 import os
 import subprocess
 
@@ -41,8 +42,44 @@ def has_plan(tmp_path_factory):
     return ask
 
 
+def clouds(rng, K, n, offset=0.0, size=0.4):
+    pts = [rng.uniform(0.0, size, size=(n, 3)) + [offset * k, 0.0, 0.0] for k in range(K)]
+    return [p.astype(np.float32) for p in pts], [rng.uniform(0.1, 1.0, size=(n, 3)).astype(np.float32) for _ in range(K)]
+
+
 def near(K, reach):
     return [(k, k + d) for k in range(K) for d in range(1, reach + 1) if k + d < K]
+
+
+def cliques(K):
+    """Two complete graphs, joined by one edge."""
+    h = K // 2
+    return ([(m, n) for m in range(h) for n in range(m + 1, h)] + [(h - 1, h)] +
+            [(m, n) for m in range(h, K) for n in range(m + 1, K)])
+
+
+@pytest.mark.parametrize("K,graph", [(200, "near"), (88, "all"), (80, "cliques"), (86, "cliques"), (24, "cliques")])
+def test_dense_step(K, graph, has_plan):
+    from paper_2403_01254_amd import rkhsba
+    rng = np.random.default_rng(K)
+    edges = near(K, 3) if graph == "near" else cliques(K) if graph == "cliques" else near(K, K)
+    assert has_plan(K, edges) == (K == 24)
+    pts, feats = clouds(rng, K, 12)
+    poses = np.stack([oracle.se3_exp(rng.normal(scale=0.02, size=6)) for _ in range(K)])
+    damping = 1e-2
+    with rkhsba.Context(ell=0.15, damping_rel=damping) as ctx:
+        ctx.build_neighbors(pts, feats, "dense")
+        H, b, _, _ = ctx.accumulate_normal_eqs(poses, edges)
+        got, _, _ = ctx.gn_step(poses, edges, 1)
+    H, b = H[6:, 6:], b[6:]
+    n = len(b)
+    delta = np.linalg.solve(H + damping * np.trace(H) / n * np.eye(n), -b)
+    # the condition number is at most n / damping + 1, the elimination's relative error some n eps times that
+    tol = 4.0 * n * n / damping * np.finfo(float).eps * np.linalg.norm(delta) + 1e-14
+    for k in range(1, K):
+        R, t, step = poses[k, :9].reshape(3, 3), poses[k, 9:], oracle.se3_exp(delta[6 * k - 6:6 * k])
+        np.testing.assert_allclose(got[k, :9].reshape(3, 3), R @ step[:9].reshape(3, 3), rtol=0.0, atol=tol)
+        np.testing.assert_allclose(got[k, 9:], R @ step[9:] + t, rtol=0.0, atol=tol)
 
 
 @pytest.mark.parametrize("line", [True, False])
