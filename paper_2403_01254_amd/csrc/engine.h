@@ -199,6 +199,9 @@ struct Problem {
   int64_t alias_slot0 = -1;
   double occupancy = 0.0;           // points per occupied cell of the problem's grid
   double occupancy_r = 0.0;         // points per occupied cell of edge r_c (0: not measured)
+  // the block-sparse elimination plan (empty: none) of the edge list and fixed frame it was last laid out with
+  std::vector<int32_t> plan_key;
+  std::vector<uint16_t> plan;
 };
 
 // One item of an evaluated set.

@@ -1033,18 +1033,25 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
         vec[n].push_back(e_glob * 2 + 1);
       }
     }
-    // systems too large for a dense triangle in LDS: a sparse plan, where its blocks fit
+    // systems too large for a dense triangle in LDS: a sparse plan, where its blocks fit.  It depends on the edges and
+    // the fixed frame alone and stays with the problem (64 frames take 0.05 ms to plan, 512 ten times that), while a set's
+    // layout is made anew whenever a problem joins or leaves it.
     S.plan0 = -1;
     if (S.n > kLdsSystem && it.n_iter > 0 && S.n / 6 <= kSparseMaxFrames) {
-      const int nf = S.n / 6;
-      auto frame = [&](int k) { return it.fixed >= 0 && k >= it.fixed ? k + 1 : k; };
-      std::vector<uint8_t> adj((size_t)nf * nf, 0);
-      for (int r = 0; r < nf; ++r)
-        for (int c = 0; c < nf; ++c) adj[(size_t)r * nf + c] = r != c && !blk[(size_t)frame(r) * K + frame(c)].empty();
-      const std::vector<uint16_t> plan = sparse_plan(nf, std::move(adj));
-      if (!plan.empty()) {
+      std::vector<int32_t> pkey(it.edges, it.edges + 2 * it.E);
+      pkey.push_back(it.fixed);
+      if (pkey != p->plan_key) {
+        const int nf = S.n / 6;
+        auto frame = [&](int k) { return it.fixed >= 0 && k >= it.fixed ? k + 1 : k; };
+        std::vector<uint8_t> adj((size_t)nf * nf, 0);
+        for (int r = 0; r < nf; ++r)
+          for (int c = 0; c < nf; ++c) adj[(size_t)r * nf + c] = r != c && !blk[(size_t)frame(r) * K + frame(c)].empty();
+        p->plan = sparse_plan(nf, std::move(adj));
+        p->plan_key = std::move(pkey);
+      }
+      if (!p->plan.empty()) {
         S.plan0 = (int32_t)plans.size();
-        plans.insert(plans.end(), plan.begin(), plan.end());
+        plans.insert(plans.end(), p->plan.begin(), p->plan.end());
       }
     }
     need_h = need_h || S.plan0 < 0;

@@ -118,3 +118,28 @@ def test_nearly_free_directions_go_to_the_dense_elimination(K, line, has_plan):
     else:
         np.testing.assert_allclose(a[0], b[0], rtol=0.0, atol=1e-10)
     np.testing.assert_array_equal(a[2], b[2])
+
+
+def test_plan_follows_the_edge_list(has_plan):
+    """One set of frames stepped with several edge lists in turn, with and without a plan: each as in a fresh context."""
+    from paper_2403_01254_amd import rkhsba
+    K = 40
+    rng = np.random.default_rng(0)
+    pts, feats = clouds(rng, K, 20)
+    poses = np.stack([oracle.se3_exp(rng.normal(scale=0.02, size=6)) for _ in range(K)])
+    lists = [near(K, 1), near(K, 3), near(K, K), near(K, 3)[::-1], [(n, m) for m, n in near(K, 1)]]
+    assert [has_plan(K, e) for e in lists] == [True, True, False, True, True]
+
+    def context():
+        ctx = rkhsba.Context(ell=0.15, damping_rel=1e-3)
+        ctx.build_neighbors(pts, feats, "dense")
+        return ctx
+
+    want = []
+    for e in lists:
+        with context() as ctx:
+            want.append(ctx.gn_step(poses, e, 2))
+    with context() as ctx:
+        for k in (0, 1, 2, 1, 3, 4, 0, 2, 4, 0):
+            for x, y in zip(ctx.gn_step(poses, lists[k], 2), want[k]):
+                np.testing.assert_array_equal(x, y)
