@@ -616,7 +616,7 @@ int Engine::build(ProbParams par_in, int K, const int64_t* n_points, const float
                               key_bits, k1_.p, v1_.p, hist_scratch_.p, in_tmp ? k1_.p : k2_.p, in_tmp ? v1_.p : v2_.p,
                               in_tmp ? k2_.p : k1_.p, in_tmp ? v2_.p : v1_.p, bst));
       RK_HIP(launch_radix_sort(k1_.p, v1_.p, k2_.p, v2_.p, hist_scratch_.p, d_tiles_.p, d_segs_.p, plan, key_bits, true,
-                               true, bst));
+                               bst));
       p->n_rows = std::max<int64_t>(rows_total, 1);
       p->rbase = rows_.alloc(p->n_rows, bst);
       RK_HIP(row_sizes_.reserve(rows_total));
@@ -1233,7 +1233,7 @@ void Engine::evaluate(SetLayout& lay, int mode, bool reuse_binning, int step, bo
                       lay.bin_bits, sc_->bk.p, sc_->bv.p, sc_->bhist.p, sorted == sc_->bv.p ? sc_->bv2.p : sc_->bv.p,
                       sorted, st));
     RK_HIP(launch_radix_sort(sc_->bk.p, sc_->bv.p, sc_->bk2.p, sc_->bv2.p, sc_->bhist.p, lay.d_etiles.p,
-                             lay.d_esegs.p, lay.plan, lay.bin_bits, true, false, st));
+                             lay.d_esegs.p, lay.plan, lay.bin_bits, false, st));
     sorted_v_ = sorted;
     lay.binned = true;
     lay.bin_gen = scratch_gen_;

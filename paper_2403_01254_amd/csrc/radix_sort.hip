@@ -179,12 +179,12 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge(const uint32_t* __restr
 
 hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp, uint32_t* hist,
                              const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan, int bits,
-                             bool hist0, bool keep_keys, hipStream_t st) {
+                             bool keep_keys, hipStream_t st) {
   if (plan.n_tiles <= 0) return hipSuccess;
   uint32_t *ki = keys, *vi = vals, *ko = keys_tmp, *vo = vals_tmp;
   for (int shift = 0; shift < bits; shift += 8) {
     uint32_t* kw = shift + 8 < bits || keep_keys ? ko : nullptr;
-    if (shift > 0 || !hist0) k_hist<<<plan.n_tiles, kSortThreads, 0, st>>>(ki, d_tiles, shift, hist);
+    if (shift > 0) k_hist<<<plan.n_tiles, kSortThreads, 0, st>>>(ki, d_tiles, shift, hist);
     if (plan.max_seg_tiles <= kFusedTiles) {
       k_scatter<true><<<plan.n_tiles, kSortThreads, 0, st>>>(ki, vi, kw, vo, d_tiles, d_segs, hist, shift);
     } else {

@@ -212,8 +212,6 @@ __device__ inline float rule_s2(float3 q, float zx, float zy, float zz, float& d
   return fmaf(dz, dz, fmaf(dy, dy, dx * dx));
 }
 
-__device__ inline int cell_of(float v, double inv_cell) { return (int)floor((double)v * inv_cell); }
-
 // 10-bit-per-axis Morton interleave.
 __device__ inline uint32_t spread10(uint32_t v) {
   v &= 0x3ffu;

@@ -126,7 +126,7 @@ constexpr int kSortItems = 8;
 constexpr int kSortTile = kSortThreads * kSortItems;
 // Segments of at most this many elements are sorted in runs of kSortTile, all digits in one launch, and the runs of a
 // segment of several are merged by a second.  Larger ones take two launches per digit.  The merge reads a segment's
-// keys once per run and searches every other run: 12 segments of 16,000 elements 12.8 + 12 us, and 28 of 30,000 18 + 55,
+// keys once per run (four times up to 128 runs, whose workgroups it splits) and searches every other run: 12 segments of 16,000 elements 12.8 + 12 us, and 28 of 30,000 18 + 55,
 // where the tiles take 63.
 constexpr int kMergeMax = 16384;
 
@@ -181,13 +181,12 @@ struct SortTables {
 // ---------------------------------------------------------------- launchers
 // Each returns hipSuccess or the first HIP error.  All run on `st`.
 
-// Digit passes of the tiled segments, over key bits [0, bits).  hist0: the tiles' counts of digit 0 are in
-// `hist` already.  keep_keys: the sorted keys are wanted too, not only the values.  The result ends in (keys, vals)
-// or, for an odd number of digits, in (keys_tmp, vals_tmp):
-// sort_ends_in_tmp(bits).
+// Digit passes of the tiled segments, over key bits [0, bits); the tiles' counts of digit 0 are in `hist` already.
+// keep_keys: the sorted keys are wanted too, not only the values.  The result ends in (keys, vals) or, for an odd number
+// of digits, in (keys_tmp, vals_tmp): sort_ends_in_tmp(bits).
 hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp,
                              uint32_t* hist, const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan,
-                             int bits, bool hist0, bool keep_keys, hipStream_t st);
+                             int bits, bool keep_keys, hipStream_t st);
 // Merges the sorted runs of the segments of several, from (keys, vals) to (out_keys, out_vals); out_keys may be null.
 hipError_t launch_merge(const uint32_t* keys, const uint32_t* vals, const SortTile* d_pieces, const SortSeg* d_segs,
                         const SortPlan& plan, uint32_t* out_keys, uint32_t* out_vals, hipStream_t st);

@@ -604,7 +604,7 @@ __device__ __forceinline__ int solve_sparse(const SolveArgs& a, const ProbSys& S
   if (t == 0) *bad = 0;
   __syncthreads();
   const int nf = local[0], n_off = local[1], n = 6 * nf;
-  // (index arithmetic on the one LDS array; no pointers of their own into it)
+  // offsets of the plan's pieces in `local`
   const int o_order = kSparseHeader, o_col = o_order + nf, o_upd = o_col + nf + 1, o_row = o_upd + nf + 1;
   const int o_cols = o_row + n_off, o_list = o_cols + n_off;
   double* rhs = L + 36 * (nf + n_off);

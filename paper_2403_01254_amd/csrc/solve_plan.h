@@ -16,32 +16,16 @@ constexpr int kLdsSystem = 128;            // unknowns of the largest system who
 constexpr size_t kSparseLds = 148 * 1024;  // blocks, right side, a column's products and the plan
 constexpr int kSparseMaxFrames = 512;
 
-// Words of a plan (16 bits each), in this order.  Block ids: p for the diagonal block of column p, then n_frames + o
-// for the off-diagonal block o in column order; `row` and `col` are positions in the order.
-struct SparsePlanView {
-  int n_frames, n_off, n_upd, rows_max;  // header (rows_max: most block rows below a diagonal block)
-  const uint16_t *order, *col_ptr, *upd_ptr, *row, *col, *upd;  // upd: 3 words each: off-diagonal i, k, target id
-};
+// Words of a plan (16 bits each): n frames, off-diagonal blocks, updates, most block rows below a diagonal block; the
+// order; for each column its first off-diagonal block and its first update (n + 1 each); the off-diagonal blocks' rows,
+// then their columns; 3 words an update: off-diagonal i, k, target id.  Block ids: p for the diagonal block of column p,
+// then n + o for the off-diagonal block o in column order; rows and columns are positions in the order.
 constexpr int kSparseHeader = 4;
 #if defined(__HIP__) || defined(__HIPCC__)
 #define RKHSBA_HD __host__ __device__
 #else
 #define RKHSBA_HD
 #endif
-RKHSBA_HD inline SparsePlanView sparse_view(const uint16_t* w) {
-  SparsePlanView v;
-  v.n_frames = w[0];
-  v.n_off = w[1];
-  v.n_upd = w[2];
-  v.rows_max = w[3];
-  v.order = w + kSparseHeader;
-  v.col_ptr = v.order + v.n_frames;
-  v.upd_ptr = v.col_ptr + v.n_frames + 1;
-  v.row = v.upd_ptr + v.n_frames + 1;
-  v.col = v.row + v.n_off;
-  v.upd = v.col + v.n_off;
-  return v;
-}
 RKHSBA_HD inline int sparse_words(int n_frames, int n_off, int n_upd) {
   return kSparseHeader + 3 * n_frames + 2 + 2 * n_off + 3 * n_upd;
 }

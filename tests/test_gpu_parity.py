@@ -533,11 +533,9 @@ def chain_of_copies(n_frames, n_points=400, seed=9):
 
 @pytest.mark.parametrize("n_frames", [40, 90])
 def test_gauss_newton_step_matches_host_solve_large_system(rk, n_frames):
-    """One Gauss-Newton step on 40 frames (a 234-unknown system, several
-    Cholesky panels with a ragged last one) or 90 frames (534 unknowns: the
-    first panels too tall for the column-major panel in LDS) equals the step
-    computed on the host from the library's own H and b (numpy solve, scipy
-    SE(3) exp)."""
+    """One Gauss-Newton step on 40 frames (a 234-unknown system) or 90 frames
+    (534 unknowns), both block-sparse, equals the step computed on the host
+    from the library's own H and b (numpy solve, scipy SE(3) exp)."""
     import scipy.linalg
     if n_frames == 40:
         p = scenes.lidar(4, n_frames=40, n_points=2000, n_neighbours=4, spacing=3.125)

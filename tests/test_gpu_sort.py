@@ -1,5 +1,5 @@
-"""Voxel and binning sorts at the sizes where their route changes: one workgroup of 512 x 4, 1024 x 8 or
-1024 x 16 elements in LDS, tiles with fused histogram sums (up to 64 tiles of 2,048), tiles with scanned
+"""Voxel and binning sorts at the sizes where their route changes: one run of 2,048 elements in LDS, runs and
+a merge (up to 16,384 elements), tiles with fused histogram sums (up to 64 tiles of 2,048), tiles with scanned
 histograms.  Cell keys and their stable order are compared with the oracle's bit for bit; a binning that lost
 or repeated a source point would change the per-source pair counts."""
 import numpy as np
