@@ -282,7 +282,10 @@ __global__ __launch_bounds__(kLanes) void k_sweep_dense(PairArgs a) {
     uint32_t nj = 0;
     bool npad = true;
     auto load_row = [&](Op& o, uint32_t j, int sub) __attribute__((always_inline)) {
-      o.load(trow + (int64_t)(uint32_t)__shfl((int)j, 16 * sub + s, 64) * Op::ROWB, g);
+      // (__shfl forms the lane's byte address anew, 2 of a sub-tile's 65 vector instructions in the loss sweep: at 5e9
+      // pairs a sweep, 64 dimensions fp8 0.98 of the staged sweep's speed with it and 0.99 without, FP32 at 6 cells 0.99
+      // and 1.00)
+      o.load(trow + (int64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(4 * s + 64 * sub, (int)j) * Op::ROWB, g);
     };
     uint32_t left = 0;  // candidates from the fetched tile on (0: none fetched)
     for (uint32_t nb = 0; left > 0 || nb < total;) {
