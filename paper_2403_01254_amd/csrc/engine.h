@@ -219,6 +219,7 @@ struct SetLayout {
   std::vector<int> ids;             // problem ids, in item order
   std::vector<int32_t> edge_key;    // pass size, problem ids, edge lists, fixed, n_iter (change detection)
   uint64_t gen = 0;                 // pool generation the tables were built for
+  uint64_t failures = 0;            // of the engine's prepare() calls when the layout was made
   int n_prob = 0, n_max = 0, E = 0;
   int64_t n_entries = 0;
   int n_pass_total = 0, n_fin_total = 0, bin_bits = 3;
@@ -433,6 +434,7 @@ class Engine {
   Arena* arena_ = nullptr;
   const uint32_t* sorted_v_ = nullptr;
   uint64_t scratch_gen_ = 0;  // bumped when a scratch buffer moves
+  uint64_t failures_ = 0;     // prepare() calls that ended in an error, perhaps without some scratch buffer
 
   std::vector<hipEvent_t> event_pool_;
 };

@@ -14,6 +14,7 @@
 namespace rkhsba {
 
 void throw_hip(hipError_t e, const char* what) {
+  (void)hipGetLastError();  // it is reported here, not by the next call's first launch
   throw Fail{e == hipErrorOutOfMemory ? RKHSBA_ENOMEM : RKHSBA_EDEVICE,
              std::string(what) + ": " + hipGetErrorString(e)};
 }
@@ -923,8 +924,15 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
     key.push_back(it.p->kc_version);
     key.insert(key.end(), it.edges, it.edges + 2 * it.E);
   }
-  if (key == lay.edge_key && !lay.sys.empty() && !arena_) return;
+  if (key == lay.edge_key && !lay.sys.empty() && lay.failures == failures_ && !arena_) return;
   lay.drop_graph();
+  lay.sys.clear();  // from here on the tables are neither the old ones nor, until the end, the new ones
+  // A scratch buffer that cannot grow is lost: after an error every layout is made again, and with it the scratch.
+  struct Watch {
+    uint64_t& failures;
+    bool done = false;
+    ~Watch() { failures += done ? 0 : 1; }
+  } watch{failures_};
 
   int E_total = 0;
   for (const SetItem& it : items) E_total += it.E;
@@ -1202,6 +1210,8 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
   lay.c_positive = positive && !items.empty();
   lay.h_total = h_total;
   lay.v_total = v_total;
+  lay.failures = failures_;
+  watch.done = true;
 }
 
 // ---------------------------------------------------------------- launches
