@@ -258,8 +258,8 @@ void Engine::send(const std::vector<Upload>& up, hipStream_t s) {
 
 // One launch and one wait for all pieces that fit the pinned buffer together.  The others first: a block in a copy of
 // its own (20 us to pageable memory; H of 8 frames is 18 KB), and spaced items through the buffer, as many as fit at a
-// time (11 us), since a two-dimensional copy moves a row at a time.  Losses of 1,025 small edges 170 us so, 14 ms in two
-// such copies, 250 in one copy of all 93 values of every edge; 2,500 edges 360 us, 34 ms, 490.
+// time (11 us), since a two-dimensional copy moves a row at a time.  Losses of 1,025 small edges 170 us so, 14 ms in
+// two such copies, 250 in one copy of all 93 values of every edge; 2,500 edges 360 us, 34 ms, 490.
 void Engine::receive(const std::vector<Download>& dn, hipStream_t s) {
   std::vector<Download> in;  // of the last launch
   size_t total = 0;
@@ -286,8 +286,9 @@ void Engine::receive(const std::vector<Download>& dn, hipStream_t s) {
     } else {
       const size_t most = kGetBytes / d.item;
       for (size_t c = 0; c < d.count; c += most) {
-        const Download part{static_cast<uint8_t*>(d.dst) + c * d.item, static_cast<const uint8_t*>(d.src) + c * d.stride,
-                            d.item, std::min(most, d.count - c), d.stride};
+        const Download part{static_cast<uint8_t*>(d.dst) + c * d.item,
+                            static_cast<const uint8_t*>(d.src) + c * d.stride, d.item, std::min(most, d.count - c),
+                            d.stride};
         fetch(&part, 1);
       }
     }
@@ -1042,8 +1043,8 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
       }
     }
     // systems too large for a dense triangle in LDS: a sparse plan, where its blocks fit.  It depends on the edges and
-    // the fixed frame alone and stays with the problem (64 frames take 0.05 ms to plan, 512 ten times that), while a set's
-    // layout is made anew whenever a problem joins or leaves it.
+    // the fixed frame alone and stays with the problem (64 frames take 0.05 ms to plan, 512 ten times that), while a
+    // set's layout is made anew whenever a problem joins or leaves it.
     S.plan0 = -1;
     if (S.n > kLdsSystem && it.n_iter > 0 && S.n / 6 <= kSparseMaxFrames) {
       std::vector<int32_t> pkey(it.edges, it.edges + 2 * it.E);
@@ -1053,7 +1054,8 @@ void Engine::prepare(SetLayout& lay, const std::vector<SetItem>& items) {
         auto frame = [&](int k) { return it.fixed >= 0 && k >= it.fixed ? k + 1 : k; };
         std::vector<uint8_t> adj((size_t)nf * nf, 0);
         for (int r = 0; r < nf; ++r)
-          for (int c = 0; c < nf; ++c) adj[(size_t)r * nf + c] = r != c && !blk[(size_t)frame(r) * K + frame(c)].empty();
+          for (int c = 0; c < nf; ++c)
+            adj[(size_t)r * nf + c] = r != c && !blk[(size_t)frame(r) * K + frame(c)].empty();
         p->plan = sparse_plan(nf, std::move(adj));
         p->plan_key = std::move(pkey);
       }

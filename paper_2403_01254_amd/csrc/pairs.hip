@@ -85,10 +85,10 @@ __device__ inline void for_each_range(const FrameInfo& T, const int4* __restrict
 // points with the 8 best kept 904 and 173 (with the cheaper list of TopK).
 constexpr int kLocalRanges = 12;
 template <bool PERM, typename Body>
-__device__ __forceinline__ void local_walk(const FrameInfo& T, const int4* __restrict__ rows, const uint32_t* __restrict__ xtab,
-                                  const KConst& kc, float3 q, bool valid, int64_t lrow,
-                                  const float4* __restrict__ pts, const int32_t* __restrict__ perm,
-                                  uint2* __restrict__ slots, Body&& body) {
+__device__ __forceinline__ void local_walk(const FrameInfo& T, const int4* __restrict__ rows,
+                                           const uint32_t* __restrict__ xtab, const KConst& kc, float3 q, bool valid,
+                                           int64_t lrow, const float4* __restrict__ pts,
+                                           const int32_t* __restrict__ perm, uint2* __restrict__ slots, Body&& body) {
   constexpr int U = 4;
   const double inv = kc.inv_cell, cell = kc.cell, reach = kc.reach;
   const double qx = q.x, qy = q.y, qz = q.z;

@@ -126,8 +126,8 @@ constexpr int kSortItems = 8;
 constexpr int kSortTile = kSortThreads * kSortItems;
 // Segments of at most this many elements are sorted in runs of kSortTile, all digits in one launch, and the runs of a
 // segment of several are merged by a second.  Larger ones take two launches per digit.  The merge reads a segment's
-// keys once per run (four times up to 128 runs, whose workgroups it splits) and searches every other run: 12 segments of 16,000 elements 12.8 + 12 us, and 28 of 30,000 18 + 55,
-// where the tiles take 63.
+// keys once per run (four times up to 128 runs, whose workgroups it splits) and searches every other run: 12 segments
+// of 16,000 elements 12.8 + 12 us, and 28 of 30,000 18 + 55, where the tiles take 63.
 constexpr int kMergeMax = 16384;
 
 // How the segments of one launch are sorted.
@@ -182,8 +182,8 @@ struct SortTables {
 // Each returns hipSuccess or the first HIP error.  All run on `st`.
 
 // Digit passes of the tiled segments, over key bits [0, bits); the tiles' counts of digit 0 are in `hist` already.
-// keep_keys: the sorted keys are wanted too, not only the values.  The result ends in (keys, vals) or, for an odd number
-// of digits, in (keys_tmp, vals_tmp): sort_ends_in_tmp(bits).
+// keep_keys: the sorted keys are wanted too, not only the values.  The result ends in (keys, vals) or, for an odd
+// number of digits, in (keys_tmp, vals_tmp): sort_ends_in_tmp(bits).
 hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp,
                              uint32_t* hist, const SortTile* d_tiles, const SortSeg* d_segs, const SortPlan& plan,
                              int bits, bool keep_keys, hipStream_t st);

@@ -166,8 +166,9 @@ struct SmallShared {
   int bad;                                        // a pivot was not positive
 };
 
-// 1 / d, correctly rounded: the hardware estimate, two Newton steps, and a last one from the exact residual, a division's
-// own chain without the scaling of its operands' exponents.  The ends of the range, where a step could leave it, divide.
+// 1 / d, correctly rounded: the hardware estimate, two Newton steps, and a last one from the exact residual, a
+// division's own chain without the scaling of its operands' exponents.  The ends of the range, where a step could
+// leave it, divide.
 __device__ inline double reciprocal(double d) {
   if (!(d > 1e-290 && d < 1e290)) return 1.0 / d;
   double r = __builtin_amdgcn_rcp(d);
@@ -577,21 +578,21 @@ __device__ __forceinline__ void solve_blocked(const ProbSys& S, const SolveArgs&
 //
 // As solve_small, one frame's 6 columns a step and -b as one more row, but only the blocks that the plan holds, and
 // the system assembled from the edges' values straight into them.  A chain of latencies: 63 steps of 2 us and their
-// way back for 64 LiDAR frames with 6 edges each, 0.18 ms, where the blocked dense elimination took 0.52 (12 panels
+// way back for 64 LiDAR frames with 6 edges each, 0.20 ms, where the blocked dense elimination took 0.52 (12 panels
 // of 32 columns through global memory) and the assembly of H before it 0.01.
 //
-// Its order is the plan's, so its last bits are not the dense elimination's.  Where the system leaves a direction nearly
-// free, they would become poses and pair counts: a pivot that elimination leaves below kWellPosed of its diagonal entry
-// sends the system to the dense elimination.  LiDAR maps of 23 to 64 frames have smallest pivots of 3e-3 and more of
-// their diagonal (poses then agree to 1e-13), depth frames in front of one wall 3e-6 and less.
+// Its order is the plan's, so its last bits are not the dense elimination's.  Where the system leaves a direction
+// nearly free, they would become poses and pair counts: a pivot that elimination leaves below kWellPosed of its
+// diagonal entry sends the system to the dense elimination.  LiDAR maps of 23 to 64 frames have smallest pivots of
+// 3e-3 and more of their diagonal (poses then agree to 1e-11), depth frames in front of one wall 3e-6 and less.
 constexpr double kWellPosed = 1e-3;
 
 struct SparseShared {
   double d[kSparseLds / sizeof(double)];
 };
 
-// Solution in y (global, n, in frame order).  0: moved; 1: no pair touches a free frame; -1: a pivot is too small, for the
-// dense elimination to look at (the same in every thread).
+// Solution in y (global, n, in frame order).  0: moved; 1: no pair touches a free frame; -1: a pivot is too small,
+// for the dense elimination to look at (the same in every thread).
 __device__ __forceinline__ int solve_sparse(const SolveArgs& a, const ProbSys& S, SparseShared& sh, double* __restrict__ red,
                             int* __restrict__ bad, double* __restrict__ y) {
   const int t = threadIdx.x;
@@ -609,7 +610,7 @@ __device__ __forceinline__ int solve_sparse(const SolveArgs& a, const ProbSys& S
   const int o_cols = o_row + n_off, o_list = o_cols + n_off;
   double* rhs = L + 36 * (nf + n_off);
   double* diag = rhs + n;                       // the diagonal before the elimination
-  double* T = diag + n;                         // a column's rows before the division by the pivots; last: the right side
+  double* T = diag + n;  // a column's rows before the division by the pivots; last: the right side
   double* dl = T + 6 * (6 * (int)local[3] + 1);  // the diagonal block's L
   double tr = 0.0;
   for (int e = t; e < 36 * (nf + n_off); e += kSolveThreads) {

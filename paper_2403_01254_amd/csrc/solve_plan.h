@@ -17,9 +17,9 @@ constexpr size_t kSparseLds = 148 * 1024;  // blocks, right side, a column's pro
 constexpr int kSparseMaxFrames = 512;
 
 // Words of a plan (16 bits each): n frames, off-diagonal blocks, updates, most block rows below a diagonal block; the
-// order; for each column its first off-diagonal block and its first update (n + 1 each); the off-diagonal blocks' rows,
-// then their columns; 3 words an update: off-diagonal i, k, target id.  Block ids: p for the diagonal block of column p,
-// then n + o for the off-diagonal block o in column order; rows and columns are positions in the order.
+// order; for each column its first off-diagonal block and its first update (n + 1 each); the off-diagonal blocks'
+// rows, then their columns; 3 words an update: off-diagonal i, k, target id.  Block ids: p for the diagonal block of
+// column p, then n + o for the off-diagonal block o in column order; rows and columns are positions in the order.
 constexpr int kSparseHeader = 4;
 #if defined(__HIP__) || defined(__HIPCC__)
 #define RKHSBA_HD __host__ __device__

@@ -11,10 +11,10 @@
 // Spread passes.  A pass whose sources lie in a few places far apart (a jump of the Morton order, isolated points)
 // walks the rows of a box that spans them all, alone for many times a compact pass's duration, at the end of the
 // launch.  A first small kernel (k_split) finds such passes and lists them as items, one per quad of the pass's
-// sources (one per source where a quad is spread itself); the sweep's first workgroups take the items, the others the
-// remaining passes in their order.  An item walks only the row batches that its own sources are near, and only the
-// tiles with a candidate that they reach.  What it leaves out adds exact zeros to its sources' moments, and what it
-// keeps has the pass's own order, so the moments are the same bit for bit, whether a pass is split or not.
+// sources (one per source where a quad is spread itself); the sweep's first workgroups take items (kFrontItems), the
+// others the remaining passes in their order.  An item walks only the row batches that its own sources are near, and
+// only the tiles with a candidate that they reach.  What it leaves out adds exact zeros to its sources' moments, and
+// what it keeps has the pass's own order, so the moments are the same bit for bit, whether a pass is split or not.
 // Sweeps with staged rows and whole passes -> now: 8 x 30,000 points, 23 dimensions 995 -> 844 us; 6 x 17,001, 64
 // dimensions 552 -> 402; 5 x 12,345 fp8 161 -> 102; 4 x 8,000, 20 dimensions 101 -> 70; 3 x 9,000 bfloat16 74 -> 48.
 // Small launches are bound by the candidates of their longest pass, one after another (about 1.5 us per 64), large
@@ -129,11 +129,11 @@ __global__ __launch_bounds__(256) void k_split(PairArgs a) {
 }
 
 // Items come first, but no more of them than half of the wavefronts that the chip holds (256 CUs of 16): the first
-// passes behind them then start while places are free, spread evenly over the SIMDs.  Behind an item list that fills the
-// chip they started where the short items ended first, and a dense edge's long passes ended up on few SIMDs: 8 x 30,000
-// points, 64 dimensions, 6 cells per r_c (2,837 items, half of the pairs in the first 1,875 passes) FP32 3.17 -> 2.55 ms,
-// bfloat16 1.45 -> 1.24, fp8 1.12 -> 0.98; with at most 1,024 items first 3.14, 1.45 and 1.12; no items first loses
-// 0.15 ms on fp8 at 4 and 8 cells.  Lists of up to kFrontItems are as they were.
+// passes behind them then start while places are free, spread evenly over the SIMDs.  Behind an item list that fills
+// the chip they started where the short items ended first, and a dense edge's long passes ended up on few SIMDs: 8 x
+// 30,000 points, 64 dimensions, 6 cells per r_c (2,837 items, half of the pairs in the first 1,875 passes) FP32 3.17
+// -> 2.55 ms, bfloat16 1.45 -> 1.24, fp8 1.12 -> 0.95; with at most 1,024 items first 3.14, 1.45 and 1.12; no items
+// first loses 0.15 ms on fp8 at 4 and 8 cells.  Lists of up to kFrontItems are as they were.
 constexpr uint32_t kFrontItems = 2048;
 
 // CM: inner products as computed (0), negative ones clamped to 0 (1), or known to be positive (2: the pair count
@@ -282,9 +282,9 @@ __global__ __launch_bounds__(kLanes) void k_sweep_dense(PairArgs a) {
     uint32_t nj = 0;
     bool npad = true;
     auto load_row = [&](Op& o, uint32_t j, int sub) __attribute__((always_inline)) {
-      // (__shfl forms the lane's byte address anew, 2 of a sub-tile's 65 vector instructions in the loss sweep: at 5e9
-      // pairs a sweep, 64 dimensions fp8 0.98 of the staged sweep's speed with it and 0.99 without, FP32 at 6 cells 0.99
-      // and 1.00)
+      // (__shfl forms the lane's byte address anew, 2 of a sub-tile's 65 vector instructions in the loss sweep: at
+      // 5e9 pairs a sweep, 64 dimensions fp8 0.98 of the staged sweep's speed with it and 0.99 without, FP32 at 6
+      // cells 0.99 and 1.00)
       o.load(trow + (int64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(4 * s + 64 * sub, (int)j) * Op::ROWB, g);
     };
     uint32_t left = 0;  // candidates from the fetched tile on (0: none fetched)
