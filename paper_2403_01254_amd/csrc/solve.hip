@@ -583,9 +583,12 @@ __device__ __forceinline__ void solve_blocked(const ProbSys& S, const SolveArgs&
 //
 // Its order is the plan's, so its last bits are not the dense elimination's.  Where the system leaves a direction
 // nearly free, they would become poses and pair counts: a pivot that elimination leaves below kWellPosed of its
-// diagonal entry sends the system to the dense elimination.  LiDAR maps of 23 to 64 frames have smallest pivots of
-// 3e-3 and more of their diagonal (poses then agree to 1e-11), depth frames in front of one wall 3e-6 and less.
-constexpr double kWellPosed = 1e-3;
+// diagonal entry sends the system to the dense elimination.  LiDAR maps of 23 to 64 frames have smallest pivots of 3e-3
+// and more of their diagonal (poses then agree to 1e-11), open chains of 24 to 48 clouds up to 25 m from their frames'
+// origins 6e-5 to 3e-4 (1e-10, mostly 1e-12), depth frames in front of one wall and clouds along a line 6e-6 and less.
+// Handed over, 24 to 64 such frames take the dense elimination's time (219 us an iteration of 24 small clouds before
+// and so, 94 by blocks): the small pivot comes early.
+constexpr double kWellPosed = 1e-5;
 
 struct SparseShared {
   double d[kSparseLds / sizeof(double)];
